@@ -896,8 +896,8 @@ void build_group_lists(dpx_plan* p, const std::vector<int>& ids, std::vector<Gro
     for (int i : ids) {
       const Design& d = p->designs[i];
       const int64_t per = static_cast<int64_t>(d.K) * d.N * d.N;
-      dhs.push_back({d.dh_part, d.h_off, per, d.nslots});
-      nb.push_back(static_cast<int>((per + dpx::kGroupThreads - 1) / dpx::kGroupThreads));
+      dhs.push_back(dpx::dh_task(d.dh_part, d.h_off, per, d.nslots));
+      nb.push_back(dpx::dh_blocks(per, d.nslots));
     }
     add_simple_group(bwd, GK_DH, dhs, nb, blob);
   }

@@ -183,7 +183,10 @@ struct DhTask {
   int64_t h_off;             // offset of the design's heights in the packed dL/dh
   int64_t per;               // K N N
   int nslots;
+  int lanes;                 // threads of a slot group (see dh_reduce_body)
 };
+DhTask dh_task(const float* part, int64_t h_off, int64_t per, int nslots);
+int dh_blocks(int64_t per, int nslots);  // blocks of the reduction of one design
 
 constexpr int kGroupThreads = 256;  // threads per block of the grouped binning / reduction
 
@@ -253,8 +256,7 @@ hipError_t launch_loss_sum(const double* per_wl, double* loss, int W, hipStream_
 constexpr int kStaticLossMaxWl = 65536;
 // device address of that array on the current device (looked up once per device)
 hipError_t static_loss_scratch(double** out);
-hipError_t launch_dh_reduce(const float* part, float* dh, int nchunk, int64_t per_chunk,
-                            hipStream_t s);
+hipError_t launch_dh_reduce(const float* part, float* dh, int nslots, int64_t per, hipStream_t s);
 hipError_t launch_fill_zero(float* p, int64_t n, hipStream_t s);
 // adds the number of NaN and infinite values among x[0..n) to *count (integer atomics)
 hipError_t launch_count_nonfinite(const float* x, int64_t n, unsigned* count, hipStream_t s);

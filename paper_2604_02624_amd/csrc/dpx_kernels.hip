@@ -146,26 +146,84 @@ hipError_t static_loss_scratch(double** out) {
   return hipSuccess;
 }
 
-__device__ __forceinline__ void dh_reduce_body(const float* __restrict__ part, float* __restrict__ dh,
-                                               int nchunk, int64_t per_chunk, int64_t i) {
-  if (i >= per_chunk) return;
-  double s = 0.0;
-  for (int c = 0; c < nchunk; ++c) s += part[c * per_chunk + i];
-  dh[i] = static_cast<float>(s);
+// Sum of the gradient slots in double, in an order fixed by the sizes alone.  Bound by the slots'
+// traffic (128 MB for 2048 slots of a two-layer 64 x 64 design) and, where one thread walks all
+// slots of an element, by one load latency per slot: that form took 794 us at 4096 wavelengths of a
+// three-layer 64 x 64 design and 64 us (2.6 TB/s) at 128 slots of five 256 x 256 layers.  So a
+// block of 256 threads takes LANES x 4 elements with 256 / LANES groups of threads, each summing
+// every (256 / LANES)-th slot with 16-byte loads, four in flight; the groups' sums are added in
+// order.
+template <int LANES>
+__device__ __forceinline__ void dh_reduce_body(const float* __restrict__ part, float* __restrict__ dh, int nslots,
+                                               int64_t per, int64_t block, double* sh) {
+  constexpr int G = kGroupThreads / LANES;
+  const int g = threadIdx.x / LANES, l = threadIdx.x % LANES;
+  const int64_t first = block * (LANES * 4);
+  const int64_t i = first + l * 4;  // per is a multiple of four (K N N with N even)
+  double s[4] = {0.0, 0.0, 0.0, 0.0};
+  if (i < per) {
+    int c = g;
+    for (; c + 3 * G < nslots; c += 4 * G) {
+      float4 v[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const float4*>(part + (c + u * G) * per + i);
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        s[0] += v[u].x;
+        s[1] += v[u].y;
+        s[2] += v[u].z;
+        s[3] += v[u].w;
+      }
+    }
+    for (; c < nslots; c += G) {
+      const float4 v = *reinterpret_cast<const float4*>(part + c * per + i);
+      s[0] += v.x;
+      s[1] += v.y;
+      s[2] += v.z;
+      s[3] += v.w;
+    }
+  }
+#pragma unroll
+  for (int u = 0; u < 4; ++u) sh[g * (LANES * 4) + l * 4 + u] = s[u];
+  __syncthreads();
+  const int e = threadIdx.x;
+  if (e < LANES * 4 && first + e < per) {
+    double t = 0.0;
+#pragma unroll
+    for (int k = 0; k < G; ++k) t += sh[k * (LANES * 4) + e];
+    dh[first + e] = static_cast<float>(t);
+  }
 }
 
-__global__ void dh_reduce_kernel(const float* __restrict__ part, float* __restrict__ dh, int nchunk,
-                                 int64_t per_chunk) {
-  dh_reduce_body(part, dh, nchunk, per_chunk, static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x);
+// 16 groups of 16 threads where 64-thread groups would leave most CUs without a block and there
+// are slots enough to share, else 4 groups of 64
+constexpr int kDhNarrow = 16, kDhWide = 64;
+static int dh_lanes(int64_t per, int nslots) {
+  return per < 512LL * kDhWide * 4 && nslots >= 4 * (kGroupThreads / kDhNarrow) ? kDhNarrow : kDhWide;
+}
+int dh_blocks(int64_t per, int nslots) {
+  const int lanes = dh_lanes(per, nslots);
+  return static_cast<int>((per + lanes * 4 - 1) / (lanes * 4));
+}
+
+template <int LANES>
+__global__ void __launch_bounds__(kGroupThreads)
+dh_reduce_kernel(const float* __restrict__ part, float* __restrict__ dh, int nslots, int64_t per) {
+  __shared__ double sh[kGroupThreads * 4];
+  dh_reduce_body<LANES>(part, dh, nslots, per, blockIdx.x, sh);
 }
 
 // grouped: task = one design's gradient slots -> its dL/dh in the packed output
-__global__ void dh_group_kernel(GroupArgs g, float* __restrict__ dl_dh) {
+__global__ void __launch_bounds__(kGroupThreads) dh_group_kernel(GroupArgs g, float* __restrict__ dl_dh) {
+  __shared__ double sh[kGroupThreads * 4];
   const int ti = group_task(g, blockIdx.x);
   const DhTask& t = static_cast<const DhTask*>(g.tasks)[ti];
-  const int local = static_cast<int>(blockIdx.x) - g.block0[ti];
-  dh_reduce_body(t.part, dl_dh + t.h_off, t.nslots, t.per,
-                 static_cast<int64_t>(local) * blockDim.x + threadIdx.x);
+  const int64_t local = static_cast<int>(blockIdx.x) - g.block0[ti];
+  if (t.lanes == kDhNarrow) dh_reduce_body<kDhNarrow>(t.part, dl_dh + t.h_off, t.nslots, t.per, local, sh);
+  else dh_reduce_body<kDhWide>(t.part, dl_dh + t.h_off, t.nslots, t.per, local, sh);
+}
+DhTask dh_task(const float* part, int64_t h_off, int64_t per, int nslots) {
+  return {part, h_off, per, nslots, dh_lanes(per, nslots)};
 }
 
 // ------------------------------------------------------------------------------------------
@@ -483,11 +541,12 @@ hipError_t launch_loss_sum(const double* per_wl, double* loss, int W, hipStream_
   return hipGetLastError();
 }
 
-hipError_t launch_dh_reduce(const float* part, float* dh, int nchunk, int64_t per_chunk,
-                            hipStream_t s) {
-  const int th = 256;
-  dh_reduce_kernel<<<static_cast<unsigned>((per_chunk + th - 1) / th), th, 0, s>>>(part, dh, nchunk,
-                                                                                 per_chunk);
+hipError_t launch_dh_reduce(const float* part, float* dh, int nslots, int64_t per, hipStream_t s) {
+  const unsigned blocks = static_cast<unsigned>(dh_blocks(per, nslots));
+  if (dh_lanes(per, nslots) == kDhNarrow)
+    dh_reduce_kernel<kDhNarrow><<<blocks, kGroupThreads, 0, s>>>(part, dh, nslots, per);
+  else
+    dh_reduce_kernel<kDhWide><<<blocks, kGroupThreads, 0, s>>>(part, dh, nslots, per);
   return hipGetLastError();
 }
 
