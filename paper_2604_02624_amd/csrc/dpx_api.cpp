@@ -143,7 +143,8 @@ struct dpx_plan {
   PassTotals totals[DPX_PASS_COUNT];
   dpx_opts opts;
   int device = 0;
-  std::map<int, float2*> twiddles;
+  std::map<int, float2*> twiddles;       // tables inside table_allocs (tw_key, col_key)
+  std::vector<float2*> table_allocs;
   std::map<int, float2*> dft;      // matrix-core column pass: key M * 4 + pad
   // grouped schedule (opts.schedule): every pass of every design as one launch per transform
   // length, mode and variant; task arrays in one device buffer
@@ -294,7 +295,7 @@ void layout_design(const dpx_design& src, const dpx_opts& o, Design& d) {
   d.w_per_block = wpb;
   d.slots_per_lane = (chunk + wpb - 1) / wpb;
   d.nslots = d.lanes * d.slots_per_lane;
-  d.col_variant = o.force_variant >= 0 ? o.force_variant : dpx::default_col_variant(d.M);
+  d.col_variant = o.force_variant >= 0 ? o.force_variant : dpx::default_col_variant(d.M, d.pad, chunk);
   // the band-limited spectrum is applied by the per-element evaluation: the mirrored variants'
   // tile widths without the mirror
   if (src.band_limited && d.col_variant >= 2 && d.col_variant <= 3) d.col_variant -= 2;
@@ -426,6 +427,8 @@ dpx_status check_outputs(dpx_plan* p, std::initializer_list<OutputSpan> outs, hi
 
 // key of a twiddle table in dpx_plan::twiddles
 int tw_key(int M, int plan) { return M * 8 + plan; }
+// key of the split column transforms' table there (radix plans stay below 4)
+int col_key(int M, int pad) { return M * 8 + 4 + pad; }
 
 // the radix plan a column launch runs: the design's, unless its transfer function comes from a
 // source that only plan 0 has (tables, band limit, translated gaps)
@@ -450,6 +453,7 @@ RowArgs row_args(const dpx_plan* p, const Design& d, int w0, int wc, int lane) {
   a.spec = spec_of_lane(d, lane);
   const int64_t nn = static_cast<int64_t>(d.N) * d.N;
   a.ckpt_first = d.ck_first;
+  a.all_columns = d.col_variant == 4 ? 1 : 0;
   if (p->opts.checkpoint_mode == 1) {
     a.ckpt = d.ckpt ? d.ckpt + static_cast<int64_t>(lane) * (d.K - d.ck_first) * d.wl_chunk * nn : nullptr;
     a.ckpt_w_stride = d.wl_chunk;
@@ -537,6 +541,17 @@ dpx_status run_row(dpx_plan* p, const Design& d, int mode, RowArgs a, int row_lo
   return DPX_OK;
 }
 
+// Wavelengths per column block, while that leaves several blocks per CU: two in the staged form (the
+// second one's rows are prefetched while the first is transformed; best of 1, 2, 4, 8 on 4096
+// wavelengths of 512 x 512), four with the split transforms, whose blocks also stage a table (512
+// points, 1024 wavelengths: 647, 620 and 616 us per pass with 2, 4 and 8; 384 points, 512
+// wavelengths: 211, 204, 210)
+int col_wavelengths_per_block(const Design& d, int wc) {
+  const int64_t tiles = static_cast<int64_t>(wc) * (d.M / 8);
+  if (dpx::col_split(d.M, d.pad) && tiles >= 4 * 8192) return 4;
+  return tiles >= 2 * 8192 ? 2 : 1;
+}
+
 ColArgs col_args(const dpx_plan* p, const Design& d, int lane, int layer, int w0, int wc, int in_lo,
                  int in_hi, int out_lo, int out_hi) {
   ColArgs c{};
@@ -560,13 +575,11 @@ ColArgs col_args(const dpx_plan* p, const Design& d, int lane, int layer, int w0
     auto it = p->dft.find(d.M * 4 + d.pad);
     c.dft = it == p->dft.end() ? nullptr : it->second;
   }
-  // two wavelengths per column block (the second one's rows are prefetched while the first
-  // is transformed; measured best of 1, 2, 4, 8 on the large workload) when that still
-  // leaves several blocks per CU
-  c.col_wpb = (static_cast<int64_t>(wc) * (d.M / 8) >= 2 * 8192) ? 2 : 1;
+  c.col_wpb = col_wavelengths_per_block(d, wc);
   const int64_t hs = d.M / 2 + 1;
   c.htab = (d.htab && layer >= 0) ? d.htab + static_cast<int64_t>(d.zslot[layer]) * d.W * hs * hs : nullptr;
-  c.tw = p->twiddles.at(tw_key(d.M, col_plan_of(d, c)));
+  const int plan = col_plan_of(d, c);
+  c.tw = p->twiddles.at(plan == 0 && dpx::col_split(d.M, d.pad) ? col_key(d.M, d.pad) : tw_key(d.M, plan));
   return c;
 }
 
@@ -590,7 +603,12 @@ dpx_status run_col(dpx_plan* p, const Design& d, int lane, int layer, bool conj,
   if (in_lo == 0 && in_hi == d.N && out_lo == 0 && out_hi == d.N)
     t.instance = conj ? DPX_PASS_COL_ADJ_FULL : DPX_PASS_COL_FWD_FULL;
   DPX_TRY(timer_begin(p, s, t));
-  hipError_t e = dpx::launch_col(d.M, d.pad, conj, d.col_variant, col_plan_of(d, c), c, wc, s);
+  // a translated gap evaluates every element, which the 512-point wide tile's three barriers per
+  // wavelength make wait for the slowest of eight wavefronts: 8 columns (five layers of 256 x 256,
+  // 128 wavelengths: 1369 against 1485 us per step)
+  int variant = d.col_variant;
+  if (p->opts.force_variant < 0 && !p->opts.autotune && variant == 3 && (c.sx != 0.0 || c.sy != 0.0) && d.M / d.pad >= 256) variant = 2;
+  hipError_t e = dpx::launch_col(d.M, d.pad, conj, variant, col_plan_of(d, c), c, wc, s);
   if (e != hipSuccess) return fail(DPX_E_DEVICE, "column pass launch failed: %s", hipGetErrorString(e));
   DPX_TRY(timer_end(p, s, t));
   return DPX_OK;
@@ -781,7 +799,7 @@ void add_col_position(dpx_plan* p, const std::vector<ColItem>& items, bool conj,
       const Design& d = p->designs[it.design];
       dpx::ColTask t{};
       t.a = col_args(p, d, 0, it.layer, 0, d.W, it.in_lo, it.in_hi, it.out_lo, it.out_hi);
-      t.gx = d.M / dpx::col_tile_width(d.M, d.col_variant);
+      t.gx = d.M / dpx::col_tile_width(d.M, d.pad, d.col_variant);
       t.nblocks = t.gx * ((d.W + t.a.col_wpb - 1) / t.a.col_wpb);
       tasks.push_back(t);
       nb.push_back(t.nblocks);
@@ -974,6 +992,7 @@ dpx_status run_lds(dpx_plan* p, const Design& d, bool adjoint, const float* h, c
   dpx::LdsArgs a{};
   a.wl = d.d_wl;
   a.tw = p->twiddles.at(tw_key(d.M, 0));
+  a.col_tab = p->twiddles.at(col_key(d.M, d.pad));
   a.zrev = d.d_zrev;
   a.h = h + d.h_off;
   a.u_in = u_in ? reinterpret_cast<const float2*>(u_in) + d.u_off : nullptr;
@@ -1339,7 +1358,11 @@ dpx_status upload_wavelengths(Design& d) {
     tab[w].ca = kTwoPi * d.kappa[w] / lam;
     const double r = md * d.n_m / lam;
     tab[w].q0 = r * r;
-    tab[w].ct = kTwoPi * (d.n_mat[w] - d.n_m) / lam;
+    tab[w].ct = static_cast<float>(kTwoPi * (d.n_mat[w] - d.n_m) / lam);
+    const double half = d.M / 2;
+    int k = static_cast<int>(std::sqrt(std::min(tab[w].q0, half * half + 1.0)));
+    if (static_cast<double>(k) * k >= tab[w].q0) --k;  // q0 = kx^2 is outside the disc
+    tab[w].radius = k;
   }
   if (hipMemcpy(d.d_wl, tab.data(), d.W * sizeof(WlConst), hipMemcpyHostToDevice) != hipSuccess)
     return fail(DPX_E_DEVICE, "copy of the wavelength table failed");
@@ -1418,18 +1441,31 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
     }
     p->bytes += d.bytes;
     if ((st = upload_wavelengths(d)) != DPX_OK) break;
-    // the twiddle tables of every radix plan of the length (a few KB each): the autotuner and
-    // a column pass falling back to plan 0 may use any of them
-    for (int pl = 0; pl < dpx::radix_plan_count(d.M) && st == DPX_OK; ++pl) {
-      if (p->twiddles.count(tw_key(d.M, pl))) continue;
-      std::vector<float2> tw;
-      dpx::build_twiddle_table(d.M, pl, tw);
-      float2* dtw = nullptr;
-      const int64_t tb = static_cast<int64_t>(tw.size()) * 8;
-      if ((st = dev_alloc(&dtw, tb, "twiddles")) != DPX_OK) break;
-      p->twiddles[tw_key(d.M, pl)] = dtw;
-      if (hipMemcpy(dtw, tw.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
-        st = fail(DPX_E_DEVICE, "copy of the twiddle table failed");
+    // the twiddle tables of every radix plan of the length (a few KB each: the autotuner and a
+    // column pass falling back to plan 0 may use any of them) and that of the split column
+    // transforms where the length has them, in one allocation and one copy
+    std::vector<float2> tables;
+    std::vector<std::pair<int, size_t>> parts;  // key, offset
+    auto add_table = [&](int key, auto&& build) {
+      if (p->twiddles.count(key)) return;
+      std::vector<float2> t;
+      build(t);
+      parts.push_back({key, tables.size()});
+      tables.insert(tables.end(), t.begin(), t.end());
+      tables.resize((tables.size() + 31) / 32 * 32, make_float2(0.f, 0.f));  // 256-byte aligned parts
+    };
+    for (int pl = 0; pl < dpx::radix_plan_count(d.M); ++pl)
+      add_table(tw_key(d.M, pl), [&](std::vector<float2>& t) { dpx::build_twiddle_table(d.M, pl, t); });
+    if (dpx::col_split(d.M, d.pad))
+      add_table(col_key(d.M, d.pad), [&](std::vector<float2>& t) { dpx::build_col_table(d.M, d.pad, t); });
+    if (!tables.empty()) {
+      float2* dt = nullptr;
+      const int64_t tb = static_cast<int64_t>(tables.size()) * 8;
+      if ((st = dev_alloc(&dt, tb, "twiddles")) != DPX_OK) break;
+      p->table_allocs.push_back(dt);
+      for (const auto& kv : parts) p->twiddles[kv.first] = dt + kv.second;
+      if (hipMemcpy(dt, tables.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
+        st = fail(DPX_E_DEVICE, "copy of the twiddle tables failed");
         break;
       }
       p->bytes += tb;
@@ -1547,7 +1583,7 @@ dpx_status dpx_plan_destroy(dpx_plan* p) {
     (void)hipEventDestroy(t.stop);
   }
   for (auto& d : p->designs) free_design(d);
-  for (auto& kv : p->twiddles) hipFree(kv.second);
+  for (auto* t : p->table_allocs) hipFree(t);
   for (auto& kv : p->dft) hipFree(kv.second);
   if (p->d_tasks) hipFree(p->d_tasks);
   if (p->d_nonfinite) hipFree(p->d_nonfinite);

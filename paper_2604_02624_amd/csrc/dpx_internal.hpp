@@ -15,8 +15,14 @@ namespace dpx {
 //   q0 = (M dx n_m / lambda)^2              [-]     squared radius of the propagating disc
 //                                                   in units of the frequency grid step
 //   ct = 2 pi (n - n_m) / lambda            [1/m]   phase per metre (gradient)
+//   radius                                  [-]     largest |kx| with kx^2 < q0, at most M / 2: the
+//                                                   spectrum columns that carry anything.  H is zero
+//                                                   on every other column, which is neither written
+//                                                   nor read
 struct WlConst {
-  double rt, ca, q0, ct;
+  double rt, ca, q0;
+  float ct;
+  int radius;
 };
 
 enum RowMode : int {
@@ -34,8 +40,10 @@ enum RowMode : int {
 constexpr int row_pass_kind(int mode) { return 2 + (mode == ROW_ADJ_LAST_U ? ROW_ADJ_LAST : mode); }
 
 // Threads per row-pass block: 512 (eight transforms of 1024) where the registers allow two
-// such blocks per CU next to their LDS, 256 for the register-heavy adjoint middle pass.
-constexpr int row_threads_of_mode(int mode) { return mode == ROW_ADJ_MID ? 256 : 512; }
+// such blocks per CU next to their LDS, 256 for the register-heavy adjoint passes with a gradient
+// (136-168 registers at 512 and 1024 points allow three wavefronts per SIMD, of which blocks of
+// 512 threads could use two).
+constexpr int row_threads_of_mode(int mode) { return mode >= ROW_ADJ_MID ? 256 : 512; }
 // Threads of a row-pass block for P lanes per transform: the mode's count when transforms tile
 // a wavefront; three or so whole transforms (about 256 threads) when one spans wavefronts.
 constexpr int row_threads_for(int P, int mode) {
@@ -63,6 +71,8 @@ struct RowArgs {
   int accumulate;            // dL/dh partials: add to the slot instead of overwriting it
   int no_layer;              // ROW_FWD_FIRST only: u_in passes unchanged (the input plane before
                              // an input gap: no transmission, h not read)
+  int all_columns;           // 1: every spectrum column is written and read (the matrix-core column
+                             // pass does not skip the columns outside the propagating disc)
   int ckpt_first;            // 1: layer 0 has no checkpoint slab (ROW_ADJ_LAST_U rebuilds
                              // u_in t_0(h) from u_in and h)
 };
@@ -70,7 +80,8 @@ struct RowArgs {
 struct ColArgs {
   float2* spec;              // [wc][N][M]
   const WlConst* wl;         // [W] (global w)
-  const float2* tw;          // per-stage twiddle table of the transform length
+  const float2* tw;          // per-stage twiddle table of the transform length, or the table of
+                             // the split column transforms (col_fft.hpp) where they run
   double zrev;               // z / (M dx): revolutions per unit of sqrt(q)
   double sx, sy;             // lateral translation of the gap / (M dx): revolutions per signed
                              // frequency index (0, 0 unless the plan has a misalignment)
@@ -94,6 +105,7 @@ struct ColArgs {
 struct LdsArgs {
   const WlConst* wl;         // [W]
   const float2* tw;          // per-stage twiddle table of the transform length
+  const float2* col_tab;     // table of the column transforms (col_fft.hpp)
   const double* zrev;        // [K] z_l / (M dx)
   const float* h;            // [K][N][N] heights of the design
   const float2* u_in;        // [N][N] or null (unit plane wave)
@@ -105,8 +117,19 @@ struct LdsArgs {
   int K, fov, bin, W;
 };
 
+// Sum of |o|^2 over the b x b bin at o (row stride `stride`), fused multiply-adds in a fixed order
+__device__ __forceinline__ float bin_sum(const float2* __restrict__ o, int stride, int bin) {
+  float s = 0.f;
+  for (int a = 0; a < bin; ++a)
+    for (int b = 0; b < bin; ++b) {
+      const float2 v = o[static_cast<size_t>(a) * stride + b];
+      s = fmaf(v.x, v.x, fmaf(v.y, v.y, s));
+    }
+  return s;
+}
+
 // Intensity of output i of a [w_count][T][T] image set: sum of |o|^2 over the b x b bin of the
-// [w_count][fov][fov] window field (fused multiply-adds in a fixed order)
+// [w_count][fov][fov] window field
 __device__ __forceinline__ void bin_intensity_body(const float2* __restrict__ ofov, float* __restrict__ out,
                                                    int w_count, int fov, int bin, size_t i) {
   const int T = fov / bin;
@@ -115,14 +138,7 @@ __device__ __forceinline__ void bin_intensity_body(const float2* __restrict__ of
   const int w = static_cast<int>(i / (static_cast<size_t>(T) * T));
   const int r = static_cast<int>(i % (static_cast<size_t>(T) * T));
   const int ty = r / T, tx = r % T;
-  const float2* o = ofov + static_cast<size_t>(w) * fov * fov;
-  float s = 0.f;
-  for (int a = 0; a < bin; ++a)
-    for (int b = 0; b < bin; ++b) {
-      const float2 v = o[static_cast<size_t>(ty * bin + a) * fov + tx * bin + b];
-      s = fmaf(v.x, v.x, fmaf(v.y, v.y, s));
-    }
-  out[i] = s;
+  out[i] = bin_sum(ofov + (static_cast<size_t>(w) * fov + ty * bin) * fov + tx * bin, fov, bin);
 }
 
 constexpr int kLdsThreads = 512;
@@ -211,6 +227,9 @@ __device__ __forceinline__ int group_task(const GroupArgs& g, int b) {
   hipError_t launch_col_##m(int pad, bool conj, int variant, int plan, const ColArgs& a, int w_count,    \
                             hipStream_t s);                                                             \
   void twiddle_table_##m(int plan, std::vector<float2>& out);                                           \
+  void col_table_##m(int pad, std::vector<float2>& out);                                                \
+  bool col_split_##m(int pad);                                                                          \
+  int col_tile_width_##m(int pad, int variant);                                                         \
   hipError_t launch_col_group_##m(int pad, bool conj, int variant, bool table, bool full,               \
                                   const GroupArgs& g, hipStream_t s);                                   \
   hipError_t launch_transfer_table_##m(const WlConst* wl, int W, double zrev, float2* out, hipStream_t s); \
@@ -229,7 +248,11 @@ hipError_t launch_loss_group(const GroupArgs& g, const float* I, const float* ta
                              hipStream_t s);
 hipError_t launch_loss_sum_group(const LossTask* tasks, int ntasks, double* loss, hipStream_t s);
 hipError_t launch_dh_group(const GroupArgs& g, float* dl_dh, hipStream_t s);
-int col_tile_width(int M, int variant);  // columns per block of a transform variant (0-3)
+// columns per block of a transform variant (0-3) on radix plan 0
+int col_tile_width(int M, int pad, int variant);
+// whether radix plan 0's column passes run the split transforms (col_fft.hpp), and their table
+bool col_split(int M, int pad);
+void build_col_table(int M, int pad, std::vector<float2>& out);
 
 // launchers (dpx_kernels.hip); each returns a hipError_t from the launch
 // plan: the radix plan of the transforms (0 .. radix_plan_count(M) - 1)
@@ -241,7 +264,7 @@ bool col_variant_supported(int M, int pad, int variant);
 // column pass
 void build_dft_table(int M, int pad, std::vector<float2>& out);
 extern const char* const kColVariantNames[kColVariants];
-int default_col_variant(int M);
+int default_col_variant(int M, int pad, int wavelengths);
 hipError_t launch_col(int M, int pad, bool conj, int variant, int plan, const ColArgs& a, int w_count,
                       hipStream_t s);
 // fills out[w][|kx|][|ky|] (w < W, |kx|, |ky| <= M/2) with H / M^2 of the gap z = zrev M dx,

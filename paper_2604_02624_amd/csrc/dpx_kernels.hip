@@ -421,8 +421,16 @@ const char* const kColVariantNames[kColVariants] = {"tile8", "tile16", "tile8+mi
 
 // built-in choice when no variant is forced and no autotuning is asked for: the mirrored forms
 // where transforms stay in one wavefront; at 1600 the wide tile (8 columns, 10 waves per CU in
-// one block) beats the narrow one, which the registers hold to one 5-wave block per CU
-int default_col_variant(int M) { return !wave_local(M) ? 1 : M >= 512 ? 2 : 3; }
+// one block) beats the narrow one, which the registers hold to one 5-wave block per CU.  The split
+// transforms take 16 columns, so that a row segment is a whole 128-byte line (512 points, 1024
+// wavelengths: column and next row pass 1165 against 1174 us, 256 points 700 against 780), except
+// where the wide block is short of registers (384 points without padding: 96 against 66 us) or the
+// launch would leave CUs empty.
+int default_col_variant(int M, int pad, int wavelengths) {
+  if (!wave_local(M)) return 1;
+  if (!col_split(M, pad)) return M >= 512 ? 2 : 3;
+  return (M / pad >= 384 || static_cast<int64_t>(wavelengths) * (M / 16) < 512) ? 2 : 3;
+}
 
 bool col_variant_supported(int M, int pad, int variant) {
   if (variant < 0 || variant >= kColVariants) return false;
@@ -431,10 +439,34 @@ bool col_variant_supported(int M, int pad, int variant) {
   return true;
 }
 
-int col_tile_width(int M, int variant) {
-  const int P = row_lanes_per_transform(M);
-  if (!wave_local(M)) return variant == 0 ? 4 : 8;
-  return ((variant == 0 || variant == 2) && 8 * P >= 64) ? 8 : 16;
+int col_tile_width(int M, int pad, int variant) {
+  switch (M) {
+#define DPX_CASE(m) case m: return col_tile_width_##m(pad, variant);
+    DPX_FOR_EACH_M(DPX_CASE)
+#undef DPX_CASE
+    default:
+      return 16;
+  }
+}
+
+bool col_split(int M, int pad) {
+  switch (M) {
+#define DPX_CASE(m) case m: return col_split_##m(pad);
+    DPX_FOR_EACH_M(DPX_CASE)
+#undef DPX_CASE
+    default:
+      return false;
+  }
+}
+
+void build_col_table(int M, int pad, std::vector<float2>& out) {
+  switch (M) {
+#define DPX_CASE(m) case m: col_table_##m(pad, out); return;
+    DPX_FOR_EACH_M(DPX_CASE)
+#undef DPX_CASE
+    default:
+      out.clear();
+  }
 }
 
 

@@ -36,8 +36,11 @@ hipError_t with_plan(int plan, F&& f) {
 template <int PAD, int V>
 hipError_t row_mode(int mode, const RowArgs& a, dim3 grid, hipStream_t s) {
   if constexpr (M == 1600 && PAD == 2 && V == 0) {
-    if (mode == ROW_FWD_MID) {
-      row_kernel_w3<M, PAD, ROW_FWD_MID><<<grid, row_block_threads<M, ROW_FWD_MID>(), 0, s>>>(a);
+    if (mode == ROW_FWD_MID || mode == ROW_ADJ_MID) {
+      if (mode == ROW_FWD_MID)
+        row_kernel_w3<M, PAD, ROW_FWD_MID><<<grid, row_block_threads<M, ROW_FWD_MID>(), 0, s>>>(a);
+      else
+        row_kernel_w3<M, PAD, ROW_ADJ_MID><<<grid, row_block_threads<M, ROW_ADJ_MID>(), 0, s>>>(a);
       return hipGetLastError();
     }
   }
@@ -86,22 +89,31 @@ bool full_rows(const ColArgs& a) { return a.in_lo == 0 && a.out_lo == 0 && a.in_
 
 template <int PAD, int TX, int HM, int V>
 hipError_t col_launch(bool conj, const ColArgs& a, int w_count, hipStream_t s) {
+  constexpr int THREADS = ColShape<M, PAD, TX, V>::THREADS;
   dim3 grid(M / TX, (w_count + a.col_wpb - 1) / a.col_wpb);
   const bool full = full_rows(a);
   if (conj) {
-    if (full) col_kernel<M, PAD, true, TX, HM, true, V><<<grid, TX * Geo<M>::P, 0, s>>>(a);
-    else col_kernel<M, PAD, true, TX, HM, false, V><<<grid, TX * Geo<M>::P, 0, s>>>(a);
+    if (full) col_kernel<M, PAD, true, TX, HM, true, V><<<grid, THREADS, 0, s>>>(a);
+    else col_kernel<M, PAD, true, TX, HM, false, V><<<grid, THREADS, 0, s>>>(a);
   } else {
-    if (full) col_kernel<M, PAD, false, TX, HM, true, V><<<grid, TX * Geo<M>::P, 0, s>>>(a);
-    else col_kernel<M, PAD, false, TX, HM, false, V><<<grid, TX * Geo<M>::P, 0, s>>>(a);
+    if (full) col_kernel<M, PAD, false, TX, HM, true, V><<<grid, THREADS, 0, s>>>(a);
+    else col_kernel<M, PAD, false, TX, HM, false, V><<<grid, THREADS, 0, s>>>(a);
   }
   return hipGetLastError();
 }
 
-// tile widths of the transform variants: 8 / 16 columns, or 4 / 8 when a transform spans
-// wavefronts (blocks stay within 1024 threads)
-constexpr int kTileNarrow = Geo<M>::WAVE_LOCAL ? 8 : 4;
-constexpr int kTileWide = Geo<M>::WAVE_LOCAL ? 16 : 8;
+// tile widths of the transform variants: 8 / 16 columns (16 / 16 where 8 columns would not fill
+// whole wavefronts), or 4 / 8 when a transform spans wavefronts (blocks stay within 1024 threads)
+template <int PAD, int V>
+constexpr int tile_narrow() {
+  if (ColShape<M, PAD, 16, V>::SPLIT) return ColSplit<M, PAD>::NARROW ? 8 : 16;
+  return !Geo<M>::WAVE_LOCAL ? 4 : 8 * Geo<M>::P >= 64 ? 8 : 16;
+}
+template <int PAD, int V>
+constexpr int tile_wide() {
+  return ColShape<M, PAD, 16, V>::SPLIT || Geo<M>::WAVE_LOCAL ? 16 : 8;
+}
+constexpr bool wide_variant(int variant) { return variant == 1 || variant == 3; }
 
 // H sources of each radix plan: plan 0 has them all; the other plans only the evaluated and
 // mirrored transfer functions of the untranslated, full-spectrum gap (the plan layer refuses
@@ -131,8 +143,8 @@ hipError_t col_variant(int variant, int plan, bool conj, const ColArgs& args, in
   const int hm = h_mode(variant, a.htab != nullptr, shifted, a.band_limited != 0);
   return with_plan(plan, [&](auto vc) -> hipError_t {
     constexpr int V = decltype(vc)::value;
-    if (col_tile_width(M, variant) == kTileNarrow) return col_launch_h<PAD, kTileNarrow, V>(hm, conj, a, w_count, s);
-    return col_launch_h<PAD, kTileWide, V>(hm, conj, a, w_count, s);
+    if (!wide_variant(variant)) return col_launch_h<PAD, tile_narrow<PAD, V>(), V>(hm, conj, a, w_count, s);
+    return col_launch_h<PAD, tile_wide<PAD, V>(), V>(hm, conj, a, w_count, s);
   });
 }
 
@@ -154,12 +166,13 @@ hipError_t colgemm_launch(bool conj, const ColArgs& a, int w_count, hipStream_t 
 
 template <int PAD, int TX, int HM>
 hipError_t col_group_tx(bool conj, bool full, const GroupArgs& g, hipStream_t s) {
+  constexpr int THREADS = ColShape<M, PAD, TX, 0>::THREADS;
   if (conj) {
-    if (full) col_group_kernel<M, PAD, true, TX, HM, true><<<group_grid(g), TX * Geo<M>::P, 0, s>>>(g);
-    else col_group_kernel<M, PAD, true, TX, HM, false><<<group_grid(g), TX * Geo<M>::P, 0, s>>>(g);
+    if (full) col_group_kernel<M, PAD, true, TX, HM, true><<<group_grid(g), THREADS, 0, s>>>(g);
+    else col_group_kernel<M, PAD, true, TX, HM, false><<<group_grid(g), THREADS, 0, s>>>(g);
   } else {
-    if (full) col_group_kernel<M, PAD, false, TX, HM, true><<<group_grid(g), TX * Geo<M>::P, 0, s>>>(g);
-    else col_group_kernel<M, PAD, false, TX, HM, false><<<group_grid(g), TX * Geo<M>::P, 0, s>>>(g);
+    if (full) col_group_kernel<M, PAD, false, TX, HM, true><<<group_grid(g), THREADS, 0, s>>>(g);
+    else col_group_kernel<M, PAD, false, TX, HM, false><<<group_grid(g), THREADS, 0, s>>>(g);
   }
   return hipGetLastError();
 }
@@ -178,8 +191,8 @@ hipError_t col_group_h(int hm, bool conj, bool full, const GroupArgs& g, hipStre
 template <int PAD>
 hipError_t col_group_variant(int variant, bool table, bool conj, bool full, const GroupArgs& g, hipStream_t s) {
   const int hm = h_mode(variant, table);
-  if (col_tile_width(M, variant) == kTileNarrow) return col_group_h<PAD, kTileNarrow>(hm, conj, full, g, s);
-  return col_group_h<PAD, kTileWide>(hm, conj, full, g, s);
+  if (!wide_variant(variant)) return col_group_h<PAD, tile_narrow<PAD, 0>()>(hm, conj, full, g, s);
+  return col_group_h<PAD, tile_wide<PAD, 0>()>(hm, conj, full, g, s);
 }
 
 }  // namespace
@@ -220,6 +233,18 @@ void DPX_NAME(twiddle_table_)(int plan, std::vector<float2>& out) {
     twiddle_table_host<M, decltype(vc)::value>(out);
     return hipSuccess;
   });
+}
+
+void DPX_NAME(col_table_)(int pad, std::vector<float2>& out) {
+  if (pad == 2) col_table_host<M, 2>(out);
+  else col_table_host<M, 1>(out);
+}
+
+bool DPX_NAME(col_split_)(int pad) { return pad == 2 ? ColSplit<M, 2>::BUILT : ColSplit<M, 1>::BUILT; }
+
+int DPX_NAME(col_tile_width_)(int pad, int variant) {
+  if (pad == 2) return wide_variant(variant) ? tile_wide<2, 0>() : tile_narrow<2, 0>();
+  return wide_variant(variant) ? tile_wide<1, 0>() : tile_narrow<1, 0>();
 }
 
 hipError_t DPX_NAME(launch_col_group_)(int pad, bool conj, int variant, bool table, bool full, const GroupArgs& g,

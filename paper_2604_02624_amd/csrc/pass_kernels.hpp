@@ -14,6 +14,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include "col_fft.hpp"
 #include "dpx_internal.hpp"
 #include "fft.hpp"
 #include "phase.hpp"
@@ -28,6 +29,86 @@ __device__ __forceinline__ float2 buffer_load_c64(__amdgpu_buffer_rsrc_t r, unsi
   const auto v = __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0);
   return make_float2(__uint_as_float(v[0]), __uint_as_float(v[1]));
 }
+
+// One 8-byte store, the same way.
+__device__ __forceinline__ void buffer_store_c64(__amdgpu_buffer_rsrc_t r, unsigned voff, unsigned soff, float2 v) {
+  typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+  const u32x2 u = {__float_as_uint(v.x), __float_as_uint(v.y)};
+  __builtin_amdgcn_raw_buffer_store_b64(u, r, voff, soff, 0);
+}
+
+// Reads an object that no kernel of the launch writes through the constant address space: scalar
+// loads where the pointer is uniform (a plain load is a vector load as soon as the kernel stores
+// anything, since the compiler cannot rule out an overlap).
+template <typename T>
+__device__ __forceinline__ T load_uniform(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole dwords");
+  typedef const unsigned __attribute__((address_space(4)))* words;
+  unsigned v[sizeof(T) / 4];
+  const words q = (words) reinterpret_cast<uintptr_t>(p);
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(T) / 4; ++i) v[i] = q[i];
+  T out;
+  __builtin_memcpy(&out, v, sizeof(T));
+  return out;
+}
+
+// The lane's first row index, opaque to the optimiser: the per-element row terms of the
+// transfer function (ky, ky^2, their conversions to FP64) are the same for every wavelength, and
+// left visible the compiler keeps all E of them live across the wavelength loop, which spills.
+// Derived from this value they are recomputed per wavelength (a few integer operations).
+__device__ __forceinline__ int opaque_lane_row(int j0) {
+  asm volatile("" : "+v"(j0));
+  return j0;
+}
+
+// One spectrum row as the row passes read and write it: lane j0 holds columns j0 + P t.  The
+// accesses go through a buffer resource over the wavelength's plane, and a lane whose column
+// lies outside the disc takes an offset beyond the plane, so its load returns zero and its store
+// is dropped without memory traffic and without a branch.  Bound by HBM: on the 1600-point glass
+// design (28 % of the columns evanescent on average over 400-750 nm) the planes' traffic falls by
+// as much; where every column propagates the select per access is hidden by the memory time.
+template <int M, int PAD>
+struct SpectrumRow {
+  static constexpr int E = Geo<M>::E, P = Geo<M>::P;
+  __amdgpu_buffer_rsrc_t rs;
+  unsigned voff;  // byte offset of (row y, column j0)
+  int j0, radius;
+
+  // plane: uniform over the block; y and j0 per lane; radius: the wavelength's, or M (every column)
+  __device__ __forceinline__ SpectrumRow(float2* plane, int y, int j0_, int radius_) : j0(j0_), radius(radius_) {
+    const uint64_t base = reinterpret_cast<uint64_t>(plane);
+    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
+    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32)));
+    rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((hi << 32) | lo), 0, M / PAD * M * 8,
+                                           kBufferRsrcWord3);
+    voff = static_cast<unsigned>((y * M + j0) * 8);
+  }
+  // The lane's offset in register t if its column is below `below` or at least `from`, else one past
+  // every plane (j: j0, opaque, so that the offsets of the loads are not held for the stores).
+  __device__ __forceinline__ unsigned offset(int t, int j, int below, int from) const {
+    // a register's columns lie on one side of M / 2 where P divides it, the register in the middle
+    // holds both sides otherwise
+    bool in;
+    if (P * (t + 1) <= M / 2) in = j < below - P * t;
+    else if (P * t >= M / 2) in = j >= from - P * t;
+    else in = j < below - P * t || j >= from - P * t;
+    return in ? voff : 0x80000000u;
+  }
+  __device__ __forceinline__ void load(float2 (&reg)[E]) const {
+    const int j = opaque_lane_row(j0);
+#pragma unroll
+    for (int t = 0; t < E; ++t) reg[t] = buffer_load_c64(rs, offset(t, j, radius + 1, M - radius), P * t * 8);
+  }
+  // stores end on whole 128-byte lines, or the memory pays for part of one at both ends of the gap
+  // (first pass of 1024 wavelengths of 512 points: 209 us with ends at the disc, 183 without a gap)
+  __device__ __forceinline__ void store(const float2 (&reg)[E]) const {
+    const int j = opaque_lane_row(j0);
+    const int below = (radius + 16) & ~15, from = M - ((radius + 15) & ~15);
+#pragma unroll
+    for (int t = 0; t < E; ++t) buffer_store_c64(rs, offset(t, j, below, from), P * t * 8, reg[t]);
+  }
+};
 
 // Eq. 1 with the +j reading: t = exp(-ca h) exp(+i 2 pi rt h); phase argument in double.
 __device__ __forceinline__ float2 transmission(float h, const WlConst& c) {
@@ -60,8 +141,6 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
   constexpr int EN = E / PAD;  // registers that hold x < N
   constexpr bool HALF = (PAD == 2);
   constexpr int RG = Geo<M>::ROW_REGION;
-  stage_twiddles<M, V>(tw, a.tw, threadIdx.x, kRowThreads);
-  __syncthreads();
 
   const int N = M / PAD;
   const int g = threadIdx.x / P;
@@ -70,11 +149,25 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
   const int y_raw = a.row_lo + bx * G + g;
   const bool active = y_raw < a.row_hi;
   const int y = active ? y_raw : a.row_lo;
-  const size_t plane = static_cast<size_t>(N) * M;
   const size_t nn = static_cast<size_t>(N) * N;
+  // the lane's part of row y of wavelength w's plane
+  auto spectrum = [&](int w, const WlConst& c) {
+    return SpectrumRow<M, PAD>(a.spec + static_cast<size_t>(w - a.w_begin) * N * M, y, j0,
+                               a.all_columns ? M : c.radius);
+  };
 
   const int wb = a.w_begin + by * a.w_per_block;
   const int we = min(wb + a.w_per_block, a.w_begin + a.w_count);
+  // A wavelength's row loads depend on its constants: they are scalar loads (load_uniform), read one
+  // wavelength ahead, so that no wait for them comes on top of the rows'.  The first row is
+  // requested before the twiddle table goes to LDS, every later one right behind the stores of the
+  // one before.
+  WlConst c = load_uniform(a.wl + wb);
+  auto constants_after = [&](int w) { return load_uniform(a.wl + min(w + 1, we - 1)); };
+  auto stage_table = [&]() {
+    stage_twiddles<M, V>(tw, a.tw, threadIdx.x, kRowThreads);
+    __syncthreads();
+  };
 
   float hreg[EN];
   if constexpr (MODE == ROW_FWD_FIRST || MODE == ROW_FWD_MID || MODE == ROW_ADJ_MID ||
@@ -89,10 +182,11 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
 #pragma unroll
     for (int t = 0; t < EN; ++t)
       uin[t] = a.u_in ? a.u_in[static_cast<size_t>(y) * N + j0 + P * t] : make_float2(1.f, 0.f);
+    stage_table();
     for (int w = wb; w < we; ++w) {
-      const WlConst c = a.wl[w];
       const int wc = w - a.w_begin;
       float2 reg[E];
+      const WlConst next = constants_after(w);
       if (a.no_layer) {
 #pragma unroll
         for (int t = 0; t < EN; ++t) reg[t] = uin[t];
@@ -107,20 +201,16 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
         for (int t = 0; t < EN; ++t) ck[j0 + P * t] = reg[t];
       }
       fft<M, false, HALF, V, XPad<M>::ROWS>(reg, lds, j0, tw);
-      if (active) {
-        float2* dst = a.spec + wc * plane + static_cast<size_t>(y) * M;
-#pragma unroll
-        for (int t = 0; t < E; ++t) dst[j0 + P * t] = reg[t];
-      }
+      if (active) spectrum(w, c).store(reg);
+      c = next;
     }
   } else if constexpr (MODE == ROW_FWD_MID) {
+    float2 reg[E];
+    spectrum(wb, c).load(reg);
+    stage_table();
     for (int w = wb; w < we; ++w) {
-      const WlConst c = a.wl[w];
       const int wc = w - a.w_begin;
-      float2* row = a.spec + wc * plane + static_cast<size_t>(y) * M;
-      float2 reg[E];
-#pragma unroll
-      for (int t = 0; t < E; ++t) reg[t] = row[j0 + P * t];
+      const WlConst next = constants_after(w);
       fft<M, true, false, V, XPad<M>::ROWS>(reg, lds, j0, tw);
 #pragma unroll
       for (int t = 0; t < EN; ++t) reg[t] = cmul(reg[t], transmission(hreg[t], c));
@@ -131,20 +221,19 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
         for (int t = 0; t < EN; ++t) ck[j0 + P * t] = reg[t];
       }
       fft<M, false, HALF, V, XPad<M>::ROWS>(reg, lds, j0, tw);
-      if (active) {
-#pragma unroll
-        for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
-      }
+      if (active) spectrum(w, c).store(reg);
+      c = next;
+      if (w + 1 < we) spectrum(w + 1, c).load(reg);
     }
   } else if constexpr (MODE == ROW_FWD_LAST) {
     const int F = a.fov;
     const int x0 = (N - F) / 2;
+    float2 reg[E];
+    spectrum(wb, c).load(reg);
+    stage_table();
     for (int w = wb; w < we; ++w) {
       const int wc = w - a.w_begin;
-      const float2* row = a.spec + wc * plane + static_cast<size_t>(y) * M;
-      float2 reg[E];
-#pragma unroll
-      for (int t = 0; t < E; ++t) reg[t] = row[j0 + P * t];
+      const WlConst next = constants_after(w);
       fft<M, true, false, V, XPad<M>::ROWS>(reg, lds, j0, tw);
       if (active) {
         float2* dst = a.ofov + static_cast<size_t>(wc) * F * F + static_cast<size_t>(y - x0) * F;
@@ -154,12 +243,16 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
           if (x >= x0 && x < x0 + F) dst[x - x0] = reg[t];
         }
       }
+      c = next;
+      if (w + 1 < we) spectrum(w + 1, c).load(reg);
     }
   } else if constexpr (MODE == ROW_ADJ_SEED) {
     const int F = a.fov, b = a.bin, T = F / b;
     const int x0 = (N - F) / 2;
+    stage_table();
     for (int w = wb; w < we; ++w) {
       const int wc = w - a.w_begin;
+      const WlConst next = constants_after(w);
       const float2* o = a.ofov + static_cast<size_t>(wc) * F * F + static_cast<size_t>(y - x0) * F;
       const float* d = a.dl_di + static_cast<size_t>(w) * T * T + static_cast<size_t>((y - x0) / b) * T;
       float2 reg[E];
@@ -174,11 +267,8 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
         }
       }
       fft<M, false, HALF, V, XPad<M>::ROWS>(reg, lds, j0, tw);
-      if (active) {
-        float2* dst = a.spec + wc * plane + static_cast<size_t>(y) * M;
-#pragma unroll
-        for (int t = 0; t < E; ++t) dst[j0 + P * t] = reg[t];
-      }
+      if (active) spectrum(w, c).store(reg);
+      c = next;
     }
   } else {  // ROW_ADJ_MID, ROW_ADJ_LAST, ROW_ADJ_LAST_U
     // ROW_ADJ_LAST_U: the input field meets the first layer directly, so the field after the
@@ -190,18 +280,17 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
     float acc[EN];
 #pragma unroll
     for (int t = 0; t < EN; ++t) acc[t] = 0.f;
+    float2 reg[E];
+    spectrum(wb, c).load(reg);
+    stage_table();
     for (int w = wb; w < we; ++w) {
-      const WlConst c = a.wl[w];
       const int wc = w - a.w_begin;
-      float2* row = a.spec + wc * plane + static_cast<size_t>(y) * M;
+      const WlConst next = constants_after(w);
       const float2* ck = REBUILD ? nullptr
                                  : a.ckpt + (static_cast<size_t>(a.layer - a.ckpt_first) * a.ckpt_w_stride + wc) * nn +
                                        static_cast<size_t>(y) * N;
-      float2 reg[E];
-#pragma unroll
-      for (int t = 0; t < E; ++t) reg[t] = row[j0 + P * t];
       fft<M, true, false, V, XPad<M>::ROWS>(reg, lds, j0, tw);
-      const float ct = static_cast<float>(c.ct);
+      const float ct = c.ct;
       const float ca = static_cast<float>(c.ca);
 #pragma unroll
       for (int t = 0; t < EN; ++t) {
@@ -221,11 +310,10 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
       }
       if constexpr (MODE == ROW_ADJ_MID) {
         fft<M, false, HALF, V, XPad<M>::ROWS>(reg, lds, j0, tw);
-        if (active) {
-#pragma unroll
-          for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
-        }
+        if (active) spectrum(w, c).store(reg);
       }
+      c = next;
+      if (w + 1 < we) spectrum(w + 1, c).load(reg);
     }
     if (active) {
       float* dst = a.dh_part +
@@ -268,7 +356,7 @@ __global__ void __launch_bounds__((row_block_threads<M, MODE>())) row_group_kern
   __shared__ float2 lds_all[row_block_threads<M, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
   __shared__ float2 tw[twiddle_count<M>()];
   const int ti = group_task(g, blockIdx.x);
-  const RowTask& t = static_cast<const RowTask*>(g.tasks)[ti];
+  const RowTask t = load_uniform(static_cast<const RowTask*>(g.tasks) + ti);
   const int local = static_cast<int>(blockIdx.x) - g.block0[ti];
   if (local >= t.nblocks) return;  // alignment padding between tasks
   RowArgs a = t.a;
@@ -276,15 +364,6 @@ __global__ void __launch_bounds__((row_block_threads<M, MODE>())) row_group_kern
   a.u_in = g.call.u_in ? g.call.u_in + t.u_off : nullptr;
   a.dl_di = g.call.dl_di ? g.call.dl_di + t.img_off : nullptr;
   row_body<M, PAD, MODE>(a, local % t.gx, local / t.gx, lds_all, tw);
-}
-
-// The lane's first row index, opaque to the optimiser: the per-element row terms of the
-// transfer function (ky, ky^2, their conversions to FP64) are the same for every wavelength, and
-// left visible the compiler keeps all E of them live across the wavelength loop, which spills.
-// Derived from this value they are recomputed per wavelength (a few integer operations).
-__device__ __forceinline__ int opaque_lane_row(int j0) {
-  asm volatile("" : "+v"(j0));
-  return j0;
 }
 
 // H(kx, ky) / M^2 with the conjugate for the adjoint; 0 outside the propagating disc.  zrev is
@@ -326,6 +405,17 @@ __device__ __forceinline__ void col_block_item(int L, int total, int gx, int& bx
   by = item / gx;
 }
 
+// Drops the wavelengths at both ends of [wb, we) for which every column of the tile at kx0 lies
+// outside the propagating disc: such columns are never read back (SpectrumRow), so a block with
+// nothing else ends at once.  A wavelength between two others is transformed all the same; what
+// it leaves in columns outside its disc is not read.
+template <int M, int TX>
+__device__ __forceinline__ void trim_evanescent(const ColArgs& a, int kx0, int& wb, int& we) {
+  const int k = kx0 < M / 2 ? kx0 : M - (kx0 + TX - 1);  // the tile's smallest |kx|
+  while (wb < we && k > load_uniform(&a.wl[a.w_begin + wb].radius)) ++wb;
+  while (wb < we && k > load_uniform(&a.wl[a.w_begin + we - 1].radius)) --we;
+}
+
 // Block (bx, by) of a column pass: column tile bx, wavelength block by.
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V = 0>
 __device__ __forceinline__ void col_body(const ColArgs& a, int bx, int by, float2* tile, float2* tw) {
@@ -359,8 +449,10 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int bx, int by, float
   // Row k of a lane is one buffer load at the lane's 32-bit byte offset plus the scalar offset
   // k P M 8, so no per-row address stays live.
   constexpr bool PREFETCH = HALF && HM != kHBand;
-  const int wb = by * a.col_wpb;
-  const int we = min(wb + a.col_wpb, a.w_count);
+  int wb = by * a.col_wpb;
+  int we = min(wb + a.col_wpb, a.w_count);
+  trim_evanescent<M, TX>(a, kx0, wb, we);
+  if (wb >= we) return;
   const unsigned voff = static_cast<unsigned>((((FULL ? 0 : a.in_lo) + yy) * M + kx0 + cc) * 8);
   // The plane's base address is the same in every lane; reading it through readfirstlane
   // keeps the descriptor in scalar registers (a descriptor left in vector registers makes
@@ -419,7 +511,7 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int bx, int by, float
       if (w + 1 < we) fetch(w + 1);
     }
 
-    const WlConst c = a.wl[a.w_begin + w];
+    const WlConst c = load_uniform(a.wl + a.w_begin + w);
     float2 reg[E];
 #pragma unroll
     for (int t = 0; t < EN; ++t) {
@@ -532,32 +624,241 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int bx, int by, float
   }
 }
 
+// Transfer function of the split column transforms on v[k2], k2 = 0 .. R2 - 1, of one (column, k1)
+// of half h: element k2 is frequency ky = NH (k1 + R1 k2) + h.  HC: the half where it is known at
+// compile time (a body of its own per half), else -1.
+template <int M, int PAD, bool CONJ, int HM, int HC>
+__device__ __forceinline__ void apply_transfer(float2* v, const ColArgs& a, const WlConst& c, int w, int kx, int half,
+                                               int k1) {
+  const int h = HC >= 0 ? HC : half;
+  using G = ColSplit<M, PAD>;
+  constexpr int R2 = G::R2;
+  const int kxs = kx < M / 2 ? kx : kx - M;
+  const double base = c.q0 - static_cast<double>(kxs * kxs);
+  const int row0 = opaque_lane_row(G::NH * k1 + h);  // frequency of k2 = 0 (see opaque_lane_row)
+  auto ky_of = [&](int k2) { return row0 + G::NH * G::R1 * k2; };
+  if constexpr (HM == kHMirror) {
+    // H depends on ky^2 only: frequency M - ky of (k1, k2) belongs to k1' = R1 - k1 - h (mod R1) at
+    // k2' = R2 - 1 - k2, or at R2 - k2 on the lane k1 = 0 of the even half, which mirrors onto
+    // itself.  So a lane evaluates the lower half of its frequencies (that one lane one more) and
+    // takes the upper half from its partner.
+    const int partner = h ? G::R1 - 1 - k1 : (k1 ? G::R1 - k1 : 0);
+    const int src = ((static_cast<int>(threadIdx.x) & 63) - k1 + partner) << 2;
+    const bool self = h == 0 && k1 == 0;
+    float2 cur = transfer<M, CONJ>(a.zrev, base, ky_of(0));
+#pragma unroll
+    for (int u = 0; u < R2 / 2; ++u) {
+      float2 nxt = cur;  // the odd half needs no value past the lower half
+      if (u + 1 < R2 / 2 || HC != 1) nxt = transfer<M, CONJ>(a.zrev, base, ky_of(u + 1));
+      v[u] = cmul(v[u], cur);
+      float2 m;
+      m.x = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(cur.x)));
+      m.y = __int_as_float(__builtin_amdgcn_ds_bpermute(src, __float_as_int(cur.y)));
+      if (self) m = nxt;
+      v[R2 - 1 - u] = cmul(v[R2 - 1 - u], m);
+      cur = nxt;
+    }
+    static_assert(R2 % 2 == 0, "mirrored pairs");
+  } else if constexpr (HM == kHTable) {
+    constexpr int HS = M / 2 + 1;
+    const float2* hrow = a.htab + (static_cast<size_t>(a.w_begin + w) * HS + (kxs < 0 ? -kxs : kxs)) * HS;
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) {
+      const int ky = ky_of(k2);
+      const float2 hh = hrow[ky <= M / 2 ? ky : M - ky];
+      v[k2] = cmul(v[k2], CONJ ? conjf2(hh) : hh);
+    }
+  } else {
+    // per element (evaluated, translated or band-limited); the product is selected, not H, so that
+    // the compiler branches the evaluation over runs of frequencies outside the disc or band
+    const double px = HM == kHShift ? static_cast<double>(kxs) * a.sx : 0.0;
+    const double lim = HM == kHBand ? c.q0 / (4.0 * a.zrev * a.zrev + 1.0) : 0.0;
+    const bool col_in = HM != kHBand || static_cast<double>(kxs * kxs) <= lim;
+#pragma unroll
+    for (int k2 = 0; k2 < R2; ++k2) {
+      const int ky = ky_of(k2);
+      const int kys = ky < M / 2 ? ky : ky - M;
+      if constexpr (HM == kHBand) {
+        const bool in = col_in && static_cast<double>(kys * kys) <= lim;
+        v[k2] = in ? cmul(v[k2], transfer<M, CONJ>(a.zrev, base, ky)) : make_float2(0.f, 0.f);
+      } else {
+        const double q = base - static_cast<double>(kys * kys);
+        double ph = a.zrev * sqrt_pos(fmax(q, kMinNormalF64));
+        // translated gap: H times the ramp exp(-i 2 pi (kx sx + ky sy)) is one phase, reduced in
+        // FP64 like H's own; conjugated for the adjoint
+        if constexpr (HM == kHShift) ph -= fma(static_cast<double>(kys), a.sy, px);
+        const float2 hh = cis_turns_hw<M * M>(ph);
+        v[k2] = q > 0.0 ? cmul(v[k2], CONJ ? conjf2(hh) : hh) : make_float2(0.f, 0.f);
+      }
+    }
+  }
+}
+
+// Block (bx, by) of a column pass with split transforms (col_fft.hpp): column tile bx, wavelength
+// block by.  The halves run on different wavefronts.  Three block barriers per wavelength: after
+// the writes of A, after those of B, and before the next wavelength's A overwrites what C read.
+template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL>
+__device__ __forceinline__ void col_split_body(const ColArgs& a, int bx, int by, float2* tile, float2* tab) {
+  using G = ColSplit<M, PAD>;
+  constexpr int N = M / PAD;
+  constexpr int NT = G::threads(TX), R1 = G::R1, R2 = G::R2, L = G::L, GP = G::GP, REG = G::region(TX);
+  constexpr int HALF_A = TX * L, HALF_B = TX * GP;  // threads of one half in A and C, and in B
+  static_assert(HALF_A % 64 == 0 || G::NH == 1, "the half is the same over a wavefront");
+  const int tid = threadIdx.x;
+  const int kx0 = bx * TX;
+  int wb = by * a.col_wpb;
+  int we = min(wb + a.col_wpb, a.w_count);
+  trim_evanescent<M, TX>(a, kx0, wb, we);
+  if (wb >= we) return;
+
+  // A and C: column cc, rows j + L r; ha: the half in A, the row parity in C
+  const bool rows = tid < G::NH * HALF_A;
+  const int ha = G::NH == 2 ? __builtin_amdgcn_readfirstlane(tid / HALF_A) : 0;
+  const int cc = tid % TX, j = (tid / TX) % L;
+  float2* const own = tile + (static_cast<size_t>(ha) * TX + cc) * REG;
+  // B: column cb, k1 of half hb
+  const int k1 = tid % GP, cb = (tid / GP) % TX;
+  const int hb = HALF_B % 64 == 0 ? __builtin_amdgcn_readfirstlane(tid / HALF_B) : tid / HALF_B;
+  const bool freq = k1 < R1 && hb < G::NH;
+  float2* const freq_slots = tile + (static_cast<size_t>(hb < G::NH ? hb : 0) * TX + cb) * REG + G::slot(k1, 0);
+
+  auto plane = [&](int w) {
+    const uint64_t base = reinterpret_cast<uint64_t>(a.spec + static_cast<size_t>(w) * N * M);
+    const uint64_t lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
+    const uint64_t hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32)));
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((hi << 32) | lo), 0, N * M * 8,
+                                             kBufferRsrcWord3);
+  };
+  const unsigned voff = static_cast<unsigned>((j * M + kx0 + cc) * 8);
+  constexpr unsigned kNowhere = 0x80000000u;  // beyond every plane: loads give zero, stores drop
+  // The rows of the first wavelength are requested before the table is staged, those of a later one
+  // when B of the one before is done, so that they arrive during its C.
+  float2 v[R1];
+  auto fetch = [&](int w) {
+    if (!rows) return;
+    const auto rs = plane(w);
+    const int jv = opaque_lane_row(j);
+#pragma unroll
+    for (int r = 0; r < R1; ++r) {
+      const int y = jv + L * r;
+      const unsigned off = (FULL || (y >= a.in_lo && y < a.in_hi)) ? voff : kNowhere;
+      v[r] = buffer_load_c64(rs, off, L * r * M * 8);
+    }
+  };
+  fetch(wb);
+  for (int i = tid; i < G::COUNT; i += NT) tab[i] = a.tw[i];
+  for (int w = wb; w < we; ++w) {
+    if (rows) {
+      if (G::NH == 2 && ha) col_rows_forward<M, PAD, true>(v);
+      else col_rows_forward<M, PAD, false>(v);
+    }
+    if (w > wb) __syncthreads();  // C of the wavelength before has read the slots
+    if (rows) {
+#pragma unroll
+      for (int k = 0; k < R1; ++k) own[G::slot(k, j)] = v[k];
+    }
+    __syncthreads();
+    const WlConst c = load_uniform(a.wl + a.w_begin + w);
+    auto frequencies = [&](auto hc, int h) {
+      constexpr int HC = decltype(hc)::value;
+      float2 f[R2];
+#pragma unroll
+      for (int i = 0; i < R2; ++i) f[i] = freq_slots[i];
+      col_freq_forward<M, PAD>(f, tab, h, k1);
+      apply_transfer<M, PAD, CONJ, HM, HC>(f, a, c, w, kx0 + cb, h, k1);
+      col_freq_inverse<M, PAD>(f);
+#pragma unroll
+      for (int i = 0; i < R2; ++i) freq_slots[i] = f[i];
+    };
+    // A body per half saves the odd one an evaluation of H; worth it for the longest split only (512
+    // points, 1024 wavelengths: 604 against 620 us), shorter ones lose more to the longer code
+    // (256 points 171 against 152 us, 192 points, 2048 wavelengths, 224 against 183 us).
+    constexpr bool BOTH = G::NH == 2 && G::LEN >= 256;
+    if (freq) {
+      if constexpr (BOTH) {
+        if (hb) frequencies(std::integral_constant<int, 1>{}, 1);
+        else frequencies(std::integral_constant<int, 0>{}, 0);
+      } else {
+        frequencies(std::integral_constant<int, G::NH == 2 ? -1 : 0>{}, hb);
+      }
+    }
+    // v starts anew here: where no rows follow, its old values would otherwise stay live through B
+#pragma unroll
+    for (int r = 0; r < R1; ++r) asm volatile("" : "=v"(v[r].x), "=v"(v[r].y));
+    if (w + 1 < we) fetch(w + 1);
+    __syncthreads();
+    if (rows) {
+      const auto rs = plane(w);
+      const int jv = opaque_lane_row(j);
+      if constexpr (G::NH == 2) {
+        float2 y[G::RC];
+        col_rows_inverse2<M, PAD>(y, tab, j, ha, [&](int h, int k) {
+          return tile[(static_cast<size_t>(h) * TX + cc) * REG + G::slot(k, j)];
+        });
+#pragma unroll
+        for (int r = 0; r < G::RC; ++r) {
+          const int row = jv + L * (2 * r + ha);
+          const unsigned off = (FULL || (row >= a.out_lo && row < a.out_hi)) ? voff : kNowhere;
+          buffer_store_c64(rs, off, L * (2 * r + ha) * M * 8, y[r]);
+        }
+      } else {
+        float2 y[R1];
+#pragma unroll
+        for (int k = 0; k < R1; ++k) y[k] = own[G::slot(k, j)];
+        col_rows_inverse<M, PAD>(y, tab, j);
+#pragma unroll
+        for (int r = 0; r < R1; ++r) {
+          const int row = jv + L * r;
+          const unsigned off = (FULL || (row >= a.out_lo && row < a.out_hi)) ? voff : kNowhere;
+          buffer_store_c64(rs, off, L * r * M * 8, y[r]);
+        }
+      }
+    }
+  }
+}
+
+// Shape of the column kernels: the split transforms where the length has them (radix plan 0),
+// else the staged form.
+template <int M, int PAD, int TX, int V>
+struct ColShape {
+  static constexpr bool SPLIT = V == 0 && ColSplit<M, PAD>::BUILT;
+  static constexpr int THREADS = SPLIT ? ColSplit<M, PAD>::threads(TX) : TX * Geo<M>::P;
+  static constexpr int SLOTS = SPLIT ? PAD * TX * ColSplit<M, PAD>::region(TX) : TX * Geo<M>::COL_REGION;
+  static constexpr int TABLE = SPLIT ? ColSplit<M, PAD>::COUNT : twiddle_count<M, V>();
+};
+
+template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V>
+__device__ __forceinline__ void col_any_body(const ColArgs& a, int bx, int by, float2* tile, float2* tw) {
+  if constexpr (ColShape<M, PAD, TX, V>::SPLIT) col_split_body<M, PAD, CONJ, TX, HM, FULL>(a, bx, by, tile, tw);
+  else col_body<M, PAD, CONJ, TX, HM, FULL, V>(a, bx, by, tile, tw);
+}
+
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V = 0>
-__global__ void __launch_bounds__(TX * Geo<M>::P) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__((ColShape<M, PAD, TX, V>::THREADS)) __attribute__((amdgpu_waves_per_eu(4)))
 col_kernel(ColArgs a) {
-  __shared__ float2 tile[TX * Geo<M>::COL_REGION];
-  __shared__ float2 tw[twiddle_count<M, V>()];
+  __shared__ float2 tile[ColShape<M, PAD, TX, V>::SLOTS];
+  __shared__ float2 tw[ColShape<M, PAD, TX, V>::TABLE];
   int bx, by;
   col_block_item(static_cast<int>(blockIdx.x + gridDim.x * blockIdx.y), static_cast<int>(gridDim.x * gridDim.y),
                  static_cast<int>(gridDim.x), bx, by);
-  col_body<M, PAD, CONJ, TX, HM, FULL, V>(a, bx, by, tile, tw);
+  col_any_body<M, PAD, CONJ, TX, HM, FULL, V>(a, bx, by, tile, tw);
 }
 
 // One launch of a column pass for several designs of the same transform length (see
 // row_group_kernel); every task starts at a multiple of 16 blocks.
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL>
-__global__ void __launch_bounds__(TX * Geo<M>::P) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__((ColShape<M, PAD, TX, 0>::THREADS)) __attribute__((amdgpu_waves_per_eu(4)))
 col_group_kernel(GroupArgs g) {
-  __shared__ float2 tile[TX * Geo<M>::COL_REGION];
-  __shared__ float2 tw[twiddle_count<M>()];
+  __shared__ float2 tile[ColShape<M, PAD, TX, 0>::SLOTS];
+  __shared__ float2 tw[ColShape<M, PAD, TX, 0>::TABLE];
   const int ti = group_task(g, blockIdx.x);
-  const ColTask& t = static_cast<const ColTask*>(g.tasks)[ti];
+  const ColTask t = load_uniform(static_cast<const ColTask*>(g.tasks) + ti);
   const int local = static_cast<int>(blockIdx.x) - g.block0[ti];
   if (local >= t.nblocks) return;
   const ColArgs a = t.a;
   int bx, by;
   col_block_item(local, t.nblocks, t.gx, bx, by);
-  col_body<M, PAD, CONJ, TX, HM, FULL>(a, bx, by, tile, tw);
+  col_any_body<M, PAD, CONJ, TX, HM, FULL, 0>(a, bx, by, tile, tw);
 }
 
 // H / M^2 of one gap for every wavelength on the quarter plane |kx|, |ky| <= M/2 (H depends on
@@ -716,14 +1017,11 @@ struct LdsGeo {
   static constexpr int N = M / PAD;
   static constexpr int P = Geo<M>::P;
   static constexpr int RS = Geo<M>::ROW_REGION;               // row stride of the plane
-  static constexpr int CS = Geo<M>::COL_REGION;               // column exchange region
   static constexpr int RB = kLdsThreads / P;                  // rows transformed at once
-  static constexpr int CB = RB < M ? RB : M;                  // columns transformed at once
-  static constexpr long long LDS_BYTES = 8LL * (static_cast<long long>(N) * RS + CB * CS + twiddle_count<M>());
-  static constexpr bool FITS = LDS_BYTES <= 160 * 1024;
-  // the forward's window field (F <= N) is staged in the column regions for the binning
-  static_assert(M > 128 || !FITS || static_cast<long long>(CB) * CS >= static_cast<long long>(N) * N,
-                "window staging");
+  static constexpr int TABLE = ColSplit<M, PAD>::COUNT > 0 ? ColSplit<M, PAD>::COUNT : 1;
+  static constexpr long long LDS_BYTES =
+      8LL * (static_cast<long long>(N) * RS + twiddle_count<M>() + TABLE);
+  static constexpr bool FITS = ColSplit<M, PAD>::BUILT && LDS_BYTES <= 160 * 1024 && (PAD == 2 || M <= 96);
 };
 
 // forward rows of one layer: FIRST = input field times t_0, else inverse row transform of the
@@ -762,31 +1060,73 @@ __device__ __forceinline__ void lds_rows_forward(const LdsArgs& a, const WlConst
   }
 }
 
-// column transforms of one gap: rows [in_lo, in_hi) in, H or conj(H), rows [0, N) back
+// column transforms of one gap: rows [in_lo, in_hi) in, H or conj(H), rows [0, N) back.  The same
+// phases as the column kernels' (col_split_body), in place: a column's GL consecutive lanes lie in
+// one wavefront, slot (k1, j) is plane row j + R2 k1, which is the row thread's own, and the halves
+// follow each other.
 template <int M, int PAD, bool CONJ>
-__device__ __forceinline__ void lds_columns(const WlConst& c, double zrev, int in_lo, int in_hi,
-                                            float2* plane, float2* xch, const float2* tw) {
+__device__ __forceinline__ void lds_columns(const WlConst& c, const ColArgs& ca, int in_lo, int in_hi,
+                                            float2* plane, const float2* tab) {
   using G = LdsGeo<M, PAD>;
-  constexpr int E = Geo<M>::E, P = G::P, N = G::N, EN = E / PAD;
-  constexpr bool HALF = (PAD == 2);
-  const int g = threadIdx.x / P, j0 = threadIdx.x % P;
-  if (g >= G::CB) return;
-  float2* xr = xch + g * G::CS;
-  for (int kx = g; kx < M; kx += G::CB) {
-    float2 reg[E];
+  using S = ColSplit<M, PAD>;
+  constexpr int R1 = S::R1, R2 = S::R2, L = S::L, RS = G::RS;
+  constexpr int GL = pow2_at_least(L > S::GP ? L : S::GP);
+  constexpr int CB = kLdsThreads / GL;
+  const int lane = threadIdx.x % GL;
+  for (int kx = threadIdx.x / GL; kx < M; kx += CB) {
+    float2* col = plane + kx;
+    const bool rows = lane < L, freq = lane < R1;
+    float2 x[R1], b[S::NH][R1];
+    if (rows) {
 #pragma unroll
-    for (int t = 0; t < EN; ++t) {
-      const int y = j0 + P * t;
-      reg[t] = (y >= in_lo && y < in_hi) ? plane[y * G::RS + kx] : make_float2(0.f, 0.f);
+      for (int r = 0; r < R1; ++r) {
+        const int y = lane + L * r;
+        x[r] = (y >= in_lo && y < in_hi) ? col[y * RS] : make_float2(0.f, 0.f);
+      }
     }
-    fft<M, false, HALF>(reg, xr, j0, tw);
-    const int kxs = kx < M / 2 ? kx : kx - M;
-    const double base = c.q0 - static_cast<double>(kxs * kxs);
+    static_for<0, S::NH>([&](auto hc) {
+      constexpr int h = decltype(hc)::value;
+      if (rows) {
+        float2 v[R1];
 #pragma unroll
-    for (int t = 0; t < E; ++t) reg[t] = cmul(reg[t], transfer<M, CONJ>(zrev, base, j0 + P * t));
-    fft<M, true, false>(reg, xr, j0, tw);
+        for (int r = 0; r < R1; ++r) v[r] = x[r];
+        col_rows_forward<M, PAD, h == 1>(v);
 #pragma unroll
-    for (int t = 0; t < EN; ++t) plane[(j0 + P * t) * G::RS + kx] = reg[t];
+        for (int k = 0; k < R1; ++k) col[(lane + L * k) * RS] = v[k];
+      }
+      wave_sync();
+      if (freq) {
+        float2 v[R2];
+#pragma unroll
+        for (int i = 0; i < R2; ++i) v[i] = col[(i + L * lane) * RS];
+        col_freq_forward<M, PAD>(v, tab, h, lane);
+        apply_transfer<M, PAD, CONJ, kHEval, h>(v, ca, c, 0, kx, h, lane);
+        col_freq_inverse<M, PAD>(v);
+#pragma unroll
+        for (int i = 0; i < R2; ++i) col[(i + L * lane) * RS] = v[i];
+      }
+      wave_sync();
+      if (rows) {
+#pragma unroll
+        for (int k = 0; k < R1; ++k) b[h][k] = col[(lane + L * k) * RS];
+      }
+      wave_sync();
+    });
+    if (rows) {
+      if constexpr (S::NH == 2) {
+#pragma unroll
+        for (int parity = 0; parity < 2; ++parity) {
+          float2 y[S::RC];
+          col_rows_inverse2<M, PAD>(y, tab, lane, parity, [&](int h, int k) { return b[h][k]; });
+#pragma unroll
+          for (int r = 0; r < S::RC; ++r) col[(lane + L * (2 * r + parity)) * RS] = y[r];
+        }
+      } else {
+        col_rows_inverse<M, PAD>(b[0], tab, lane);
+#pragma unroll
+        for (int r = 0; r < R1; ++r) col[(lane + L * r) * RS] = b[0][r];
+      }
+    }
   }
 }
 
@@ -795,26 +1135,29 @@ __global__ void __launch_bounds__(kLdsThreads) lds_forward_kernel(LdsArgs a) {
   using G = LdsGeo<M, PAD>;
   constexpr int E = Geo<M>::E, P = G::P, N = G::N, EN = E / PAD;
   __shared__ float2 plane[N * G::RS];
-  __shared__ float2 xch[G::CB * G::CS];
   __shared__ float2 tw[twiddle_count<M>()];
+  __shared__ float2 tab[G::TABLE];
   stage_twiddles<M>(tw, a.tw, threadIdx.x, kLdsThreads);
+  for (int i = threadIdx.x; i < G::TABLE; i += kLdsThreads) tab[i] = a.col_tab[i];
   __syncthreads();
+  ColArgs gap{};  // what the transfer function of a column needs
   const int w = blockIdx.x;
   const WlConst c = a.wl[w];
   lds_rows_forward<M, PAD, true>(a, c, w, 0, plane, tw);
   __syncthreads();
   for (int l = 0; l < a.K; ++l) {
-    lds_columns<M, PAD, false>(c, a.zrev[l], 0, N, plane, xch, tw);
+    gap.zrev = a.zrev[l];
+    lds_columns<M, PAD, false>(c, gap, 0, N, plane, tab);
     __syncthreads();
     if (l + 1 < a.K) {
       lds_rows_forward<M, PAD, false>(a, c, w, l + 1, plane, tw);
       __syncthreads();
     }
   }
-  // last inverse row transforms on the window rows: output field, and its intensity in bins
+  // last inverse row transforms on the window rows: output field, and its intensity in bins (the
+  // window rows go back in place of their spectra)
   const int F = a.fov, x0 = (N - F) / 2, T = F / a.bin;
   const int g = threadIdx.x / P, j0 = threadIdx.x % P;
-  float2* win = xch;  // the column regions are free now
   for (int y = x0 + g; y < x0 + F; y += G::RB) {
     float2* row = plane + y * G::RS;
     float2 reg[E];
@@ -827,13 +1170,14 @@ __global__ void __launch_bounds__(kLdsThreads) lds_forward_kernel(LdsArgs a) {
       const int x = j0 + P * t;
       if (x >= x0 && x < x0 + F) {
         dst[x - x0] = reg[t];
-        win[(y - x0) * F + x - x0] = reg[t];
+        row[x] = reg[t];
       }
     }
   }
   __syncthreads();
   for (int i = threadIdx.x; i < T * T; i += kLdsThreads)
-    bin_intensity_body(win, a.intensity + static_cast<size_t>(w) * T * T, 1, F, a.bin, i);
+    a.intensity[static_cast<size_t>(w) * T * T + i] =
+        bin_sum(plane + (x0 + i / T * a.bin) * G::RS + x0 + i % T * a.bin, G::RS, a.bin);
 }
 
 template <int M, int PAD>
@@ -842,10 +1186,12 @@ __global__ void __launch_bounds__(kLdsThreads) lds_adjoint_kernel(LdsArgs a) {
   constexpr int E = Geo<M>::E, P = G::P, N = G::N, EN = E / PAD;
   constexpr bool HALF = (PAD == 2);
   __shared__ float2 plane[N * G::RS];
-  __shared__ float2 xch[G::CB * G::CS];
   __shared__ float2 tw[twiddle_count<M>()];
+  __shared__ float2 tab[G::TABLE];
   stage_twiddles<M>(tw, a.tw, threadIdx.x, kLdsThreads);
+  for (int i = threadIdx.x; i < G::TABLE; i += kLdsThreads) tab[i] = a.col_tab[i];
   __syncthreads();
+  ColArgs gap{};  // what the transfer function of a column needs
   const int w = blockIdx.x;
   const WlConst c = a.wl[w];
   const int F = a.fov, b = a.bin, T = F / b, x0 = (N - F) / 2;
@@ -872,9 +1218,10 @@ __global__ void __launch_bounds__(kLdsThreads) lds_adjoint_kernel(LdsArgs a) {
     for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
   }
   __syncthreads();
-  const float ct = static_cast<float>(c.ct), ca = static_cast<float>(c.ca);
+  const float ct = c.ct, ca = static_cast<float>(c.ca);
   for (int l = a.K - 1; l >= 0; --l) {
-    lds_columns<M, PAD, true>(c, a.zrev[l], l == a.K - 1 ? x0 : 0, l == a.K - 1 ? x0 + F : N, plane, xch, tw);
+    gap.zrev = a.zrev[l];
+    lds_columns<M, PAD, true>(c, gap, l == a.K - 1 ? x0 : 0, l == a.K - 1 ? x0 + F : N, plane, tab);
     __syncthreads();
     for (int y = g; y < N; y += G::RB) {
       float2* row = plane + y * G::RS;

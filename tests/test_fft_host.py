@@ -35,3 +35,18 @@ def test_lds_layouts_fit_their_regions(tmp_path):
     subprocess.run(cmd, check=True, capture_output=True, text=True)
     run = subprocess.run([str(exe)], capture_output=True, text=True)
     assert run.returncode == 0 and run.stdout.strip() == "ok", run.stdout
+
+
+@pytest.mark.skipif(shutil.which("g++") is None, reason="no host C++ compiler")
+def test_column_split_transforms_match_the_dft(tmp_path):
+    """The two-phase column transforms of every built length (host build of col_fft.hpp): forward
+    against the DFT in double precision, forward and inverse back to the rows, and their LDS slots."""
+    exe = tmp_path / "col_split"
+    cmd = ["g++", "-O2", "-std=c++17", "-ffp-contract=off", "-I", os.path.join(HERE, "host_fft"),
+           "-I", CSRC, os.path.join(HERE, "host_fft", "col_split.cpp"), "-o", str(exe)]
+    subprocess.run(cmd, check=True, capture_output=True, text=True)
+    run = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert run.returncode == 0, run.stdout
+    forward, back = (float(x) for x in run.stdout.split())
+    # at most ten butterfly levels of a few half-ulp (6e-8) roundings each, adding in quadrature
+    assert forward < 4e-7 and back < 6e-7, (forward, back)

@@ -1,0 +1,97 @@
+"""Column passes with split transforms, and the spectrum columns outside the propagating disc, which
+are neither written nor read."""
+import numpy as np
+import pytest
+
+from oracle import dpx_oracle as o
+from paper_2604_02624_amd import workloads as wk
+
+pytestmark = pytest.mark.gpu
+
+INT_TOL = 1e-5   # intensities against the FP64 oracle, relative L2 per wavelength
+GRAD_TOL = 1e-4  # dL/dh against the oracle adjoint
+
+
+@pytest.fixture(scope="module")
+def torch_dev():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+def design(n, pad, n_wl, layers=2, lo=420e-9, hi=900e-9):
+    # pitch 200 nm: the disc radius M dx / lambda runs from 0.48 M (nearly every column propagates)
+    # down to 0.22 M (more than half of them do not)
+    wl = np.linspace(lo, hi, n_wl) if n_wl > 1 else np.array([hi])
+    return wk.make_design(n=n, layers=layers, wl=wl, n_mat=wk.cauchy_index(wl), dx=200e-9, z=9e-6,
+                          fov=n // 2, pad=pad)
+
+
+def outputs(torch, plan, h, dl_di):
+    I = plan.forward(h)
+    dh = plan.backward(h, None, dl_di)
+    torch.cuda.synchronize()
+    return I.cpu().numpy(), dh.cpu().numpy()
+
+
+@pytest.mark.parametrize("n,pad", [(32, 2), (48, 2), (64, 2), (96, 2), (128, 2), (192, 2), (256, 2), (512, 2), (800, 2),
+                                   (64, 1), (96, 1), (128, 1), (192, 1), (256, 1), (384, 1), (512, 1)])
+def test_columns_outside_the_disc(torch_dev, n, pad):
+    """Against the oracle, and after the planes were filled with NaN: what an earlier call left in the
+    columns outside the disc must not reach a result."""
+    from paper_2604_02624_amd import dpx
+    torch = torch_dev
+    d = design(n, pad, 3)
+    g = np.random.default_rng(n + pad)
+    h = (g.random((2, n, n)) * 1.1e-6).astype(np.float32)
+    tau = g.random((3, n // 2, n // 2)).astype(np.float32)
+    I_ref = o.forward(d, h, None, "fft")
+    _, g_ref, _ = o.loss(I_ref, tau)
+    g32 = g_ref.astype(np.float32)
+    plan = dpx.Plan([d])
+    ht, gt = plan.pack_heights([h]), plan.pack_images([g32])
+    I, dh = outputs(torch, plan, ht, gt)
+    I = I.reshape(I_ref.shape)
+    err = max(np.linalg.norm(I[w] - I_ref[w]) / np.linalg.norm(I_ref[w]) for w in range(3))
+    assert err <= INT_TOL, err
+    dh_ref = o.grad(d, h, None, g32, "fft")
+    assert np.linalg.norm(dh.reshape(h.shape) - dh_ref) <= GRAD_TOL * np.linalg.norm(dh_ref)
+    # every propagating wavelength at 200 nm fills all columns of the plane, so NaN heights on short
+    # waves leave NaN everywhere the long ones will not look
+    short = np.full(3, 390e-9)
+    plan.set_wavelengths(0, short, wk.cauchy_index(short))
+    outputs(torch, plan, torch.full_like(ht, float("nan")), gt)
+    plan.set_wavelengths(0, d["wl"], d["n_mat"])
+    again = outputs(torch, plan, ht, gt)
+    assert np.array_equal(again[0].reshape(I.shape), I) and np.array_equal(again[1], dh)
+    plan.close()
+
+
+@pytest.mark.parametrize("n,pad,n_wl", [(32, 2, 4099), (64, 1, 4099), (96, 2, 1371), (128, 2, 1029), (256, 2, 515)])
+def test_many_wavelengths_and_gradient_slots(torch_dev, n, pad, n_wl):
+    """Odd counts that leave the last column block and the last gradient slot short: a few wavelengths
+    alone give the bits they have among all (intensities), and the gradient of a loss on them is the
+    oracle's."""
+    from paper_2604_02624_amd import dpx
+    torch = torch_dev
+    d = design(n, pad, n_wl)
+    g = np.random.default_rng(n_wl)
+    h = (g.random((2, n, n)) * 1.1e-6).astype(np.float32)
+    t = n // 2
+    pick = [0, 1, n_wl // 2, n_wl - 2, n_wl - 1]
+    sub = wk.subset_wavelengths(d, pick)
+    I_ref = o.forward(sub, h, None, "fft")
+    _, g_ref, _ = o.loss(I_ref, g.random((len(pick), t, t)))
+    g32 = g_ref.astype(np.float32)
+    dl = np.zeros((n_wl, t, t), np.float32)
+    dl[pick] = g32
+    plan, few = dpx.Plan([d]), dpx.Plan([sub])
+    ht = plan.pack_heights([h])
+    I, dh = outputs(torch, plan, ht, plan.pack_images([dl]))
+    I_few, _ = outputs(torch, few, ht, few.pack_images([g32]))
+    assert np.array_equal(I.reshape(n_wl, t, t)[pick], I_few.reshape(len(pick), t, t))
+    dh_ref = o.grad(sub, h, None, g32, "fft")
+    assert np.linalg.norm(dh.reshape(h.shape) - dh_ref) <= GRAD_TOL * np.linalg.norm(dh_ref)
+    plan.close()
+    few.close()
