@@ -48,6 +48,7 @@ dpx_status ok() {
       return fail(DPX_E_DEVICE, "%s failed: %s", #call, hipGetErrorString(e_));        \
   } while (0)
 
+constexpr int kOneLaunchLoss = 256;  // most wavelengths whose loss is summed by the last block
 constexpr double kTwoPi = 6.283185307179586476925286766559;
 
 struct Design {
@@ -87,6 +88,7 @@ struct Design {
   float2* ofov = nullptr;
   float* dh_part = nullptr;
   double* per_wl = nullptr;
+  unsigned* arrived = nullptr;  // finished blocks of the loss launch (inside the plan's tables)
   int64_t bytes = 0;
 };
 
@@ -616,14 +618,19 @@ dpx_status run_col(dpx_plan* p, const Design& d, int lane, int layer, bool conj,
 
 int64_t h_off_layer(const Design& d, int l) { return d.h_off + static_cast<int64_t>(l) * d.N * d.N; }
 
+// Whether the last row pass also forms the intensities: its blocks hold whole detector bins.  Else
+// (1600 points: three rows per block) the binning is a launch of its own.
+bool bins_in_rows(const Design& d) { return dpx::row_rows_per_block(d.M, dpx::ROW_FWD_LAST) % d.b == 0; }
+
 // forward over one chunk of wavelengths [w0, w0 + wc) on lane `lane`; leaves the output
-// field in ofov.  `after_first` (may be null) is recorded on s after the first launch.
-dpx_status forward_chunk(dpx_plan* p, const Design& d, const float* h, const float* u_in,
+// field in ofov, and the intensities where bins_in_rows (unless `intensity` is null).  `after_first` (may be null) is recorded on s after the first launch.
+dpx_status forward_chunk(dpx_plan* p, const Design& d, const float* h, const float* u_in, float* intensity,
                          int w0, int wc, int lane, hipStream_t s, hipEvent_t after_first) {
   const int fo = (d.N - d.F) / 2;
   RowArgs a = row_args(p, d, w0, wc, lane);
   a.u_in = u_in ? reinterpret_cast<const float2*>(u_in) + d.u_off : nullptr;
   a.layer = 0;
+  a.intensity = intensity && bins_in_rows(d) ? intensity + d.img_off : nullptr;
   if (d.z_in > 0.0) {
     // input plane: u_in to the spectrum unchanged, across the input gap, then layer 0 as a
     // middle pass (row inverse transform, transmission, checkpoint, row transform)
@@ -658,10 +665,11 @@ dpx_status forward_chunk(dpx_plan* p, const Design& d, const float* h, const flo
   return DPX_OK;
 }
 
-// adjoint over one chunk on lane `lane`; dL/dh partials go to the lane's own slots, added to
+// adjoint over one chunk on lane `lane` (dl_dh: null, or the output itself for a design with a single
+// gradient slot); dL/dh partials go to the lane's own slots, added to
 // what the lane's earlier chunks left there when `accumulate` is set
 dpx_status adjoint_chunk(dpx_plan* p, const Design& d, const float* h, const float* u_in, const float* dl_di,
-                         int w0, int wc, int lane, bool accumulate, hipStream_t s,
+                         float* dl_dh, int w0, int wc, int lane, bool accumulate, hipStream_t s,
                          hipEvent_t after_first) {
   const int fo = (d.N - d.F) / 2;
   RowArgs a = row_args(p, d, w0, wc, lane);
@@ -669,6 +677,7 @@ dpx_status adjoint_chunk(dpx_plan* p, const Design& d, const float* h, const flo
   a.dl_di = dl_di + d.img_off;
   a.store_ckpt = 0;
   a.accumulate = accumulate ? 1 : 0;
+  if (dl_dh) a.dh_part = dl_dh + d.h_off;  // one slot: its partials are the gradient
   DPX_TRY(run_row(p, d, dpx::ROW_ADJ_SEED, a, fo, fo + d.F, s));
   if (after_first) DPX_HIP(hipEventRecord(after_first, s));
   for (int l = d.K - 1; l >= 0; --l) {
@@ -752,6 +761,7 @@ void add_row_position(dpx_plan* p, const std::vector<RowItem>& items, std::vecto
       t.a.layer = it.layer;
       t.a.row_lo = it.row_lo;
       t.a.row_hi = it.row_hi;
+      t.bins = it.mode == dpx::ROW_FWD_LAST && bins_in_rows(d) ? 1 : 0;
       t.h_off = h_off_layer(d, it.layer);
       t.u_off = d.u_off;
       t.img_off = d.img_off;
@@ -878,6 +888,7 @@ void build_group_lists(dpx_plan* p, const std::vector<int>& ids, std::vector<Gro
     std::vector<int> nb;
     for (int i : ids) {
       const Design& d = p->designs[i];
+      if (bins_in_rows(d)) continue;
       bins.push_back({d.ofov, d.img_off, d.W, d.F, d.b});
       nb.push_back(static_cast<int>((static_cast<int64_t>(d.W) * d.T * d.T + dpx::kGroupThreads - 1) /
                                     dpx::kGroupThreads));
@@ -966,6 +977,7 @@ dpx_status run_groups(dpx_plan* p, const std::vector<GroupLaunch>& launches, con
   for (const auto& L : launches) {
     dpx::GroupArgs g = L.g;
     g.call = call;
+    g.call.intensity = out_f;
     TimedLaunch t{L.pass, nullptr, nullptr, L.bytes + (call.u_in ? L.u_bytes : 0), L.flops};
     if (L.kind == GK_COL && L.full) t.instance = L.conj ? DPX_PASS_COL_ADJ_FULL : DPX_PASS_COL_FWD_FULL;
     const bool timed = (L.kind == GK_ROW || L.kind == GK_COL);
@@ -1458,12 +1470,15 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
       add_table(tw_key(d.M, pl), [&](std::vector<float2>& t) { dpx::build_twiddle_table(d.M, pl, t); });
     if (dpx::col_split(d.M, d.pad))
       add_table(col_key(d.M, d.pad), [&](std::vector<float2>& t) { dpx::build_col_table(d.M, d.pad, t); });
-    if (!tables.empty()) {
+    const size_t count_at = tables.size();
+    tables.resize(count_at + 32, make_float2(0.f, 0.f));
+    {
       float2* dt = nullptr;
       const int64_t tb = static_cast<int64_t>(tables.size()) * 8;
       if ((st = dev_alloc(&dt, tb, "twiddles")) != DPX_OK) break;
       p->table_allocs.push_back(dt);
       for (const auto& kv : parts) p->twiddles[kv.first] = dt + kv.second;
+      d.arrived = reinterpret_cast<unsigned*>(dt + count_at);
       if (hipMemcpy(dt, tables.data(), tb, hipMemcpyHostToDevice) != hipSuccess) {
         st = fail(DPX_E_DEVICE, "copy of the twiddle tables failed");
         break;
@@ -1718,8 +1733,9 @@ dpx_status dpx_forward(dpx_plan* p, const float* h, const float* u_in, float* in
         const int wc = std::min(d.wl_chunk, d.W - w0);
         hipStream_t ls = lane_stream(p, lane, s);
         if (lane == 1 && c == 1) DPX_HIP(hipStreamWaitEvent(ls, p->ev_offset, 0));
-        DPX_TRY(forward_chunk(p, d, h, u_in, w0, wc, lane, ls,
+        DPX_TRY(forward_chunk(p, d, h, u_in, intensity, w0, wc, lane, ls,
                               (c == 0 && d.lanes > 1) ? p->ev_offset : nullptr));
+        if (bins_in_rows(d)) continue;
         const float2* of = (p->opts.checkpoint_mode == 1)
                                ? d.ofov + static_cast<int64_t>(lane) * d.wl_chunk * d.F * d.F
                                : d.ofov + static_cast<int64_t>(w0) * d.F * d.F;
@@ -1758,9 +1774,13 @@ dpx_status dpx_loss(dpx_plan* p, const float* intensity, const float* target, do
       return DPX_OK;
     }
     return for_each_design(p, s0, [&](const Design& d, int i, hipStream_t s) -> dpx_status {
+      // few wavelengths: the last block sums them; many: a launch of its own costs less than their
+      // blocks' counting on one address
+      const bool one_launch = d.W <= kOneLaunchLoss;
       hipError_t e = dpx::launch_loss(intensity + d.img_off, target + d.img_off,
-                                      dl_di ? dl_di + d.img_off : nullptr, d.per_wl, d.W, d.T, s);
-      if (e == hipSuccess) e = dpx::launch_loss_sum(d.per_wl, loss + i, d.W, s);
+                                      dl_di ? dl_di + d.img_off : nullptr, d.per_wl, d.W, d.T,
+                                      one_launch ? d.arrived : nullptr, loss + i, s);
+      if (e == hipSuccess && !one_launch) e = dpx::launch_loss_sum(d.per_wl, loss + i, d.W, s);
       if (e != hipSuccess) return fail(DPX_E_DEVICE, "loss launch failed: %s", hipGetErrorString(e));
       return DPX_OK;
     });
@@ -1807,7 +1827,7 @@ dpx_status dpx_backward(dpx_plan* p, const float* h, const float* u_in, const fl
         if (lane == 1 && c == 1) DPX_HIP(hipStreamWaitEvent(ls, p->ev_offset, 0));
         hipEvent_t first_ev = (c == 0 && d.lanes > 1) ? p->ev_offset : nullptr;
         if (!store) {
-          DPX_TRY(forward_chunk(p, d, h, u_in, w0, wc, lane, ls, first_ev));
+          DPX_TRY(forward_chunk(p, d, h, u_in, nullptr, w0, wc, lane, ls, first_ev));
           first_ev = nullptr;
         }
         if (c < d.lanes) {
@@ -1822,9 +1842,11 @@ dpx_status dpx_backward(dpx_plan* p, const float* h, const float* u_in, const fl
             if (e != hipSuccess) return fail(DPX_E_DEVICE, "slot clearing launch failed: %s", hipGetErrorString(e));
           }
         }
-        DPX_TRY(adjoint_chunk(p, d, h, u_in, dl_di, w0, wc, lane, c >= d.lanes, ls, first_ev));
+        DPX_TRY(adjoint_chunk(p, d, h, u_in, dl_di, d.nslots == 1 ? dl_dh : nullptr, w0, wc, lane, c >= d.lanes, ls,
+                              first_ev));
       }
       DPX_TRY(join_lanes(p, d, s));
+      if (d.nslots == 1) return DPX_OK;  // the row passes wrote dl_dh
       const int64_t per = static_cast<int64_t>(d.K) * d.N * d.N;
       hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.nslots, per, s);
       if (e != hipSuccess) return fail(DPX_E_DEVICE, "gradient reduction launch failed: %s", hipGetErrorString(e));
@@ -1854,7 +1876,7 @@ dpx_status dpx_loss_static(const float* intensity, const float* target, int32_t 
   hipStream_t s = static_cast<hipStream_t>(stream);
   // every partial is written by the first kernel before the second reads it, so the array
   // needs no clearing
-  e = dpx::launch_loss(intensity, target, dl_di, part, n_wl, T, s);
+  e = dpx::launch_loss(intensity, target, dl_di, part, n_wl, T, nullptr, nullptr, s);
   if (e == hipSuccess) e = dpx::launch_loss_sum(part, loss, n_wl, s);
   if (e != hipSuccess) return fail(DPX_E_DEVICE, "loss launch failed: %s", hipGetErrorString(e));
   return ok();

@@ -58,6 +58,7 @@ struct RowArgs {
                              // (chunk-local w); slab 0 holds layer ckpt_first
   float2* ofov;              // [wc][F][F] output field on the field of view
   const float* dl_di;        // [W][T][T] (global w)
+  float* intensity;          // ROW_FWD_LAST: [W][T][T] (global w) or null (formed elsewhere)
   float* dh_part;            // [nchunk][K][N][N] per-chunk dL/dh partial sums
   const WlConst* wl;         // [W] (global w)
   const float2* tw;          // per-stage twiddle table of the transform length
@@ -160,6 +161,7 @@ struct CallBuffers {
   const float* h;            // packed heights (all designs)
   const float2* u_in;        // packed input fields or null
   const float* dl_di;        // packed dL/dI or null
+  float* intensity = nullptr;  // packed intensities (forward lists)
 };
 
 struct GroupArgs {
@@ -174,6 +176,7 @@ struct RowTask {
   int64_t h_off, u_off, img_off;
   int gx;                    // row blocks (x extent of the design's own grid)
   int nblocks;               // gx times the wavelength blocks
+  int bins;                  // ROW_FWD_LAST: the pass forms the intensities
 };
 
 struct ColTask {
@@ -272,8 +275,10 @@ hipError_t launch_col(int M, int pad, bool conj, int variant, int plan, const Co
 hipError_t launch_transfer_table(int M, const WlConst* wl, int W, double zrev, float2* out, hipStream_t s);
 hipError_t launch_bin_intensity(const float2* ofov, float* out, int w_count, int fov, int bin,
                                 hipStream_t s);
+// arrived / loss: null, or a zeroed count that the launch leaves zeroed and the design's loss: then
+// the last block also sums the wavelengths (else launch_loss_sum does)
 hipError_t launch_loss(const float* I, const float* tau, float* dl_di, double* per_wl, int W, int T,
-                       hipStream_t s);
+                       unsigned* arrived, double* loss, hipStream_t s);
 hipError_t launch_loss_sum(const double* per_wl, double* loss, int W, hipStream_t s);
 // most wavelengths dpx_loss_static takes (its partials live in a fixed device array)
 constexpr int kStaticLossMaxWl = 65536;

@@ -30,94 +30,192 @@ __global__ void bin_group_kernel(GroupArgs g, float* __restrict__ out) {
 }
 
 constexpr int kLossThreads = 256;
+constexpr int kLossThreadsLarge = 1024;  // images of more than 8192 pixels, one design per launch
+constexpr int kLossCache = 16;           // pixels a thread keeps in registers
 
-__device__ double block_sum(double v, double* sh) {
-  sh[threadIdx.x] = v;
-  __syncthreads();
-  for (int s = kLossThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] += sh[threadIdx.x + s];
-    __syncthreads();
-  }
-  const double r = sh[0];
-  __syncthreads();
-  return r;
+// v plus its neighbour's value under the DPP control CTRL (0 where there is none)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_neighbour(double v) {
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, static_cast<int>(b), CTRL, ROWS, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, static_cast<int>(b >> 32), CTRL, ROWS, 0xf, true);
+  return __longlong_as_double((static_cast<long long>(hi) << 32) | static_cast<unsigned>(lo));
 }
 
-// One block per wavelength w: sums in double in a fixed tree order (bitwise reproducible).
+// Lane 63 ends with the combination of the wavefront's 64 values, in a fixed order: rows of 16 by
+// shifts, then the rows' last lanes broadcast into the rows behind.  For sums, and maxima of
+// non-negative values (missing neighbours count as zero).
+template <typename Op>
+__device__ __forceinline__ double wave_combine(double v, Op op) {
+  v = op(v, dpp_neighbour<0x111, 0xf>(v));  // row_shr 1, 2, 4, 8
+  v = op(v, dpp_neighbour<0x112, 0xf>(v));
+  v = op(v, dpp_neighbour<0x114, 0xf>(v));
+  v = op(v, dpp_neighbour<0x118, 0xf>(v));
+  v = op(v, dpp_neighbour<0x142, 0xa>(v));  // row_bcast 15 into rows 1 and 3
+  v = op(v, dpp_neighbour<0x143, 0xc>(v));  // row_bcast 31 into rows 2 and 3
+  return v;
+}
+
+// Combination over the block, in every thread; sh: THREADS / 64 doubles of this call's own.
+template <int THREADS, typename Op>
+__device__ __forceinline__ void block_combine_begin(double v, double* sh, Op op) {
+  v = wave_combine(v, op);
+  if ((threadIdx.x & 63) == 63) sh[threadIdx.x >> 6] = v;
+}
+template <int THREADS, typename Op>
+__device__ __forceinline__ double block_combine_end(const double* sh, Op op) {
+  double r = sh[0];
+#pragma unroll
+  for (int k = 1; k < THREADS / 64; ++k) r = op(r, sh[k]);
+  return r;
+}
+struct Plus {
+  __device__ __forceinline__ double operator()(double a, double b) const { return a + b; }
+};
+struct Max {
+  __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); }
+};
+
+// The pixels of one wavelength's image and target, walked several times: from registers where a
+// thread has at most kLossCache of them, else from memory.
+template <int THREADS, bool CACHED>
+struct Pixels {
+  const float* __restrict__ I;
+  const float* __restrict__ tau;
+  int P;
+  float iv[CACHED ? kLossCache : 1], tv[CACHED ? kLossCache : 1];
+  __device__ __forceinline__ Pixels(const float* I_, const float* tau_, int P_) : I(I_), tau(tau_), P(P_) {
+    if constexpr (CACHED) {
+#pragma unroll
+      for (int k = 0; k < kLossCache; ++k) {
+        const int p = threadIdx.x + k * THREADS;
+        iv[k] = p < P ? I[p] : 0.f;
+        tv[k] = p < P ? tau[p] : 0.f;
+      }
+    }
+  }
+  template <typename F>
+  __device__ __forceinline__ void each(F&& f) const {
+    if constexpr (CACHED) {
+#pragma unroll
+      for (int k = 0; k < kLossCache; ++k)
+        if (threadIdx.x + k * THREADS < P) f(static_cast<int>(threadIdx.x + k * THREADS), iv[k], tv[k]);
+    } else {
+#pragma unroll 4
+      for (int p = threadIdx.x; p < P; p += THREADS) f(p, I[p], tau[p]);
+    }
+  }
+};
+
+// One block per wavelength w: sums in double in a fixed order (bitwise reproducible).  Bound by
+// latency: each image is read once into registers and the two rounds of sums cost one block barrier
+// each (a tree of barriers and three walks over memory took 7 us at 6 images of 32 x 32 and 27 us
+// at 1024 of 64 x 64).
+template <int THREADS, bool CACHED>
+__device__ __forceinline__ void loss_image(const float* __restrict__ Iw, const float* __restrict__ tw,
+                                           float* __restrict__ gw, double* __restrict__ out, int W, int P, double* sh) {
+  constexpr int WAVES = THREADS / 64;
+  const Pixels<THREADS, CACHED> px(Iw, tw, P);
+  double si = 0.0, st = 0.0;
+  px.each([&](int, float i, float t) {
+    si += i;
+    st += t;
+  });
+  block_combine_begin<THREADS>(si, sh, Plus{});
+  block_combine_begin<THREADS>(st, sh + WAVES, Plus{});
+  __syncthreads();
+  const double S = block_combine_end<THREADS>(sh, Plus{}), St = block_combine_end<THREADS>(sh + WAVES, Plus{});
+  const double rS = S > 0.0 ? 1.0 / S : 0.0;
+  const double rSt = St > 0.0 ? 1.0 / St : 0.0;
+  double sd2 = 0.0, sdi = 0.0;
+  px.each([&](int, float i, float t) {
+    const double ih = i * rS;
+    const double d = ih - t * rSt;
+    sd2 += d * d;
+    sdi += d * ih;
+  });
+  block_combine_begin<THREADS>(sd2, sh + 2 * WAVES, Plus{});
+  block_combine_begin<THREADS>(sdi, sh + 3 * WAVES, Plus{});
+  __syncthreads();
+  const double D2 = block_combine_end<THREADS>(sh + 2 * WAVES, Plus{});
+  const double inner = block_combine_end<THREADS>(sh + 3 * WAVES, Plus{});
+  if (threadIdx.x == 0) *out = D2 / P;
+  if (gw) {
+    const double k = 2.0 * rS / (static_cast<double>(W) * P);
+    px.each([&](int p, float i, float t) {
+      const double d = i * rS - t * rSt;
+      gw[p] = static_cast<float>(k * (d - inner));
+    });
+  }
+}
+
+template <int THREADS>
 __device__ __forceinline__ void loss_body(const float* __restrict__ I, const float* __restrict__ tau,
                                           float* __restrict__ dl_di, double* __restrict__ per_wl,
                                           int W, int T, int w, double* sh) {
   const int P = T * T;
-  const float* Iw = I + static_cast<size_t>(w) * P;
-  const float* tw = tau + static_cast<size_t>(w) * P;
-  double si = 0.0, st = 0.0;
-  for (int p = threadIdx.x; p < P; p += kLossThreads) {
-    si += Iw[p];
-    st += tw[p];
-  }
-  const double S = block_sum(si, sh);
-  const double St = block_sum(st, sh);
-  const double rS = S > 0.0 ? 1.0 / S : 0.0;
-  const double rSt = St > 0.0 ? 1.0 / St : 0.0;
-  double sd2 = 0.0, sdi = 0.0;
-  for (int p = threadIdx.x; p < P; p += kLossThreads) {
-    const double ih = Iw[p] * rS;
-    const double d = ih - tw[p] * rSt;
-    sd2 += d * d;
-    sdi += d * ih;
-  }
-  const double D2 = block_sum(sd2, sh);
-  const double inner = block_sum(sdi, sh);
-  if (threadIdx.x == 0) per_wl[w] = D2 / P;
-  if (dl_di) {
-    const double k = 2.0 * rS / (static_cast<double>(W) * P);
-    float* gw = dl_di + static_cast<size_t>(w) * P;
-    for (int p = threadIdx.x; p < P; p += kLossThreads) {
-      const double ih = Iw[p] * rS;
-      const double d = ih - tw[p] * rSt;
-      gw[p] = static_cast<float>(k * (d - inner));
-    }
-  }
+  const size_t o = static_cast<size_t>(w) * P;
+  float* gw = dl_di ? dl_di + o : nullptr;
+  if (P <= THREADS * kLossCache) loss_image<THREADS, true>(I + o, tau + o, gw, per_wl + w, W, P, sh);
+  else loss_image<THREADS, false>(I + o, tau + o, gw, per_wl + w, W, P, sh);
 }
 
-__global__ void __launch_bounds__(kLossThreads)
+template <int THREADS>
+__device__ __forceinline__ void loss_sum_body(const double* __restrict__ per_wl, double* __restrict__ loss,
+                                              int W, double* sh) {
+  double s = 0.0;
+#pragma unroll 4
+  for (int w = threadIdx.x; w < W; w += THREADS) s += per_wl[w];
+  block_combine_begin<THREADS>(s, sh, Plus{});
+  __syncthreads();
+  if (threadIdx.x == 0) *loss = block_combine_end<THREADS>(sh, Plus{}) / W;
+}
+
+// arrived: null, or the design's count of finished blocks; then the block that finishes last also
+// sums the wavelengths' losses (and returns the count to zero), which saves the launch that would.
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
 loss_kernel(const float* __restrict__ I, const float* __restrict__ tau, float* __restrict__ dl_di,
-            double* __restrict__ per_wl, int W, int T) {
-  __shared__ double sh[kLossThreads];
-  loss_body(I, tau, dl_di, per_wl, W, T, blockIdx.x, sh);
+            double* __restrict__ per_wl, int W, int T, unsigned* __restrict__ arrived, double* __restrict__ loss) {
+  __shared__ double sh[4 * (THREADS / 64)];
+  __shared__ bool last;
+  loss_body<THREADS>(I, tau, dl_di, per_wl, W, T, blockIdx.x, sh);
+  if (!arrived) return;
+  if (threadIdx.x == 0) {
+    __threadfence();  // per_wl[w] before the count, for the block on another XCD that reads it
+    last = atomicAdd(arrived, 1u) == static_cast<unsigned>(W) - 1u;
+  }
+  __syncthreads();
+  if (!last) return;
+  __threadfence();
+  if (threadIdx.x == 0) *arrived = 0;
+  loss_sum_body<THREADS>(per_wl, loss, W, sh);
 }
 
 // grouped: task = one design, one block per wavelength of every design
 __global__ void __launch_bounds__(kLossThreads)
 loss_group_kernel(GroupArgs g, const float* __restrict__ I, const float* __restrict__ tau,
                   float* __restrict__ dl_di) {
-  __shared__ double sh[kLossThreads];
+  __shared__ double sh[4 * (kLossThreads / 64)];
   const int ti = group_task(g, blockIdx.x);
   const LossTask& t = static_cast<const LossTask*>(g.tasks)[ti];
   const int w = static_cast<int>(blockIdx.x) - g.block0[ti];
-  loss_body(I + t.img_off, tau + t.img_off, dl_di ? dl_di + t.img_off : nullptr, t.per_wl, t.W, t.T, w, sh);
-}
-
-__device__ __forceinline__ void loss_sum_body(const double* __restrict__ per_wl, double* __restrict__ loss,
-                                              int W, double* sh) {
-  double s = 0.0;
-  for (int w = threadIdx.x; w < W; w += kLossThreads) s += per_wl[w];
-  const double tot = block_sum(s, sh);
-  if (threadIdx.x == 0) *loss = tot / W;
+  loss_body<kLossThreads>(I + t.img_off, tau + t.img_off, dl_di ? dl_di + t.img_off : nullptr, t.per_wl, t.W, t.T, w,
+                          sh);
 }
 
 __global__ void __launch_bounds__(kLossThreads)
 loss_sum_kernel(const double* __restrict__ per_wl, double* __restrict__ loss, int W) {
-  __shared__ double sh[kLossThreads];
-  loss_sum_body(per_wl, loss, W, sh);
+  __shared__ double sh[kLossThreads / 64];
+  loss_sum_body<kLossThreads>(per_wl, loss, W, sh);
 }
 
 // grouped: block i = design i of the plan (tasks in design order)
 __global__ void __launch_bounds__(kLossThreads)
 loss_sum_group_kernel(const LossTask* __restrict__ tasks, double* __restrict__ loss) {
-  __shared__ double sh[kLossThreads];
+  __shared__ double sh[kLossThreads / 64];
   const LossTask& t = tasks[blockIdx.x];
-  loss_sum_body(t.per_wl, loss + blockIdx.x, t.W, sh);
+  loss_sum_body<kLossThreads>(t.per_wl, loss + blockIdx.x, t.W, sh);
 }
 
 // Fixed device array for the per-wavelength loss partials of dpx_loss_static (callers that cannot
@@ -266,41 +364,47 @@ __global__ void adam_sigmoid_kernel(float* __restrict__ theta, float* __restrict
 // Per-wavelength PSNR of the intensity image against its target, both normalised to unit sum
 // (as in the loss): 10 log10(max_p tau^2 / mean_p (I - tau)^2), in double; one block per
 // wavelength of one design ([W][T][T] images, out [W]).
-__global__ void __launch_bounds__(kLossThreads)
-psnr_kernel(const float* __restrict__ I, const float* __restrict__ tau, double* __restrict__ out, int T) {
-  __shared__ double sh[kLossThreads];
-  const int w = blockIdx.x;
-  const int P = T * T;
-  const float* Iw = I + static_cast<size_t>(w) * P;
-  const float* tw = tau + static_cast<size_t>(w) * P;
+template <int THREADS, bool CACHED>
+__device__ __forceinline__ void psnr_image(const float* __restrict__ Iw, const float* __restrict__ tw,
+                                           double* __restrict__ out, int P, double* sh) {
+  constexpr int WAVES = THREADS / 64;
+  const Pixels<THREADS, CACHED> px(Iw, tw, P);
   double si = 0.0, st = 0.0, mx = 0.0;
-  for (int p = threadIdx.x; p < P; p += kLossThreads) {
-    si += Iw[p];
-    st += tw[p];
-    mx = fmax(mx, static_cast<double>(tw[p]));
-  }
-  const double S = block_sum(si, sh);
-  const double St = block_sum(st, sh);
-  sh[threadIdx.x] = mx;
+  px.each([&](int, float i, float t) {
+    si += i;
+    st += t;
+    mx = fmax(mx, static_cast<double>(t));
+  });
+  block_combine_begin<THREADS>(si, sh, Plus{});
+  block_combine_begin<THREADS>(st, sh + WAVES, Plus{});
+  block_combine_begin<THREADS>(mx, sh + 2 * WAVES, Max{});
   __syncthreads();
-  for (int s = kLossThreads / 2; s > 0; s >>= 1) {
-    if (threadIdx.x < s) sh[threadIdx.x] = fmax(sh[threadIdx.x], sh[threadIdx.x + s]);
-    __syncthreads();
-  }
-  const double tmax = sh[0];
-  __syncthreads();
+  const double S = block_combine_end<THREADS>(sh, Plus{}), St = block_combine_end<THREADS>(sh + WAVES, Plus{});
+  const double tmax = block_combine_end<THREADS>(sh + 2 * WAVES, Max{});
   const double rS = S > 0.0 ? 1.0 / S : 0.0;
   const double rSt = St > 0.0 ? 1.0 / St : 0.0;
   double sd2 = 0.0;
-  for (int p = threadIdx.x; p < P; p += kLossThreads) {
-    const double d = Iw[p] * rS - tw[p] * rSt;
+  px.each([&](int, float i, float t) {
+    const double d = i * rS - t * rSt;
     sd2 += d * d;
-  }
-  const double mse = block_sum(sd2, sh) / P;
+  });
+  block_combine_begin<THREADS>(sd2, sh + 3 * WAVES, Plus{});
+  __syncthreads();
   if (threadIdx.x == 0) {
+    const double mse = block_combine_end<THREADS>(sh + 3 * WAVES, Plus{}) / P;
     const double peak = tmax * rSt;
-    out[w] = (mse > 0.0) ? 10.0 * log10(peak * peak / mse) : INFINITY;
+    *out = (mse > 0.0) ? 10.0 * log10(peak * peak / mse) : INFINITY;
   }
+}
+
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
+psnr_kernel(const float* __restrict__ I, const float* __restrict__ tau, double* __restrict__ out, int T) {
+  __shared__ double sh[4 * (THREADS / 64)];
+  const int P = T * T;
+  const size_t o = static_cast<size_t>(blockIdx.x) * P;
+  if (P <= THREADS * kLossCache) psnr_image<THREADS, true>(I + o, tau + o, out + blockIdx.x, P, sh);
+  else psnr_image<THREADS, false>(I + o, tau + o, out + blockIdx.x, P, sh);
 }
 
 __global__ void fill_zero_kernel(float* p, int64_t n) {
@@ -562,9 +666,14 @@ hipError_t launch_bin_intensity(const float2* ofov, float* out, int w_count, int
   return hipGetLastError();
 }
 
+constexpr int kLargeImage = 8192;  // pixels beyond which an image takes a block of 1024 threads
+
 hipError_t launch_loss(const float* I, const float* tau, float* dl_di, double* per_wl, int W, int T,
-                       hipStream_t s) {
-  loss_kernel<<<W, kLossThreads, 0, s>>>(I, tau, dl_di, per_wl, W, T);
+                       unsigned* arrived, double* loss, hipStream_t s) {
+  if (T * T > kLargeImage)
+    loss_kernel<kLossThreadsLarge><<<W, kLossThreadsLarge, 0, s>>>(I, tau, dl_di, per_wl, W, T, arrived, loss);
+  else
+    loss_kernel<kLossThreads><<<W, kLossThreads, 0, s>>>(I, tau, dl_di, per_wl, W, T, arrived, loss);
   return hipGetLastError();
 }
 
@@ -627,7 +736,8 @@ hipError_t launch_adam_sigmoid(float* theta, float* h, const float* dl_dh, float
 
 hipError_t launch_psnr(const float* I, const float* tau, double* out, int W, int T, hipStream_t s) {
   if (W <= 0) return hipSuccess;
-  psnr_kernel<<<W, kLossThreads, 0, s>>>(I, tau, out, T);
+  if (T * T > kLargeImage) psnr_kernel<kLossThreadsLarge><<<W, kLossThreadsLarge, 0, s>>>(I, tau, out, T);
+  else psnr_kernel<kLossThreads><<<W, kLossThreads, 0, s>>>(I, tau, out, T);
   return hipGetLastError();
 }
 

@@ -243,6 +243,30 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
           if (x >= x0 && x < x0 + F) dst[x - x0] = reg[t];
         }
       }
+      // The intensities too, where the block holds whole bins (G a multiple of the bin side): a
+      // launch less (2.5 us of the 26 of the smallest forward).  Rows meet in the exchange regions.
+      if (a.intensity) {
+        const int b = a.bin, T = F / b;
+        float* img = a.intensity + static_cast<size_t>(w) * T * T;
+        if (b == 1) {
+          if (active) {
+#pragma unroll
+            for (int t = 0; t < EN; ++t) {
+              const int x = j0 + P * t;
+              if (x >= x0 && x < x0 + F) img[(y - x0) * T + x - x0] = bin_sum(&reg[t], 1, 1);
+            }
+          }
+        } else {
+#pragma unroll
+          for (int t = 0; t < EN; ++t) lds[j0 + P * t] = reg[t];
+          __syncthreads();
+          for (int i = threadIdx.x; i < G / b * T; i += kRowThreads) {
+            const int ty = bx * (G / b) + i / T, tx = i % T;
+            if (ty < T) img[ty * T + tx] = bin_sum(lds_all + (i / T * b) * RG + x0 + tx * b, RG, b);
+          }
+          __syncthreads();
+        }
+      }
       c = next;
       if (w + 1 < we) spectrum(w + 1, c).load(reg);
     }
@@ -363,6 +387,7 @@ __global__ void __launch_bounds__((row_block_threads<M, MODE>())) row_group_kern
   a.h = g.call.h ? g.call.h + t.h_off : nullptr;
   a.u_in = g.call.u_in ? g.call.u_in + t.u_off : nullptr;
   a.dl_di = g.call.dl_di ? g.call.dl_di + t.img_off : nullptr;
+  if constexpr (MODE == ROW_FWD_LAST) a.intensity = t.bins ? g.call.intensity + t.img_off : nullptr;
   row_body<M, PAD, MODE>(a, local % t.gx, local / t.gx, lds_all, tw);
 }
 
