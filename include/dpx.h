@@ -170,14 +170,20 @@ typedef struct dpx_opts {
                                every design in one wavelength chunk on one stream and a
                                transform column variant (0-3), else DPX_E_UNSUPPORTED.
                                Results are bitwise identical across schedules. */
-  int32_t small_path;       /* 0 = the multi-pass kernels; 1 = for transform lengths up to 128
-                               (pad 2; up to 96 with pad 1) in store mode, per-design schedule,
-                               one stream, no forced column variant and no transfer tables,
-                               each wavelength's plane stays in LDS and the forward (with the
-                               binning) and the adjoint (with the dL/dh partials, one slot per
-                               wavelength) are one launch each.  Same bits either way.  Not the
-                               default: measured on MI355X it ties the multi-pass kernels on
-                               a few wavelengths and is slower on many (one block per CU). */
+  int32_t small_path;       /* 1 = for transform lengths up to 128 (pad 2; up to 96 with pad 1) in
+                               store mode, per-design schedule, one stream, no forced column
+                               variant and no transfer tables, each wavelength's plane stays in
+                               LDS and the forward (with the binning) and the adjoint (with the
+                               dL/dh partials, one slot per wavelength) are one launch each.  Same
+                               bits either way (dL/dh to rounding: its slots differ).
+                               0 = automatic: that path for a plan of one design without other
+                               requests (schedule, wl_chunk, autotune, variants, radix plans,
+                               tables, band limit, input gap) where it is the faster one on
+                               MI355X (64 points without padding always and with it up to 2048
+                               wavelengths, 96 points from 96 to 1024, 128 points from 64 on),
+                               if max_workspace_bytes leaves room for its slots.  A misalignment
+                               sends an automatic plan's calls through the multi-pass kernels
+                               while it is set. */
   int32_t check_finite;     /* nonzero (a debugging aid): dpx_forward, dpx_loss and
                                dpx_backward count the NaN and infinite values in what they
                                wrote (intensities; loss and dL/dI; dL/dh), wait for the stream
@@ -206,7 +212,8 @@ typedef struct dpx_layout {
   int64_t workspace_bytes;         /* device bytes the plan holds for this design */
   int32_t transfer_tables;         /* transfer tables held for this design (one per distinct
                                       gap; 0 = H is evaluated in the column passes) */
-  int32_t lds_path;                /* 1: this design runs LDS-resident (dpx_opts.small_path) */
+  int32_t lds_path;                /* 1: the design's next calls run LDS-resident
+                                      (dpx_opts.small_path) */
 } dpx_layout;
 
 typedef struct dpx_plan dpx_plan;

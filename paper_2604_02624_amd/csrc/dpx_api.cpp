@@ -71,6 +71,8 @@ struct Design {
   int row_plan = 0;  // radix plans of the row and column transforms
   int col_plan = 0;
   bool lds = false;  // forward and adjoint as one LDS-resident launch each
+  bool lds_auto = false;    // the same unless a misalignment is set, with the passes' layout beside it
+  bool misaligned = false;  // dz, sx or sy is not zero
   // 1: the input field meets layer 0 directly, so its field after the first transmission,
   // u_in t_0(h), is rebuilt by the last adjoint pass and gets no checkpoint slab
   int ck_first = 0;
@@ -249,8 +251,17 @@ dpx_status validate(const dpx_design* ds, int32_t nd, const dpx_opts* o) {
   return DPX_OK;
 }
 
+// slabs of checkpoints and slots of gradient partials a design holds: the LDS-resident kernels store
+// every layer's field and take one slot per wavelength
+int ckpt_slabs(const Design& d) { return d.lds_auto ? d.K : d.K - d.ck_first; }
+int gradient_slots(const Design& d) { return d.lds_auto ? std::max(d.nslots, d.W) : d.nslots; }
+// whether the next calls run the design LDS-resident
+bool lds_now(const Design& d) { return d.lds || (d.lds_auto && !d.misaligned); }
+
 // Geometry and byte counts for one design (host only).
-void layout_design(const dpx_design& src, const dpx_opts& o, Design& d) {
+// single: the plan's only design; lds_wanted: false lays the design out without the automatic
+// LDS-resident path
+void layout_design(const dpx_design& src, const dpx_opts& o, bool single, Design& d, bool lds_wanted = true) {
   d.N = src.n;
   d.pad = src.pad;
   d.M = src.pad * src.n;
@@ -291,6 +302,13 @@ void layout_design(const dpx_design& src, const dpx_opts& o, Design& d) {
     chunk = d.W;
     wpb = 1;
   }
+  // and where it is the faster one and nothing asks for a form that only the passes have.  The plan
+  // then has room for both: a misalignment, which the LDS-resident kernels cannot apply, sends the
+  // calls through the passes while it is set.
+  d.lds_auto = lds_wanted && single && !d.lds && o.small_path == 0 && o.checkpoint_mode == 0 && o.streams <= 1 &&
+               o.wl_chunk == 0 && o.schedule == 0 && !o.autotune && o.force_variant < 0 && o.force_plan < 0 &&
+               o.transfer_table == 0 && src.z_in == 0.0 && src.band_limited == 0 &&
+               dpx::lds_path_supported(d.M, d.pad) && dpx::lds_path_preferred(d.M, d.pad, d.W);
   d.wl_chunk = chunk;
   d.nchunks = (d.W + chunk - 1) / chunk;
   d.lanes = std::max(1, std::min(lanes_wanted, d.nchunks));
@@ -324,9 +342,9 @@ void layout_design(const dpx_design& src, const dpx_opts& o, Design& d) {
   const int of_w = ck_w;
   d.ck_first = (src.z_in == 0.0 && !d.lds) ? 1 : 0;
   d.bytes = static_cast<int64_t>(d.lanes) * d.wl_chunk * d.N * d.M * 8  // spec
-            + static_cast<int64_t>(d.K - d.ck_first) * ck_w * nn * 8  // checkpoints
+            + static_cast<int64_t>(ckpt_slabs(d)) * ck_w * nn * 8  // checkpoints
             + static_cast<int64_t>(of_w) * d.F * d.F * 8      // output field
-            + static_cast<int64_t>(d.nslots) * d.K * nn * 4   // dL/dh partials
+            + static_cast<int64_t>(gradient_slots(d)) * d.K * nn * 4   // dL/dh partials
             + static_cast<int64_t>(d.W) * 8                   // per-wavelength loss
             + static_cast<int64_t>(d.W) * sizeof(WlConst)
             + static_cast<int64_t>(d.K) * 8;                  // gap table
@@ -337,6 +355,10 @@ void layout_design(const dpx_design& src, const dpx_opts& o, Design& d) {
     d.table_bytes = 0;
     d.nzslots = 0;
     d.zslot.clear();
+  }
+  if (d.lds_auto && o.max_workspace_bytes > 0 && d.bytes + static_cast<int64_t>(d.M) * 8 > o.max_workspace_bytes) {
+    d = Design();
+    layout_design(src, o, single, d, false);
   }
 }
 
@@ -1000,7 +1022,7 @@ dpx_status run_groups(dpx_plan* p, const std::vector<GroupLaunch>& launches, con
 // LDS-resident forward (with the intensity binning) or adjoint (with the dL/dh partials) of a
 // whole design in one launch
 dpx_status run_lds(dpx_plan* p, const Design& d, bool adjoint, const float* h, const float* u_in,
-                   float* intensity, const float* dl_di, hipStream_t s) {
+                   float* intensity, const float* dl_di, float* dl_dh, hipStream_t s) {
   dpx::LdsArgs a{};
   a.wl = d.d_wl;
   a.tw = p->twiddles.at(tw_key(d.M, 0));
@@ -1012,7 +1034,7 @@ dpx_status run_lds(dpx_plan* p, const Design& d, bool adjoint, const float* h, c
   a.ofov = d.ofov;
   a.intensity = intensity ? intensity + d.img_off : nullptr;
   a.dl_di = dl_di ? dl_di + d.img_off : nullptr;
-  a.dh_part = d.dh_part;
+  a.dh_part = d.W == 1 && dl_dh ? dl_dh + d.h_off : d.dh_part;
   a.K = d.K;
   a.fov = d.F;
   a.bin = d.b;
@@ -1342,7 +1364,7 @@ dpx_status dpx_plan_query(const dpx_design* ds, int32_t nd, const dpx_opts* opts
   bool groupable_all = o.checkpoint_mode == 0;
   for (int i = 0; i < nd; ++i) {
     Design d;
-    layout_design(ds[i], o, d);
+    layout_design(ds[i], o, nd == 1, d);
     tot += d.bytes;
     ms[d.M] = 1;
     groupable_all = groupable_all && d.nchunks == 1 && d.lanes == 1 && d.col_variant <= 3 && d.z_in == 0.0 &&
@@ -1418,7 +1440,7 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
   for (int i = 0; i < nd && st == DPX_OK; ++i) {
     const dpx_design& src = ds[i];
     Design& d = p->designs[i];
-    layout_design(src, o, d);
+    layout_design(src, o, nd == 1, d);
     d.wl.assign(src.wl, src.wl + src.n_wl);
     d.n_mat.assign(src.n_mat, src.n_mat + src.n_wl);
     d.kappa.assign(src.n_wl, 0.0);
@@ -1437,9 +1459,9 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
     const int ck_w = (o.checkpoint_mode == 1) ? d.lanes * d.wl_chunk : d.W;
     if ((st = dev_alloc(&d.d_wl, d.W * sizeof(WlConst), "wavelength table")) != DPX_OK) break;
     if ((st = dev_alloc(&d.spec, static_cast<int64_t>(d.lanes) * d.wl_chunk * d.N * d.M * 8, "spectra")) != DPX_OK) break;
-    if ((st = dev_alloc(&d.ckpt, static_cast<int64_t>(d.K - d.ck_first) * ck_w * nn * 8, "checkpoints")) != DPX_OK) break;
+    if ((st = dev_alloc(&d.ckpt, static_cast<int64_t>(ckpt_slabs(d)) * ck_w * nn * 8, "checkpoints")) != DPX_OK) break;
     if ((st = dev_alloc(&d.ofov, static_cast<int64_t>(ck_w) * d.F * d.F * 8, "output field")) != DPX_OK) break;
-    if ((st = dev_alloc(&d.dh_part, static_cast<int64_t>(d.nslots) * d.K * nn * 4, "gradient partials")) != DPX_OK) break;
+    if ((st = dev_alloc(&d.dh_part, static_cast<int64_t>(gradient_slots(d)) * d.K * nn * 4, "gradient partials")) != DPX_OK) break;
     if ((st = dev_alloc(&d.per_wl, d.W * 8, "per-wavelength loss")) != DPX_OK) break;
     if ((st = dev_alloc(&d.htab, d.table_bytes, "transfer tables")) != DPX_OK) break;
     if ((st = dev_alloc(&d.d_zrev, static_cast<int64_t>(d.K) * 8, "gap table")) != DPX_OK) break;
@@ -1629,7 +1651,7 @@ dpx_status dpx_plan_layout(const dpx_plan* p, int32_t i, dpx_layout* out) {
   out->target_side = d.T;
   out->workspace_bytes = d.bytes;
   out->transfer_tables = d.nzslots;
-  out->lds_path = d.lds ? 1 : 0;
+  out->lds_path = lds_now(d) ? 1 : 0;
   return ok();
 }
 
@@ -1694,6 +1716,7 @@ dpx_status dpx_plan_set_misalignment(dpx_plan* p, int32_t i, const double* dz, c
   d.dz = nz;
   d.sx = nx;
   d.sy = ny;
+  d.misaligned = any;
   // store-mode checkpoints of an earlier forward belong to the old transfer functions
   p->fwd_valid = false;
   return ok();
@@ -1725,7 +1748,7 @@ dpx_status dpx_forward(dpx_plan* p, const float* h, const float* u_in, float* in
     if (p->grouped)
       return run_group_parts(p, p->g_fwd, {h, reinterpret_cast<const float2*>(u_in), nullptr}, intensity, s0);
     return for_each_design(p, s0, [&](const Design& d, int, hipStream_t s) -> dpx_status {
-      if (d.lds) return run_lds(p, d, false, h, u_in, intensity, nullptr, s);
+      if (lds_now(d)) return run_lds(p, d, false, h, u_in, intensity, nullptr, nullptr, s);
       DPX_TRY(fork_lanes(p, d, s));
       for (int c = 0; c < d.nchunks; ++c) {
         const int lane = c % d.lanes;
@@ -1811,9 +1834,10 @@ dpx_status dpx_backward(dpx_plan* p, const float* h, const float* u_in, const fl
     if (p->grouped)
       return run_group_parts(p, p->g_bwd, {h, reinterpret_cast<const float2*>(u_in), dl_di}, dl_dh, s0);
     return for_each_design(p, s0, [&](const Design& d, int, hipStream_t s) -> dpx_status {
-      if (d.lds) {
-        DPX_TRY(run_lds(p, d, true, h, u_in, nullptr, dl_di, s));
-        hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.nslots,
+      if (lds_now(d)) {
+        DPX_TRY(run_lds(p, d, true, h, u_in, nullptr, dl_di, dl_dh, s));
+        if (d.W == 1) return DPX_OK;  // one slot: the launch wrote dl_dh
+        hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.W,
                                              static_cast<int64_t>(d.K) * d.N * d.N, s);
         if (e != hipSuccess) return fail(DPX_E_DEVICE, "gradient reduction launch failed: %s", hipGetErrorString(e));
         return DPX_OK;

@@ -145,6 +145,8 @@ __device__ __forceinline__ void bin_intensity_body(const float2* __restrict__ of
 constexpr int kLdsThreads = 512;
 // whether the LDS-resident kernels are built for this transform length and pad
 bool lds_path_supported(int M, int pad);
+// whether they are the faster choice for so many wavelengths
+bool lds_path_preferred(int M, int pad, int wavelengths);
 hipError_t launch_lds(int M, int pad, bool adjoint, const LdsArgs& a, hipStream_t s);
 
 // ------------------------------------------------------------------------------------------

@@ -633,6 +633,21 @@ bool lds_path_supported(int M, int pad) {
   }
 }
 
+// A wavelength on one CU costs no launches and no plane traffic between the passes, but takes the CU's
+// own time for all of it, so the passes win where a few wavelengths leave the other CUs idle (128
+// and 96 points) and, for the short transforms whose planes stay in the last-level cache, where
+// there are thousands.  Measured, one forward, loss and gradient of two to six layers, passes
+// against LDS-resident, us: 64 points 53 / 33 (1 wavelength), 89 / 54 (512), 180 / 169 (2048),
+// 287 / 322 (4096); 96 points 85 / 93 (32), 93 / 94 (64), 112 / 97 (128), 300 / 282 (1024), 513 / 537
+// (2048); 128 points 66 / 71 (32), 74 / 72 (64), 128 / 82 (256), 1005 / 780 (4096); 64 points without
+// padding 62 / 52 (1), 117 / 71 (256), 707 / 629 (4096), 96 without padding 83 / 166 (1), 182 / 200 (256).
+bool lds_path_preferred(int M, int pad, int wavelengths) {
+  if (pad == 1) return M == 64;
+  if (M == 64) return wavelengths <= 2048;
+  if (M == 96) return wavelengths >= 96 && wavelengths <= 1024;
+  return M == 128 && wavelengths >= 64;
+}
+
 hipError_t launch_lds(int M, int pad, bool adjoint, const LdsArgs& a, hipStream_t s) {
   switch (M) {
 #define DPX_CASE(m) case m: return launch_lds_##m(pad, adjoint, a, s);

@@ -95,3 +95,37 @@ def test_many_wavelengths_and_gradient_slots(torch_dev, n, pad, n_wl):
     assert np.linalg.norm(dh.reshape(h.shape) - dh_ref) <= GRAD_TOL * np.linalg.norm(dh_ref)
     plan.close()
     few.close()
+
+
+@pytest.mark.parametrize("n,pad,n_wl", [(32, 2, 1), (32, 2, 2048), (48, 2, 96), (48, 2, 1024), (64, 2, 64), (64, 1, 1),
+                                        (64, 1, 130)])
+def test_automatic_lds_path(torch_dev, n, pad, n_wl):
+    """The sizes at which a plan without requests runs LDS-resident: the passes' bits (dL/dh to the
+    rounding of its slots), a misalignment through the passes and back, and a workspace limit that the
+    passes meet but the slots do not."""
+    from paper_2604_02624_amd import dpx
+    torch = torch_dev
+    d = design(n, pad, n_wl)
+    g = np.random.default_rng(n_wl)
+    h = (g.random((2, n, n)) * 1.1e-6).astype(np.float32)
+    auto, passes = dpx.Plan([d]), dpx.Plan([d], schedule=1)
+    assert auto.uses_lds_path() and not passes.uses_lds_path()
+    ht = auto.pack_heights([h])
+    gt = torch.as_tensor(g.standard_normal(auto.img_count).astype(np.float32)).cuda()
+    for shift in (None, np.array([40e-9, -25e-9])):
+        for p in (auto, passes):
+            p.set_misalignment(0, None, shift, shift)
+        assert bool(auto.layout(0)["lds_path"]) == (shift is None)
+        a, b = outputs(torch, auto, ht, gt), outputs(torch, passes, ht, gt)
+        assert np.array_equal(a[0], b[0])
+        # sums of n_wl terms in single precision over at most 16 of them, then in double
+        assert np.linalg.norm(a[1] - b[1]) <= 2e-6 * np.linalg.norm(b[1])
+    auto.set_misalignment(0)
+    assert auto.layout(0)["lds_path"] == 1
+    need = dpx.plan_query([d], schedule=1)
+    tight = dpx.Plan([d], max_workspace_bytes=need)
+    assert not tight.uses_lds_path()
+    passes.set_misalignment(0)
+    assert all(np.array_equal(a, b) for a, b in zip(outputs(torch, tight, ht, gt), outputs(torch, passes, ht, gt)))
+    for p in (auto, passes, tight):
+        p.close()
