@@ -86,6 +86,34 @@ struct ColSplit {
   static constexpr int threads(int TX) { return NH * TX * (L > GP ? L : GP); }
 };
 
+// LEN = 512 (1024 zero-padded points, or 512 periodic ones) would need 32 registers of data in one
+// of two phases, or leave half of the lanes idle there.  Its B is a transform of 64 points on eight lanes,
+// 8 x 8 with an exchange of its own inside the wavefront: LEN = 8 . (8 . 8).  With j = j1 + 8 i and
+// k2 = m + 8 q,
+//   B1: c[k1][j1][m] = sum_i a[j1 + 8 i][k1] (w_M^(8 K1))^i w_8^(i m)
+//   B2: X[k1][m + 8 q] = sum_j1 c[k1][j1][m] (w_M^(K1 + 8 NH m))^j1 w_8^(j1 q)
+// and back, X -> (over q) -> (over m, twiddled by w_64^(-j1)) -> b[k1][j1 + 8 i].  A lane of B is k1 + 8 j1
+// or k1 + 8 m, so the frequency of (lane, q) is NH (lane + 64 q) + h.  Eight registers of data per
+// lane: the halves follow each other on the same threads, with the rows and the even half's result
+// kept in registers, and every exchange goes back to slots that only its own lane or wavefront uses.
+template <int M, int PAD>
+struct ColSplit3 {
+  static constexpr int LEN = M / PAD, NH = PAD;
+  static constexpr bool BUILT = LEN == 512;
+  static constexpr int L = 64;  // row threads of a column, lanes of B
+  // table: B1 [4][NH][8], B2 [4][NH][64], back [4][8], C [4][64], with two halves w_M^n [LEN]
+  static constexpr int OFF_B2 = 4 * NH * 8;
+  static constexpr int OFF_R = OFF_B2 + 4 * NH * 64;
+  static constexpr int OFF_C = OFF_R + 4 * 8;
+  static constexpr int OFF_W = OFF_C + 4 * 64;
+  static constexpr int COUNT = OFF_W + (NH == 2 ? LEN : 0);
+  // Slots: k1 is 74 apart (2 mod 8: eight k1 and two neighbouring j cover the 16 bank pairs), j padded
+  // by one after every eight (neighbouring m of B2 fall on odd distances), columns 594 apart
+  // (2 mod 16, for eight columns and two j).
+  static constexpr int REG = 594;
+  static __host__ __device__ constexpr int slot(int k1, int j) { return k1 * 74 + j + (j >> 3); }
+};
+
 // exp(-2 pi i num / den) with the numerator reduced first
 inline float2 unit_root(long long num, long long den) {
   const double ang = 6.283185307179586476925286766559 * static_cast<double>(num % den) / static_cast<double>(den);
@@ -131,6 +159,23 @@ inline void col_table_host(std::vector<float2>& out) {
       for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
     }
   }
+}
+
+template <int M, int PAD>
+inline void col3_table_host(std::vector<float2>& out) {
+  using G = ColSplit3<M, PAD>;
+  out.assign(G::COUNT, make_float2(1.f, 0.f));
+  for (int e = 0; e < 4; ++e) {
+    for (int h = 0; h < G::NH; ++h) {
+      for (int k1 = 0; k1 < 8; ++k1) out[(e * G::NH + h) * 8 + k1] = input_twiddle(8, e, 8 * (G::NH * k1 + h), M);
+      for (int l = 0; l < 64; ++l)  // l = k1 + 8 m
+        out[G::OFF_B2 + (e * G::NH + h) * 64 + l] = input_twiddle(8, e, G::NH * l + h, M);
+    }
+    for (int j = 0; j < 8; ++j) out[G::OFF_R + e * 8 + j] = input_twiddle(8, e, j, 64);
+    for (int j = 0; j < 64; ++j) out[G::OFF_C + e * 64 + j] = input_twiddle(8, e, j, G::LEN);
+  }
+  if constexpr (G::NH == 2)
+    for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -294,6 +339,15 @@ __device__ __forceinline__ void col_freq_forward(float2* v, const float2* __rest
 template <int M, int PAD>
 __device__ __forceinline__ void col_freq_inverse(float2* v) {
   DFT<ColSplit<M, PAD>::R2, true, false>::run(v);
+}
+
+// The four pairs of an eight-point transform with twiddled inputs, `step` table entries apart
+template <bool INV>
+__device__ __forceinline__ void dft8_table(float2* v, const float2* __restrict__ tab, int step) {
+  float2 p[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) p[e] = tab[e * step];
+  dft_fused<8, INV>(v, p);
 }
 
 }  // namespace dpx

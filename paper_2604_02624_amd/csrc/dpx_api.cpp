@@ -274,7 +274,7 @@ void layout_design(const dpx_design& src, const dpx_opts& o, bool single, Design
   d.n_m = src.n_medium;
   d.z_in = src.z_in;
   d.band = src.band_limited != 0;
-  d.row_group = dpx::row_rows_per_block(d.M, dpx::ROW_FWD_MID);
+  d.row_group = dpx::row_rows_per_block(d.M, d.pad, dpx::ROW_FWD_MID);
   const int row_blocks = (d.N + d.row_group - 1) / d.row_group;
   // wavelengths per chunk: everything at once unless asked otherwise (recompute mode
   // defaults to chunks of 64).  Concurrent lanes run chunks of wavelengths on several
@@ -552,7 +552,7 @@ int64_t row_bytes(const Design& d, int mode, int wc, int nwb, bool accumulate, b
 dpx_status run_row(dpx_plan* p, const Design& d, int mode, RowArgs a, int row_lo, int row_hi, hipStream_t s) {
   a.row_lo = row_lo;
   a.row_hi = row_hi;
-  const int rg = dpx::row_rows_per_block(d.M, mode);
+  const int rg = dpx::row_rows_per_block(d.M, d.pad, mode);
   const int nrb = (row_hi - row_lo + rg - 1) / rg;
   const int nwb = (a.w_count + d.w_per_block - 1) / d.w_per_block;
   TimedLaunch t{dpx::row_pass_kind(mode), nullptr, nullptr,
@@ -567,12 +567,15 @@ dpx_status run_row(dpx_plan* p, const Design& d, int mode, RowArgs a, int row_lo
 
 // Wavelengths per column block, while that leaves several blocks per CU: two in the staged form (the
 // second one's rows are prefetched while the first is transformed; best of 1, 2, 4, 8 on 4096
-// wavelengths of 512 x 512), four with the split transforms, whose blocks also stage a table (512
-// points, 1024 wavelengths: 647, 620 and 616 us per pass with 2, 4 and 8; 384 points, 512
-// wavelengths: 211, 204, 210)
-int col_wavelengths_per_block(const Design& d, int wc) {
+// wavelengths of 512 x 512).  Of the split forms, halves of up to 256 points take four, whose blocks
+// also stage a table (512 points, 1024 wavelengths: 647, 620 and 616 us per pass with 2, 4 and 8; 384
+// points, 512 wavelengths: 211, 204, 210), unpadded columns one (128 points, 2048 wavelengths: 108
+// us against 113 and 118 with 2 and 4; 256 points 49, 52, 52) and halves of 512 points one (their
+// kernel runs no more).
+int col_wavelengths_per_block(const Design& d, int wc, int plan) {
   const int64_t tiles = static_cast<int64_t>(wc) * (d.M / 8);
-  if (dpx::col_split(d.M, d.pad) && tiles >= 4 * 8192) return 4;
+  if (plan == 0 && d.col_variant != 4 && dpx::col_split(d.M, d.pad))
+    return d.pad == 2 && d.M / d.pad < 512 && tiles >= 4 * 8192 ? 4 : 1;
   return tiles >= 2 * 8192 ? 2 : 1;
 }
 
@@ -599,10 +602,10 @@ ColArgs col_args(const dpx_plan* p, const Design& d, int lane, int layer, int w0
     auto it = p->dft.find(d.M * 4 + d.pad);
     c.dft = it == p->dft.end() ? nullptr : it->second;
   }
-  c.col_wpb = col_wavelengths_per_block(d, wc);
   const int64_t hs = d.M / 2 + 1;
   c.htab = (d.htab && layer >= 0) ? d.htab + static_cast<int64_t>(d.zslot[layer]) * d.W * hs * hs : nullptr;
   const int plan = col_plan_of(d, c);
+  c.col_wpb = col_wavelengths_per_block(d, wc, plan);
   c.tw = p->twiddles.at(plan == 0 && dpx::col_split(d.M, d.pad) ? col_key(d.M, d.pad) : tw_key(d.M, plan));
   return c;
 }
@@ -642,7 +645,7 @@ int64_t h_off_layer(const Design& d, int l) { return d.h_off + static_cast<int64
 
 // Whether the last row pass also forms the intensities: its blocks hold whole detector bins.  Else
 // (1600 points: three rows per block) the binning is a launch of its own.
-bool bins_in_rows(const Design& d) { return dpx::row_rows_per_block(d.M, dpx::ROW_FWD_LAST) % d.b == 0; }
+bool bins_in_rows(const Design& d) { return dpx::row_rows_per_block(d.M, d.pad, dpx::ROW_FWD_LAST) % d.b == 0; }
 
 // forward over one chunk of wavelengths [w0, w0 + wc) on lane `lane`; leaves the output
 // field in ofov, and the intensities where bins_in_rows (unless `intensity` is null).  `after_first` (may be null) is recorded on s after the first launch.
@@ -787,7 +790,7 @@ void add_row_position(dpx_plan* p, const std::vector<RowItem>& items, std::vecto
       t.h_off = h_off_layer(d, it.layer);
       t.u_off = d.u_off;
       t.img_off = d.img_off;
-      const int rg = dpx::row_rows_per_block(d.M, it.mode);
+      const int rg = dpx::row_rows_per_block(d.M, d.pad, it.mode);
       t.gx = (it.row_hi - it.row_lo + rg - 1) / rg;
       const int nwb = (d.W + d.w_per_block - 1) / d.w_per_block;
       t.nblocks = t.gx * nwb;

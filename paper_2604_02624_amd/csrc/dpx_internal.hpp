@@ -43,11 +43,14 @@ constexpr int row_pass_kind(int mode) { return 2 + (mode == ROW_ADJ_LAST_U ? ROW
 // such blocks per CU next to their LDS, 256 for the register-heavy adjoint passes with a gradient
 // (136-168 registers at 512 and 1024 points allow three wavefronts per SIMD, of which blocks of
 // 512 threads could use two).
-constexpr int row_threads_of_mode(int mode) { return mode >= ROW_ADJ_MID ? 256 : 512; }
+// So do all passes of unpadded rows with 16 values per lane (131-160 registers at 512 points).
+constexpr int row_threads_of_mode(int values, int pad, int mode) {
+  return mode >= ROW_ADJ_MID || (pad == 1 && values >= 16) ? 256 : 512;
+}
 // Threads of a row-pass block for P lanes per transform: the mode's count when transforms tile
 // a wavefront; three or so whole transforms (about 256 threads) when one spans wavefronts.
-constexpr int row_threads_for(int P, int mode) {
-  return (P <= 64 && 64 % P == 0) ? row_threads_of_mode(mode) : (256 / P) * P;
+constexpr int row_threads_for(int M, int P, int pad, int mode) {
+  return (P <= 64 && 64 % P == 0) ? row_threads_of_mode(M / P, pad, mode) : (256 / P) * P;
 }
 
 struct RowArgs {
@@ -313,6 +316,6 @@ void build_twiddle_table(int M, int plan, std::vector<float2>& out);
 int radix_plan_count(int M);
 const char* radix_plan_name(int M, int plan);
 int row_lanes_per_transform(int M);  // P = M / E
-int row_rows_per_block(int M, int mode);  // rows (transforms) per row-pass block
+int row_rows_per_block(int M, int pad, int mode);  // rows (transforms) per row-pass block
 
 }  // namespace dpx

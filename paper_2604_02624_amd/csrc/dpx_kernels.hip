@@ -499,10 +499,10 @@ int row_lanes_per_transform(int M) {
   }
 }
 
-int row_rows_per_block(int M, int mode) {
+int row_rows_per_block(int M, int pad, int mode) {
   const int P = row_lanes_per_transform(M);
   if (P == 0) return 0;
-  return row_threads_for(P, mode) / P;
+  return row_threads_for(M, P, pad, mode) / P;
 }
 
 namespace {

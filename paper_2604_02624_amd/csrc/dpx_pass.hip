@@ -38,15 +38,15 @@ hipError_t row_mode(int mode, const RowArgs& a, dim3 grid, hipStream_t s) {
   if constexpr (M == 1600 && PAD == 2 && V == 0) {
     if (mode == ROW_FWD_MID || mode == ROW_ADJ_MID) {
       if (mode == ROW_FWD_MID)
-        row_kernel_w3<M, PAD, ROW_FWD_MID><<<grid, row_block_threads<M, ROW_FWD_MID>(), 0, s>>>(a);
+        row_kernel_w3<M, PAD, ROW_FWD_MID><<<grid, row_block_threads<M, PAD, ROW_FWD_MID>(), 0, s>>>(a);
       else
-        row_kernel_w3<M, PAD, ROW_ADJ_MID><<<grid, row_block_threads<M, ROW_ADJ_MID>(), 0, s>>>(a);
+        row_kernel_w3<M, PAD, ROW_ADJ_MID><<<grid, row_block_threads<M, PAD, ROW_ADJ_MID>(), 0, s>>>(a);
       return hipGetLastError();
     }
   }
   switch (mode) {
 #define DPX_ROW(MD) \
-  case MD: row_kernel<M, PAD, MD, V><<<grid, row_block_threads<M, MD>(), 0, s>>>(a); break;
+  case MD: row_kernel<M, PAD, MD, V><<<grid, row_block_threads<M, PAD, MD>(), 0, s>>>(a); break;
     DPX_ROW(ROW_FWD_FIRST)
     DPX_ROW(ROW_FWD_MID)
     DPX_ROW(ROW_FWD_LAST)
@@ -64,7 +64,7 @@ template <int PAD>
 hipError_t row_group_mode(int mode, const GroupArgs& g, hipStream_t s) {
   switch (mode) {
 #define DPX_ROW(MD) \
-  case MD: row_group_kernel<M, PAD, MD><<<group_grid(g), row_block_threads<M, MD>(), 0, s>>>(g); break;
+  case MD: row_group_kernel<M, PAD, MD><<<group_grid(g), row_block_threads<M, PAD, MD>(), 0, s>>>(g); break;
     DPX_ROW(ROW_FWD_FIRST)
     DPX_ROW(ROW_FWD_MID)
     DPX_ROW(ROW_FWD_LAST)
@@ -103,14 +103,16 @@ hipError_t col_launch(bool conj, const ColArgs& a, int w_count, hipStream_t s) {
 }
 
 // tile widths of the transform variants: 8 / 16 columns (16 / 16 where 8 columns would not fill
-// whole wavefronts), or 4 / 8 when a transform spans wavefronts (blocks stay within 1024 threads)
+// whole wavefronts, 8 / 8 for halves of 512 points), or 4 / 8 when a transform spans wavefronts (blocks stay within 1024 threads)
 template <int PAD, int V>
 constexpr int tile_narrow() {
+  if (ColShape<M, PAD, 8, V>::SPLIT3) return 8;
   if (ColShape<M, PAD, 16, V>::SPLIT) return ColSplit<M, PAD>::NARROW ? 8 : 16;
   return !Geo<M>::WAVE_LOCAL ? 4 : 8 * Geo<M>::P >= 64 ? 8 : 16;
 }
 template <int PAD, int V>
 constexpr int tile_wide() {
+  if (ColShape<M, PAD, 8, V>::SPLIT3) return 8;
   return ColShape<M, PAD, 16, V>::SPLIT || Geo<M>::WAVE_LOCAL ? 16 : 8;
 }
 constexpr bool wide_variant(int variant) { return variant == 1 || variant == 3; }
@@ -236,11 +238,18 @@ void DPX_NAME(twiddle_table_)(int plan, std::vector<float2>& out) {
 }
 
 void DPX_NAME(col_table_)(int pad, std::vector<float2>& out) {
-  if (pad == 2) col_table_host<M, 2>(out);
-  else col_table_host<M, 1>(out);
+  const auto build = [&](auto padc) {
+    constexpr int PD = decltype(padc)::value;
+    if constexpr (ColSplit3<M, PD>::BUILT) col3_table_host<M, PD>(out);
+    else col_table_host<M, PD>(out);
+  };
+  if (pad == 2) build(std::integral_constant<int, 2>{});
+  else build(std::integral_constant<int, 1>{});
 }
 
-bool DPX_NAME(col_split_)(int pad) { return pad == 2 ? ColSplit<M, 2>::BUILT : ColSplit<M, 1>::BUILT; }
+bool DPX_NAME(col_split_)(int pad) {
+  return pad == 2 ? ColSplit<M, 2>::BUILT || ColSplit3<M, 2>::BUILT : ColSplit<M, 1>::BUILT || ColSplit3<M, 1>::BUILT;
+}
 
 int DPX_NAME(col_tile_width_)(int pad, int variant) {
   if (pad == 2) return wide_variant(variant) ? tile_wide<2, 0>() : tile_narrow<2, 0>();

@@ -123,8 +123,8 @@ __device__ __forceinline__ float2 transmission(float h, const WlConst& c) {
   return t;
 }
 
-template <int M, int MODE>
-constexpr int row_block_threads() { return row_threads_for(Geo<M>::P, MODE); }
+template <int M, int PAD, int MODE>
+constexpr int row_block_threads() { return row_threads_for(M, Geo<M>::P, PAD, MODE); }
 
 // ------------------------------------------------------------------------------------------
 // Row pass.  A block owns G = 256 / P consecutive rows (one transform group per row) and
@@ -134,7 +134,7 @@ constexpr int row_block_threads() { return row_threads_for(Geo<M>::P, MODE); }
 // lds_all: G exchange regions; tw: room for the twiddle table (both in LDS).
 template <int M, int PAD, int MODE, int V = 0>
 __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float2* lds_all, float2* tw) {
-  constexpr int kRowThreads = row_block_threads<M, MODE>();
+  constexpr int kRowThreads = row_block_threads<M, PAD, MODE>();
   constexpr int E = Geo<M>::E;
   constexpr int P = Geo<M>::P;
   constexpr int G = kRowThreads / P;
@@ -355,8 +355,8 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
 }
 
 template <int M, int PAD, int MODE, int V = 0>
-__global__ void __launch_bounds__((row_block_threads<M, MODE>())) row_kernel(RowArgs a) {
-  __shared__ float2 lds_all[row_block_threads<M, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
+__global__ void __launch_bounds__((row_block_threads<M, PAD, MODE>())) row_kernel(RowArgs a) {
+  __shared__ float2 lds_all[row_block_threads<M, PAD, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
   __shared__ float2 tw[twiddle_count<M, V>()];
   row_body<M, PAD, MODE, V>(a, blockIdx.x, blockIdx.y, lds_all, tw);
 }
@@ -365,9 +365,9 @@ __global__ void __launch_bounds__((row_block_threads<M, MODE>())) row_kernel(Row
 // middle pass at transform 1600 fits it without spilling, and three of its 240-thread blocks
 // then share a CU instead of two.
 template <int M, int PAD, int MODE>
-__global__ void __launch_bounds__((row_block_threads<M, MODE>())) __attribute__((amdgpu_waves_per_eu(3)))
+__global__ void __launch_bounds__((row_block_threads<M, PAD, MODE>())) __attribute__((amdgpu_waves_per_eu(3)))
 row_kernel_w3(RowArgs a) {
-  __shared__ float2 lds_all[row_block_threads<M, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
+  __shared__ float2 lds_all[row_block_threads<M, PAD, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
   __shared__ float2 tw[twiddle_count<M>()];
   row_body<M, PAD, MODE>(a, blockIdx.x, blockIdx.y, lds_all, tw);
 }
@@ -376,8 +376,8 @@ row_kernel_w3(RowArgs a) {
 // block finds its design's task, patches the per-call buffers into the design's arguments
 // and runs the same body as the single-design kernel.
 template <int M, int PAD, int MODE>
-__global__ void __launch_bounds__((row_block_threads<M, MODE>())) row_group_kernel(GroupArgs g) {
-  __shared__ float2 lds_all[row_block_threads<M, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
+__global__ void __launch_bounds__((row_block_threads<M, PAD, MODE>())) row_group_kernel(GroupArgs g) {
+  __shared__ float2 lds_all[row_block_threads<M, PAD, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
   __shared__ float2 tw[twiddle_count<M>()];
   const int ti = group_task(g, blockIdx.x);
   const RowTask t = load_uniform(static_cast<const RowTask*>(g.tasks) + ti);
@@ -649,25 +649,24 @@ __device__ __forceinline__ void col_body(const ColArgs& a, int bx, int by, float
   }
 }
 
-// Transfer function of the split column transforms on v[k2], k2 = 0 .. R2 - 1, of one (column, k1)
-// of half h: element k2 is frequency ky = NH (k1 + R1 k2) + h.  HC: the half where it is known at
+// Transfer function of the split column transforms on v[k2], k2 = 0 .. R2 - 1, of lane k1 < R1 of a
+// column and half h: element k2 is frequency ky = NH (k1 + R1 k2) + h.  HC: the half where it is known at
 // compile time (a body of its own per half), else -1.
-template <int M, int PAD, bool CONJ, int HM, int HC>
+template <int M, int PAD, bool CONJ, int HM, int HC, int R1, int R2>
 __device__ __forceinline__ void apply_transfer(float2* v, const ColArgs& a, const WlConst& c, int w, int kx, int half,
                                                int k1) {
   const int h = HC >= 0 ? HC : half;
-  using G = ColSplit<M, PAD>;
-  constexpr int R2 = G::R2;
+  constexpr int NH = PAD;
   const int kxs = kx < M / 2 ? kx : kx - M;
   const double base = c.q0 - static_cast<double>(kxs * kxs);
-  const int row0 = opaque_lane_row(G::NH * k1 + h);  // frequency of k2 = 0 (see opaque_lane_row)
-  auto ky_of = [&](int k2) { return row0 + G::NH * G::R1 * k2; };
+  const int row0 = opaque_lane_row(NH * k1 + h);  // frequency of k2 = 0 (see opaque_lane_row)
+  auto ky_of = [&](int k2) { return row0 + NH * R1 * k2; };
   if constexpr (HM == kHMirror) {
     // H depends on ky^2 only: frequency M - ky of (k1, k2) belongs to k1' = R1 - k1 - h (mod R1) at
     // k2' = R2 - 1 - k2, or at R2 - k2 on the lane k1 = 0 of the even half, which mirrors onto
     // itself.  So a lane evaluates the lower half of its frequencies (that one lane one more) and
     // takes the upper half from its partner.
-    const int partner = h ? G::R1 - 1 - k1 : (k1 ? G::R1 - k1 : 0);
+    const int partner = h ? R1 - 1 - k1 : (k1 ? R1 - k1 : 0);
     const int src = ((static_cast<int>(threadIdx.x) & 63) - k1 + partner) << 2;
     const bool self = h == 0 && k1 == 0;
     float2 cur = transfer<M, CONJ>(a.zrev, base, ky_of(0));
@@ -790,7 +789,7 @@ __device__ __forceinline__ void col_split_body(const ColArgs& a, int bx, int by,
 #pragma unroll
       for (int i = 0; i < R2; ++i) f[i] = freq_slots[i];
       col_freq_forward<M, PAD>(f, tab, h, k1);
-      apply_transfer<M, PAD, CONJ, HM, HC>(f, a, c, w, kx0 + cb, h, k1);
+      apply_transfer<M, PAD, CONJ, HM, HC, R1, R2>(f, a, c, w, kx0 + cb, h, k1);
       col_freq_inverse<M, PAD>(f);
 #pragma unroll
       for (int i = 0; i < R2; ++i) freq_slots[i] = f[i];
@@ -842,24 +841,143 @@ __device__ __forceinline__ void col_split_body(const ColArgs& a, int bx, int by,
   }
 }
 
+// The same for halves of 512 points (ColSplit3): eight columns, one wavefront per column in B, the
+// halves one after the other, one wavelength per block.  Two block barriers per half, none between a
+// half's C and the next A, since a row thread's slots are its own.  Bound by vector instructions and
+// the power they draw (2.0 GHz).  Three blocks of eight wavefronts share a CU; 1024 points, 1024
+// wavelengths: 2463 us per pass against 2927 for the staged form with its two blocks (2483 and 2517
+// with two and four wavelengths per block and the next one's rows prefetched).
+template <int M, int PAD, bool CONJ, int HM, bool FULL>
+__device__ __forceinline__ void col_split3_body(const ColArgs& a, int bx, int by, float2* tile, float2* tab) {
+  using G = ColSplit3<M, PAD>;
+  constexpr int N = M / PAD, TX = 8, NT = TX * G::L, NH = G::NH;
+  const int tid = threadIdx.x;
+  const int kx0 = bx * TX;
+  const int w = by;
+  const WlConst c = load_uniform(a.wl + a.w_begin + w);
+  if ((kx0 < M / 2 ? kx0 : M - (kx0 + TX - 1)) > c.radius) return;  // as trim_evanescent
+
+  // A and C: thread of column t % 8, row t / 8 + 64 r; B: lane of column t / 64.  The addresses are
+  // formed where they are used (opaque_lane_row), or they alone would take ten of the 80 registers
+  // that six wavefronts per SIMD leave.
+  auto own_slots = [&](int t) { return tile + t % TX * G::REG + G::slot(0, 0) + t / TX + (t / TX >> 3); };
+  constexpr int S1 = G::slot(1, 0), S8 = G::slot(0, 8);
+
+  const uint64_t base = reinterpret_cast<uint64_t>(a.spec + static_cast<size_t>(w) * N * M);
+  const uint64_t base_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
+  const uint64_t base_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32)));
+  const auto rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((base_hi << 32) | base_lo), 0, N * M * 8,
+                                                    kBufferRsrcWord3);
+  constexpr unsigned kNowhere = 0x80000000u;  // beyond every plane: loads give zero, stores drop
+  float2 x[8], acc[8];
+  {
+    const int t = opaque_lane_row(tid), j = t / TX;
+    const unsigned voff = static_cast<unsigned>((j * M + kx0 + t % TX) * 8);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      const int y = j + 64 * r;
+      const unsigned off = (FULL || (y >= a.in_lo && y < a.in_hi)) ? voff : kNowhere;
+      x[r] = buffer_load_c64(rs, off, 64 * r * M * 8);
+    }
+  }
+  for (int i = tid; i < G::COUNT; i += NT) tab[i] = a.tw[i];
+  static_for<0, NH>([&](auto hc) {
+    constexpr int h = decltype(hc)::value;
+    {
+      float2 v[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) v[r] = x[r];
+      if constexpr (h == 1) dft_odd<8>(v);
+      else DFT<8, false, false>::run(v);
+      float2* const own = own_slots(opaque_lane_row(tid));
+#pragma unroll
+      for (int k = 0; k < 8; ++k) own[k * S1] = v[k];
+    }
+    __syncthreads();
+    {
+      float2 f[8];
+      const int t = opaque_lane_row(tid), lane = t & 63, k1 = t & 7, l8 = lane >> 3;
+      float2* const freq = tile + (t >> 6) * G::REG + k1 * S1;
+      float2* const fixed = freq + l8;       // (k1, l8 + 8 i): B1 and its inverse
+      float2* const run = freq + l8 * S8;    // (k1, i + 8 l8): B2
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = fixed[i * S8];
+      dft8_table<false>(f, tab + h * 8 + k1, NH * 8);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) fixed[i * S8] = f[i];
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = run[i];
+      dft8_table<false>(f, tab + G::OFF_B2 + h * 64 + lane, NH * 64);
+      apply_transfer<M, PAD, CONJ, HM, h, 64, 8>(f, a, c, w, kx0 + (t >> 6), h, lane);
+      DFT<8, true, false>::run(f);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) run[i] = f[i];
+      wave_sync();
+#pragma unroll
+      for (int i = 0; i < 8; ++i) f[i] = fixed[i * S8];
+      dft8_table<true>(f, tab + G::OFF_R + l8, 8);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) fixed[i * S8] = f[i];
+    }
+    __syncthreads();
+    {
+      float2 y[8];
+      const int t = opaque_lane_row(tid), j = t / TX;
+      const float2* const own = own_slots(t);
+#pragma unroll
+      for (int k = 0; k < 8; ++k) y[k] = own[k * S1];
+      dft8_table<true>(y, tab + G::OFF_C + j, 64);
+      if constexpr (h == 0) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r) acc[r] = y[r];
+      } else {  // the odd half turned by the conjugate of w_M^n
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+          const float2 q = tab[G::OFF_W + j + 64 * r];
+          acc[r] = make_float2(fmaf(q.y, y[r].y, fmaf(q.x, y[r].x, acc[r].x)),
+                               fmaf(-q.y, y[r].x, fmaf(q.x, y[r].y, acc[r].y)));
+        }
+      }
+    }
+  });
+  const int t = opaque_lane_row(tid), jv = t / TX;
+  const unsigned voff = static_cast<unsigned>((jv * M + kx0 + t % TX) * 8);
+#pragma unroll
+  for (int r = 0; r < 8; ++r) {
+    const int row = jv + 64 * r;
+    const unsigned off = (FULL || (row >= a.out_lo && row < a.out_hi)) ? voff : kNowhere;
+    buffer_store_c64(rs, off, 64 * r * M * 8, acc[r]);
+  }
+}
+
 // Shape of the column kernels: the split transforms where the length has them (radix plan 0),
 // else the staged form.
 template <int M, int PAD, int TX, int V>
 struct ColShape {
+  static constexpr bool SPLIT3 = V == 0 && ColSplit3<M, PAD>::BUILT;  // TX = 8
   static constexpr bool SPLIT = V == 0 && ColSplit<M, PAD>::BUILT;
-  static constexpr int THREADS = SPLIT ? ColSplit<M, PAD>::threads(TX) : TX * Geo<M>::P;
-  static constexpr int SLOTS = SPLIT ? PAD * TX * ColSplit<M, PAD>::region(TX) : TX * Geo<M>::COL_REGION;
-  static constexpr int TABLE = SPLIT ? ColSplit<M, PAD>::COUNT : twiddle_count<M, V>();
+  static constexpr int THREADS =
+      SPLIT3 ? TX * ColSplit3<M, PAD>::L : SPLIT ? ColSplit<M, PAD>::threads(TX) : TX * Geo<M>::P;
+  static constexpr int SLOTS = SPLIT3  ? TX * ColSplit3<M, PAD>::REG
+                               : SPLIT ? PAD * TX * ColSplit<M, PAD>::region(TX)
+                                       : TX * Geo<M>::COL_REGION;
+  static constexpr int TABLE =
+      SPLIT3 ? ColSplit3<M, PAD>::COUNT : SPLIT ? ColSplit<M, PAD>::COUNT : twiddle_count<M, V>();
+  // wavefronts per SIMD the registers are held to: three blocks of eight wavefronts per CU for the
+  // halves of 512 points, else four
+  static constexpr int WAVES = SPLIT3 ? 6 : 4;
 };
 
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V>
 __device__ __forceinline__ void col_any_body(const ColArgs& a, int bx, int by, float2* tile, float2* tw) {
-  if constexpr (ColShape<M, PAD, TX, V>::SPLIT) col_split_body<M, PAD, CONJ, TX, HM, FULL>(a, bx, by, tile, tw);
+  if constexpr (ColShape<M, PAD, TX, V>::SPLIT3) col_split3_body<M, PAD, CONJ, HM, FULL>(a, bx, by, tile, tw);
+  else if constexpr (ColShape<M, PAD, TX, V>::SPLIT) col_split_body<M, PAD, CONJ, TX, HM, FULL>(a, bx, by, tile, tw);
   else col_body<M, PAD, CONJ, TX, HM, FULL, V>(a, bx, by, tile, tw);
 }
 
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V = 0>
-__global__ void __launch_bounds__((ColShape<M, PAD, TX, V>::THREADS)) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__((ColShape<M, PAD, TX, V>::THREADS)) __attribute__((amdgpu_waves_per_eu((ColShape<M, PAD, TX, V>::WAVES))))
 col_kernel(ColArgs a) {
   __shared__ float2 tile[ColShape<M, PAD, TX, V>::SLOTS];
   __shared__ float2 tw[ColShape<M, PAD, TX, V>::TABLE];
@@ -872,7 +990,7 @@ col_kernel(ColArgs a) {
 // One launch of a column pass for several designs of the same transform length (see
 // row_group_kernel); every task starts at a multiple of 16 blocks.
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL>
-__global__ void __launch_bounds__((ColShape<M, PAD, TX, 0>::THREADS)) __attribute__((amdgpu_waves_per_eu(4)))
+__global__ void __launch_bounds__((ColShape<M, PAD, TX, 0>::THREADS)) __attribute__((amdgpu_waves_per_eu((ColShape<M, PAD, TX, 0>::WAVES))))
 col_group_kernel(GroupArgs g) {
   __shared__ float2 tile[ColShape<M, PAD, TX, 0>::SLOTS];
   __shared__ float2 tw[ColShape<M, PAD, TX, 0>::TABLE];
@@ -1125,7 +1243,7 @@ __device__ __forceinline__ void lds_columns(const WlConst& c, const ColArgs& ca,
 #pragma unroll
         for (int i = 0; i < R2; ++i) v[i] = col[(i + L * lane) * RS];
         col_freq_forward<M, PAD>(v, tab, h, lane);
-        apply_transfer<M, PAD, CONJ, kHEval, h>(v, ca, c, 0, kx, h, lane);
+        apply_transfer<M, PAD, CONJ, kHEval, h, R1, R2>(v, ca, c, 0, kx, h, lane);
         col_freq_inverse<M, PAD>(v);
 #pragma unroll
         for (int i = 0; i < R2; ++i) col[(i + L * lane) * RS] = v[i];

@@ -98,7 +98,98 @@ void check() {
   std::fprintf(stderr, "M=%d pad %d: back %.3g\n", M, PAD, std::sqrt(err / ref));
 }
 
+// the same for halves of 512 points, whose B is 8 x 8 with an exchange of its own
+template <int M, int PAD>
+void check3() {
+  using G = ColSplit3<M, PAD>;
+  constexpr int NH = G::NH, LEN = G::LEN;
+  std::vector<float2> tab;
+  col3_table_host<M, PAD>(tab);
+  std::mt19937 g(M + PAD);
+  std::normal_distribution<float> nd;
+  std::vector<float2> x(LEN), acc(LEN);
+  for (auto& v : x) v = make_float2(nd(g), nd(g));
+  std::set<int> used;
+  for (int k1 = 0; k1 < 8; ++k1)
+    for (int j = 0; j < 64; ++j)
+      if (G::slot(k1, j) >= G::REG || !used.insert(G::slot(k1, j)).second) {
+        std::printf("M=%d pad %d: slot (%d, %d)\n", M, PAD, k1, j);
+        ++failures;
+      }
+  std::set<int> rows, b1, b2;  // 16 lanes: eight columns and two j; eight k1 and two j1 (m)
+  for (int l = 0; l < 16; ++l) {
+    rows.insert((l % 8 * G::REG + G::slot(0, l / 8)) % 16);
+    b1.insert(G::slot(l % 8, l / 8) % 16);
+    b2.insert(G::slot(l % 8, 8 * (l / 8)) % 16);
+  }
+  if (rows.size() < 16 || b1.size() < 16 || b2.size() < 16) {
+    std::printf("M=%d pad %d: bank conflicts\n", M, PAD);
+    ++failures;
+  }
+  double err = 0.0, ref = 0.0;
+  for (int h = 0; h < NH; ++h) {
+    std::vector<float2> lds(G::REG);
+    for (int j = 0; j < 64; ++j) {
+      float2 v[8];
+      for (int r = 0; r < 8; ++r) v[r] = x[j + 64 * r];
+      if (h) dft_odd<8>(v);
+      else DFT<8, false, false>::run(v);
+      for (int k = 0; k < 8; ++k) lds[G::slot(k, j)] = v[k];
+    }
+    auto step = [&](auto body) {  // every lane reads all before any writes, as wave_sync orders it
+      std::vector<float2> out(lds);
+      for (int lane = 0; lane < 64; ++lane) body(lane & 7, lane >> 3, lane, out);
+      lds = out;
+    };
+    step([&](int k1, int j1, int, std::vector<float2>& out) {
+      float2 f[8];
+      for (int i = 0; i < 8; ++i) f[i] = lds[G::slot(k1, j1 + 8 * i)];
+      dft8_table<false>(f, tab.data() + h * 8 + k1, NH * 8);
+      for (int i = 0; i < 8; ++i) out[G::slot(k1, j1 + 8 * i)] = f[i];
+    });
+    step([&](int k1, int m, int lane, std::vector<float2>& out) {
+      float2 f[8];
+      for (int i = 0; i < 8; ++i) f[i] = lds[G::slot(k1, i + 8 * m)];
+      dft8_table<false>(f, tab.data() + G::OFF_B2 + h * 64 + lane, NH * 64);
+      for (int q = 0; q < 8; ++q) {
+        const long long K = NH * (lane + 64 * q) + h;
+        cd s = 0.0;
+        for (int n = 0; n < LEN; ++n) s += cd(x[n].x, x[n].y) * std::polar(1.0, -2.0 * M_PI * double((n * K) % M) / M);
+        err += std::norm(s - cd(f[q].x, f[q].y));
+        ref += std::norm(s);
+        f[q] = make_float2(f[q].x / M, f[q].y / M);
+      }
+      DFT<8, true, false>::run(f);
+      for (int i = 0; i < 8; ++i) out[G::slot(k1, i + 8 * m)] = f[i];
+    });
+    step([&](int k1, int j1, int, std::vector<float2>& out) {
+      float2 f[8];
+      for (int i = 0; i < 8; ++i) f[i] = lds[G::slot(k1, j1 + 8 * i)];
+      dft8_table<true>(f, tab.data() + G::OFF_R + j1, 8);
+      for (int i = 0; i < 8; ++i) out[G::slot(k1, j1 + 8 * i)] = f[i];
+    });
+    for (int j = 0; j < 64; ++j) {
+      float2 y[8];
+      for (int k = 0; k < 8; ++k) y[k] = lds[G::slot(k, j)];
+      dft8_table<true>(y, tab.data() + G::OFF_C + j, 64);
+      for (int r = 0; r < 8; ++r) {
+        if (h == 0) acc[j + 64 * r] = y[r];
+        else acc[j + 64 * r] = cadd(acc[j + 64 * r], cmulc(y[r], tab[G::OFF_W + j + 64 * r]));
+      }
+    }
+  }
+  worst_fwd = std::max(worst_fwd, std::sqrt(err / ref));
+  err = ref = 0.0;
+  for (int n = 0; n < LEN; ++n) {
+    err += std::norm(cd(acc[n].x, acc[n].y) - cd(x[n].x, x[n].y));
+    ref += std::norm(cd(x[n].x, x[n].y));
+  }
+  worst_back = std::max(worst_back, std::sqrt(err / ref));
+  std::fprintf(stderr, "M=%d pad %d: back %.3g\n", M, PAD, std::sqrt(err / ref));
+}
+
 int main() {
+  check3<1024, 2>(); check3<512, 1>();
   check<64, 2>(); check<96, 2>(); check<128, 2>(); check<192, 2>(); check<256, 2>(); check<384, 2>(); check<512, 2>();
   check<64, 1>(); check<96, 1>(); check<128, 1>(); check<192, 1>(); check<256, 1>(); check<384, 1>();
   std::printf("%.9g %.9g\n", worst_fwd, worst_back);
