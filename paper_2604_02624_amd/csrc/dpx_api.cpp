@@ -552,14 +552,15 @@ int64_t row_bytes(const Design& d, int mode, int wc, int nwb, bool accumulate, b
 dpx_status run_row(dpx_plan* p, const Design& d, int mode, RowArgs a, int row_lo, int row_hi, hipStream_t s) {
   a.row_lo = row_lo;
   a.row_hi = row_hi;
-  const int rg = dpx::row_rows_per_block(d.M, d.pad, mode);
-  const int nrb = (row_hi - row_lo + rg - 1) / rg;
   const int nwb = (a.w_count + d.w_per_block - 1) / d.w_per_block;
+  const bool small = dpx::row_blocks_small(d.M, d.pad, mode, row_hi - row_lo, nwb);
+  const int rg = dpx::row_rows_per_block(d.M, d.pad, mode, small);
+  const int nrb = (row_hi - row_lo + rg - 1) / rg;
   TimedLaunch t{dpx::row_pass_kind(mode), nullptr, nullptr,
                 row_bytes(d, mode, a.w_count, nwb, a.accumulate != 0, a.u_in != nullptr),
                 row_flops(d, mode, a.w_count, row_hi - row_lo)};
   DPX_TRY(timer_begin(p, s, t));
-  hipError_t e = dpx::launch_row(d.M, d.pad, mode, d.row_plan, a, nrb, nwb, s);
+  hipError_t e = dpx::launch_row(d.M, d.pad, mode, d.row_plan, small, a, nrb, nwb, s);
   if (e != hipSuccess) return fail(DPX_E_DEVICE, "row pass (mode %d) launch failed: %s", mode, hipGetErrorString(e));
   DPX_TRY(timer_end(p, s, t));
   return DPX_OK;
@@ -643,9 +644,14 @@ dpx_status run_col(dpx_plan* p, const Design& d, int lane, int layer, bool conj,
 
 int64_t h_off_layer(const Design& d, int l) { return d.h_off + static_cast<int64_t>(l) * d.N * d.N; }
 
-// Whether the last row pass also forms the intensities: its blocks hold whole detector bins.  Else
-// (1600 points: three rows per block) the binning is a launch of its own.
-bool bins_in_rows(const Design& d) { return dpx::row_rows_per_block(d.M, d.pad, dpx::ROW_FWD_LAST) % d.b == 0; }
+// Whether the last row pass, of wc wavelengths (0: grouped launches), also forms the intensities: its
+// blocks hold whole detector bins.  Else (1600 points: three rows per block; wide bins on small blocks)
+// the binning is a launch of its own.
+bool bins_in_rows(const Design& d, int wc = 0) {
+  const bool small = wc > 0 && dpx::row_blocks_small(d.M, d.pad, dpx::ROW_FWD_LAST, d.F,
+                                                     (wc + d.w_per_block - 1) / d.w_per_block);
+  return dpx::row_rows_per_block(d.M, d.pad, dpx::ROW_FWD_LAST, small) % d.b == 0;
+}
 
 // forward over one chunk of wavelengths [w0, w0 + wc) on lane `lane`; leaves the output
 // field in ofov, and the intensities where bins_in_rows (unless `intensity` is null).  `after_first` (may be null) is recorded on s after the first launch.
@@ -655,7 +661,7 @@ dpx_status forward_chunk(dpx_plan* p, const Design& d, const float* h, const flo
   RowArgs a = row_args(p, d, w0, wc, lane);
   a.u_in = u_in ? reinterpret_cast<const float2*>(u_in) + d.u_off : nullptr;
   a.layer = 0;
-  a.intensity = intensity && bins_in_rows(d) ? intensity + d.img_off : nullptr;
+  a.intensity = intensity && bins_in_rows(d, wc) ? intensity + d.img_off : nullptr;
   if (d.z_in > 0.0) {
     // input plane: u_in to the spectrum unchanged, across the input gap, then layer 0 as a
     // middle pass (row inverse transform, transmission, checkpoint, row transform)
@@ -1761,7 +1767,7 @@ dpx_status dpx_forward(dpx_plan* p, const float* h, const float* u_in, float* in
         if (lane == 1 && c == 1) DPX_HIP(hipStreamWaitEvent(ls, p->ev_offset, 0));
         DPX_TRY(forward_chunk(p, d, h, u_in, intensity, w0, wc, lane, ls,
                               (c == 0 && d.lanes > 1) ? p->ev_offset : nullptr));
-        if (bins_in_rows(d)) continue;
+        if (bins_in_rows(d, wc)) continue;
         const float2* of = (p->opts.checkpoint_mode == 1)
                                ? d.ofov + static_cast<int64_t>(lane) * d.wl_chunk * d.F * d.F
                                : d.ofov + static_cast<int64_t>(w0) * d.F * d.F;

@@ -49,9 +49,15 @@ constexpr int row_threads_of_mode(int values, int pad, int mode) {
 }
 // Threads of a row-pass block for P lanes per transform: the mode's count when transforms tile
 // a wavefront; three or so whole transforms (about 256 threads) when one spans wavefronts.
-constexpr int row_threads_for(int M, int P, int pad, int mode) {
-  return (P <= 64 && 64 % P == 0) ? row_threads_of_mode(M / P, pad, mode) : (256 / P) * P;
+// small: 128 threads, for launches that would leave CUs without a block (row_blocks_small): two
+// wavefronts on each of many CUs instead of eight on a few, which share a SIMD's issue.
+constexpr int kSmallRowThreads = 128;
+constexpr int row_threads_for(int M, int P, int pad, int mode, bool small = false) {
+  if (!(P <= 64 && 64 % P == 0)) return (256 / P) * P;
+  return small ? kSmallRowThreads : row_threads_of_mode(M / P, pad, mode);
 }
+// Whether a row pass of `rows` rows and n_w wavelength blocks takes the small blocks
+bool row_blocks_small(int M, int pad, int mode, int rows, int n_w);
 
 struct RowArgs {
   float2* spec;              // [wc][N][M] row-transformed planes of the current chunk
@@ -229,7 +235,7 @@ __device__ __forceinline__ int group_task(const GroupArgs& g, int b) {
 // Supported transform lengths; the pass launchers of each live in their own translation unit.
 #define DPX_FOR_EACH_M(X) X(64) X(96) X(128) X(192) X(256) X(384) X(512) X(1024) X(1600)
 #define DPX_DECLARE_PASS_LAUNCHERS(m)                                                                   \
-  hipError_t launch_row_##m(int pad, int mode, int plan, const RowArgs& a, int n_row_blocks,             \
+  hipError_t launch_row_##m(int pad, int mode, int plan, bool small, const RowArgs& a, int n_row_blocks, \
                             int n_w_blocks, hipStream_t s);                                             \
   hipError_t launch_row_group_##m(int pad, int mode, const GroupArgs& g, hipStream_t s);                \
   hipError_t launch_col_##m(int pad, bool conj, int variant, int plan, const ColArgs& a, int w_count,    \
@@ -264,7 +270,7 @@ void build_col_table(int M, int pad, std::vector<float2>& out);
 
 // launchers (dpx_kernels.hip); each returns a hipError_t from the launch
 // plan: the radix plan of the transforms (0 .. radix_plan_count(M) - 1)
-hipError_t launch_row(int M, int pad, int mode, int plan, const RowArgs& a, int n_row_blocks, int n_w_blocks,
+hipError_t launch_row(int M, int pad, int mode, int plan, bool small, const RowArgs& a, int n_row_blocks, int n_w_blocks,
                       hipStream_t s);
 constexpr int kColVariants = 5;
 bool col_variant_supported(int M, int pad, int variant);
@@ -316,6 +322,7 @@ void build_twiddle_table(int M, int plan, std::vector<float2>& out);
 int radix_plan_count(int M);
 const char* radix_plan_name(int M, int plan);
 int row_lanes_per_transform(int M);  // P = M / E
-int row_rows_per_block(int M, int pad, int mode);  // rows (transforms) per row-pass block
+// rows (transforms) per row-pass block
+int row_rows_per_block(int M, int pad, int mode, bool small = false);
 
 }  // namespace dpx

@@ -499,10 +499,21 @@ int row_lanes_per_transform(int M) {
   }
 }
 
-int row_rows_per_block(int M, int pad, int mode) {
+int row_rows_per_block(int M, int pad, int mode, bool small) {
   const int P = row_lanes_per_transform(M);
   if (P == 0) return 0;
-  return row_threads_for(M, P, pad, mode) / P;
+  return row_threads_for(M, P, pad, mode, small) / P;
+}
+
+// Fewer blocks than the chip has CUs: the rows of 128-thread blocks spread over up to four times as
+// many.  Measured, forward of three layers, us: one wavelength of 96 x 96 39 -> 34, 192 x 192 51 -> 43,
+// 256 x 256 48 -> 42, 512 x 512 63 -> 59; eight of 192 x 192 60 -> 54; from 256 blocks on both forms
+// take the same time and the larger blocks stage the twiddles for more rows.
+bool row_blocks_small(int M, int pad, int mode, int rows, int n_w) {
+  const int P = row_lanes_per_transform(M);
+  if (P == 0 || P > 64 || 64 % P) return false;
+  const int per = row_rows_per_block(M, pad, mode);
+  return static_cast<int64_t>((rows + per - 1) / per) * n_w < 256;
 }
 
 namespace {
@@ -577,10 +588,10 @@ void build_col_table(int M, int pad, std::vector<float2>& out) {
 // ------------------------------------------------------------------------------------------
 // Dispatch to the per-length launchers
 // ------------------------------------------------------------------------------------------
-hipError_t launch_row(int M, int pad, int mode, int plan, const RowArgs& a, int n_row_blocks, int n_w_blocks,
+hipError_t launch_row(int M, int pad, int mode, int plan, bool small, const RowArgs& a, int n_row_blocks, int n_w_blocks,
                       hipStream_t s) {
   switch (M) {
-#define DPX_CASE(m) case m: return launch_row_##m(pad, mode, plan, a, n_row_blocks, n_w_blocks, s);
+#define DPX_CASE(m) case m: return launch_row_##m(pad, mode, plan, small, a, n_row_blocks, n_w_blocks, s);
     DPX_FOR_EACH_M(DPX_CASE)
 #undef DPX_CASE
     default:

@@ -34,7 +34,7 @@ hipError_t with_plan(int plan, F&& f) {
 }
 
 template <int PAD, int V>
-hipError_t row_mode(int mode, const RowArgs& a, dim3 grid, hipStream_t s) {
+hipError_t row_mode(int mode, bool small, const RowArgs& a, dim3 grid, hipStream_t s) {
   if constexpr (M == 1600 && PAD == 2 && V == 0) {
     if (mode == ROW_FWD_MID || mode == ROW_ADJ_MID) {
       if (mode == ROW_FWD_MID)
@@ -44,20 +44,28 @@ hipError_t row_mode(int mode, const RowArgs& a, dim3 grid, hipStream_t s) {
       return hipGetLastError();
     }
   }
-  switch (mode) {
+  const auto go = [&](auto sc) -> hipError_t {
+    constexpr bool SM = decltype(sc)::value;
+    switch (mode) {
 #define DPX_ROW(MD) \
-  case MD: row_kernel<M, PAD, MD, V><<<grid, row_block_threads<M, PAD, MD>(), 0, s>>>(a); break;
-    DPX_ROW(ROW_FWD_FIRST)
-    DPX_ROW(ROW_FWD_MID)
-    DPX_ROW(ROW_FWD_LAST)
-    DPX_ROW(ROW_ADJ_SEED)
-    DPX_ROW(ROW_ADJ_MID)
-    DPX_ROW(ROW_ADJ_LAST)
-    DPX_ROW(ROW_ADJ_LAST_U)
+  case MD: row_kernel<M, PAD, MD, V, SM><<<grid, row_block_threads<M, PAD, MD, SM>(), 0, s>>>(a); break;
+      DPX_ROW(ROW_FWD_FIRST)
+      DPX_ROW(ROW_FWD_MID)
+      DPX_ROW(ROW_FWD_LAST)
+      DPX_ROW(ROW_ADJ_SEED)
+      DPX_ROW(ROW_ADJ_MID)
+      DPX_ROW(ROW_ADJ_LAST)
+      DPX_ROW(ROW_ADJ_LAST_U)
 #undef DPX_ROW
-    default: return hipErrorInvalidValue;
+      default: return hipErrorInvalidValue;
+    }
+    return hipGetLastError();
+  };
+  if (small) {
+    if constexpr (Geo<M>::WAVE_LOCAL) return go(std::true_type{});
+    else return hipErrorInvalidValue;
   }
-  return hipGetLastError();
+  return go(std::false_type{});
 }
 
 template <int PAD>
@@ -199,13 +207,13 @@ hipError_t col_group_variant(int variant, bool table, bool conj, bool full, cons
 
 }  // namespace
 
-hipError_t DPX_NAME(launch_row_)(int pad, int mode, int plan, const RowArgs& a, int n_row_blocks, int n_w_blocks,
+hipError_t DPX_NAME(launch_row_)(int pad, int mode, int plan, bool small, const RowArgs& a, int n_row_blocks, int n_w_blocks,
                                  hipStream_t s) {
   const dim3 grid(n_row_blocks, n_w_blocks);
   return with_plan(plan, [&](auto vc) -> hipError_t {
     constexpr int V = decltype(vc)::value;
-    if (pad == 2) return row_mode<2, V>(mode, a, grid, s);
-    if (pad == 1) return row_mode<1, V>(mode, a, grid, s);
+    if (pad == 2) return row_mode<2, V>(mode, small, a, grid, s);
+    if (pad == 1) return row_mode<1, V>(mode, small, a, grid, s);
     return hipErrorInvalidValue;
   });
 }

@@ -123,8 +123,8 @@ __device__ __forceinline__ float2 transmission(float h, const WlConst& c) {
   return t;
 }
 
-template <int M, int PAD, int MODE>
-constexpr int row_block_threads() { return row_threads_for(M, Geo<M>::P, PAD, MODE); }
+template <int M, int PAD, int MODE, bool SMALL = false>
+constexpr int row_block_threads() { return row_threads_for(M, Geo<M>::P, PAD, MODE, SMALL); }
 
 // ------------------------------------------------------------------------------------------
 // Row pass.  A block owns G = 256 / P consecutive rows (one transform group per row) and
@@ -132,9 +132,9 @@ constexpr int row_block_threads() { return row_threads_for(M, Geo<M>::P, PAD, MO
 // ------------------------------------------------------------------------------------------
 // Block (bx, by) of a row pass: rows row_lo + bx G .. + G - 1, wavelength block by.
 // lds_all: G exchange regions; tw: room for the twiddle table (both in LDS).
-template <int M, int PAD, int MODE, int V = 0>
+template <int M, int PAD, int MODE, int V = 0, bool SMALL = false>
 __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float2* lds_all, float2* tw) {
-  constexpr int kRowThreads = row_block_threads<M, PAD, MODE>();
+  constexpr int kRowThreads = row_block_threads<M, PAD, MODE, SMALL>();
   constexpr int E = Geo<M>::E;
   constexpr int P = Geo<M>::P;
   constexpr int G = kRowThreads / P;
@@ -354,11 +354,11 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
   }
 }
 
-template <int M, int PAD, int MODE, int V = 0>
-__global__ void __launch_bounds__((row_block_threads<M, PAD, MODE>())) row_kernel(RowArgs a) {
-  __shared__ float2 lds_all[row_block_threads<M, PAD, MODE>() / Geo<M>::P * Geo<M>::ROW_REGION];
+template <int M, int PAD, int MODE, int V = 0, bool SMALL = false>
+__global__ void __launch_bounds__((row_block_threads<M, PAD, MODE, SMALL>())) row_kernel(RowArgs a) {
+  __shared__ float2 lds_all[row_block_threads<M, PAD, MODE, SMALL>() / Geo<M>::P * Geo<M>::ROW_REGION];
   __shared__ float2 tw[twiddle_count<M, V>()];
-  row_body<M, PAD, MODE, V>(a, blockIdx.x, blockIdx.y, lds_all, tw);
+  row_body<M, PAD, MODE, V, SMALL>(a, blockIdx.x, blockIdx.y, lds_all, tw);
 }
 
 // The same pass with at least three wavefronts per SIMD (a cap of 168 registers): the forward
