@@ -114,6 +114,24 @@ struct ColSplit3 {
   static __host__ __device__ constexpr int slot(int k1, int j) { return k1 * 74 + j + (j >> 3); }
 };
 
+// LEN = 800 (1600 zero-padded points) = 25 . 32: A and C on 32 threads per column with 25 rows each,
+// B on 25 of 32 lanes with 32 values each, so two columns per wavefront.  The halves follow each other
+// as in ColSplit3, one exchange each way, and every slot is read back by the thread that owns it.  The
+// tables (21 KB) are read through the caches: the three blocks that share a CU leave no LDS for them.
+template <int M, int PAD>
+struct ColSplit800 {
+  static constexpr int LEN = M / PAD, NH = PAD;
+  static constexpr bool BUILT = LEN == 800 && PAD == 2;
+  static constexpr int R1 = 25, R2 = 32, L = 32, GP = 32;
+  // table: B [16][NH][32] (25 used), C [24][32], w_M^n [LEN]
+  static constexpr int OFF_C = 16 * NH * 32;
+  static constexpr int OFF_W = OFF_C + 24 * 32;
+  static constexpr int COUNT = OFF_W + LEN;
+  // k1 33 slots apart (odd), columns 826 (2 mod 8, for eight columns and two j)
+  static constexpr int REG = 826;
+  static __host__ __device__ constexpr int slot(int k1, int j) { return k1 * 33 + j; }
+};
+
 // exp(-2 pi i num / den) with the numerator reduced first
 inline float2 unit_root(long long num, long long den) {
   const double ang = 6.283185307179586476925286766559 * static_cast<double>(num % den) / static_cast<double>(den);
@@ -178,6 +196,18 @@ inline void col3_table_host(std::vector<float2>& out) {
     for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
 }
 
+template <int M, int PAD>
+inline void col800_table_host(std::vector<float2>& out) {
+  using G = ColSplit800<M, PAD>;
+  out.assign(G::COUNT, make_float2(1.f, 0.f));
+  for (int e = 0; e < 16; ++e)
+    for (int h = 0; h < G::NH; ++h)
+      for (int k1 = 0; k1 < G::R1; ++k1) out[(e * G::NH + h) * 32 + k1] = input_twiddle(32, e, G::NH * k1 + h, M);
+  for (int e = 0; e < 24; ++e)
+    for (int j = 0; j < 32; ++j) out[G::OFF_C + e * 32 + j] = input_twiddle(25, e, j, G::LEN);
+  for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
+}
+
 // ------------------------------------------------------------------------------------------
 // Register transforms
 // ------------------------------------------------------------------------------------------
@@ -196,6 +226,19 @@ __device__ __forceinline__ void fused_butterfly_quarter(float2 e, float2 o, floa
   hi = make_float2(fmaf(-cq, v, e.x), fmaf(cq, u, e.y));
 }
 
+// the last level of dft_fused: v from the transforms of its even and odd inputs, p its own pairs
+template <int R, bool INV>
+__device__ __forceinline__ void dft_fused_join(const float2* e, const float2* o, const float2* p, float2* v) {
+#pragma unroll
+  for (int k = 0; k < (R > 2 ? R / 4 : 1); ++k) {
+    const float2 q = p[k];
+    const float t = INV ? -q.y : q.y;
+    fused_butterfly<INV>(e[k], o[k], q.x, t, v[k], v[k + R / 2]);
+    if constexpr (R > 2)
+      fused_butterfly_quarter<INV>(e[k + R / 4], o[k + R / 4], q.x, t, v[k + R / 4], v[k + 3 * R / 4]);
+  }
+}
+
 // R-point transform (a power of two) of v[r] base^r, natural order in and out; p: the R / 2 pairs
 // of base (of its conjugate's conjugate: INV negates t)
 template <int R, bool INV>
@@ -209,14 +252,7 @@ __device__ __forceinline__ void dft_fused(float2* v, const float2* p) {
     }
     dft_fused<R / 2, INV>(e, p);
     dft_fused<R / 2, INV>(o, p);
-#pragma unroll
-    for (int k = 0; k < (R > 2 ? R / 4 : 1); ++k) {
-      const float2 q = p[pair_index(R, k)];
-      const float t = INV ? -q.y : q.y;
-      fused_butterfly<INV>(e[k], o[k], q.x, t, v[k], v[k + R / 2]);
-      if constexpr (R > 2)
-        fused_butterfly_quarter<INV>(e[k + R / 4], o[k + R / 4], q.x, t, v[k + R / 4], v[k + 3 * R / 4]);
-    }
+    dft_fused_join<R, INV>(e, o, p + pair_index(R, 0), v);
   }
 }
 

@@ -535,8 +535,8 @@ const char* const kColVariantNames[kColVariants] = {"tile8", "tile16", "tile8+mi
                                                     "tile16+mirror", "dft-gemm-mfma"};
 
 // built-in choice when no variant is forced and no autotuning is asked for: the mirrored forms
-// where transforms stay in one wavefront; at 1600 the wide tile (8 columns, 10 waves per CU in
-// one block) beats the narrow one, which the registers hold to one 5-wave block per CU.  The split
+// where transforms stay in one wavefront; at 1600 unpadded the wide tile (8 columns, 10 waves per CU
+// in one block) beats the narrow one, which the registers hold to one 5-wave block per CU.  The split
 // transforms take 16 columns, so that a row segment is a whole 128-byte line (512 points, 1024
 // wavelengths: column and next row pass 1165 against 1174 us, 256 points 700 against 780), except
 // where the wide block is short of registers (384 points without padding: 96 against 66 us) or the

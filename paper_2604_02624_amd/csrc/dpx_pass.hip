@@ -114,13 +114,13 @@ hipError_t col_launch(bool conj, const ColArgs& a, int w_count, hipStream_t s) {
 // whole wavefronts, 8 / 8 for halves of 512 points), or 4 / 8 when a transform spans wavefronts (blocks stay within 1024 threads)
 template <int PAD, int V>
 constexpr int tile_narrow() {
-  if (ColShape<M, PAD, 8, V>::SPLIT3) return 8;
+  if (ColShape<M, PAD, 8, V>::SPLIT3 || ColShape<M, PAD, 8, V>::SPLIT800) return 8;
   if (ColShape<M, PAD, 16, V>::SPLIT) return ColSplit<M, PAD>::NARROW ? 8 : 16;
   return !Geo<M>::WAVE_LOCAL ? 4 : 8 * Geo<M>::P >= 64 ? 8 : 16;
 }
 template <int PAD, int V>
 constexpr int tile_wide() {
-  if (ColShape<M, PAD, 8, V>::SPLIT3) return 8;
+  if (ColShape<M, PAD, 8, V>::SPLIT3 || ColShape<M, PAD, 8, V>::SPLIT800) return 8;
   return ColShape<M, PAD, 16, V>::SPLIT || Geo<M>::WAVE_LOCAL ? 16 : 8;
 }
 constexpr bool wide_variant(int variant) { return variant == 1 || variant == 3; }
@@ -137,13 +137,18 @@ hipError_t col_launch_h(int hm, bool conj, const ColArgs& a, int w_count, hipStr
   } else {
     if (hm == kHTable || hm == kHBand || hm == kHShift) return hipErrorInvalidValue;
   }
-  if constexpr (Geo<M>::WAVE_LOCAL) {
+  if constexpr (V == 0 && ColSplit800<M, PAD>::BUILT) {
+    // whichever variant: the lanes of a column share a wavefront, and the mirrored form gives the bits
+    // of the evaluated one (128 wavelengths: 1080 against 1215 us)
+    return col_launch<PAD, TX, kHMirror, V>(conj, a, w_count, s);
+  } else if constexpr (Geo<M>::WAVE_LOCAL) {
     if (hm == kHMirror) return col_launch<PAD, TX, kHMirror, V>(conj, a, w_count, s);
+    return col_launch<PAD, TX, kHEval, V>(conj, a, w_count, s);
   } else {
     // the mirrored form exchanges H across the lanes of one wavefront
     if (hm == kHMirror) return hipErrorInvalidValue;
+    return col_launch<PAD, TX, kHEval, V>(conj, a, w_count, s);
   }
-  return col_launch<PAD, TX, kHEval, V>(conj, a, w_count, s);
 }
 
 template <int PAD>
@@ -190,12 +195,15 @@ hipError_t col_group_tx(bool conj, bool full, const GroupArgs& g, hipStream_t s)
 template <int PAD, int TX>
 hipError_t col_group_h(int hm, bool conj, bool full, const GroupArgs& g, hipStream_t s) {
   if (hm == kHTable) return col_group_tx<PAD, TX, kHTable>(conj, full, g, s);
-  if constexpr (Geo<M>::WAVE_LOCAL) {
+  if constexpr (ColSplit800<M, PAD>::BUILT) {
+    return col_group_tx<PAD, TX, kHMirror>(conj, full, g, s);
+  } else if constexpr (Geo<M>::WAVE_LOCAL) {
     if (hm == kHMirror) return col_group_tx<PAD, TX, kHMirror>(conj, full, g, s);
+    return col_group_tx<PAD, TX, kHEval>(conj, full, g, s);
   } else {
     if (hm == kHMirror) return hipErrorInvalidValue;
+    return col_group_tx<PAD, TX, kHEval>(conj, full, g, s);
   }
-  return col_group_tx<PAD, TX, kHEval>(conj, full, g, s);
 }
 
 template <int PAD>
@@ -248,7 +256,8 @@ void DPX_NAME(twiddle_table_)(int plan, std::vector<float2>& out) {
 void DPX_NAME(col_table_)(int pad, std::vector<float2>& out) {
   const auto build = [&](auto padc) {
     constexpr int PD = decltype(padc)::value;
-    if constexpr (ColSplit3<M, PD>::BUILT) col3_table_host<M, PD>(out);
+    if constexpr (ColSplit800<M, PD>::BUILT) col800_table_host<M, PD>(out);
+    else if constexpr (ColSplit3<M, PD>::BUILT) col3_table_host<M, PD>(out);
     else col_table_host<M, PD>(out);
   };
   if (pad == 2) build(std::integral_constant<int, 2>{});
@@ -256,7 +265,7 @@ void DPX_NAME(col_table_)(int pad, std::vector<float2>& out) {
 }
 
 bool DPX_NAME(col_split_)(int pad) {
-  return pad == 2 ? ColSplit<M, 2>::BUILT || ColSplit3<M, 2>::BUILT : ColSplit<M, 1>::BUILT || ColSplit3<M, 1>::BUILT;
+  return pad == 2 ? ColSplit<M, 2>::BUILT || ColSplit3<M, 2>::BUILT || ColSplit800<M, 2>::BUILT : ColSplit<M, 1>::BUILT || ColSplit3<M, 1>::BUILT;
 }
 
 int DPX_NAME(col_tile_width_)(int pad, int variant) {

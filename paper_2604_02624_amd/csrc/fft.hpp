@@ -91,6 +91,7 @@ constexpr int first_factor(int r) {
   if (r % 4 == 0) return 4;
   if (r % 2 == 0) return 2;
   if (r % 3 == 0) return 3;
+  if (r % 5 == 0) return 5;
   return r;
 }
 

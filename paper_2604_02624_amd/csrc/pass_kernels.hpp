@@ -951,33 +951,147 @@ __device__ __forceinline__ void col_split3_body(const ColArgs& a, int bx, int by
   }
 }
 
+// The same for halves of 800 points (ColSplit800): eight columns on 256 threads.  Bound by issue
+// and by the registers: 25 inputs, 25 sums and 32 frequencies per lane hold it to 12 wavefronts per CU,
+// where the staged form ran 10 on twice the points.  128 wavelengths of the glass design's discs,
+// us per pass: staged, every frequency evaluated 1535; this form with two blocks per CU 1215, with the
+// mirrored transfer function 1080, with three blocks 1012.
+template <int M, int PAD, bool CONJ, int HM, bool FULL>
+__device__ __forceinline__ void col_split800_body(const ColArgs& a, int bx, int by, float2* tile) {
+  using G = ColSplit800<M, PAD>;
+  constexpr int N = M / PAD, TX = 8, R1 = G::R1, R2 = G::R2, L = G::L;
+  const int tid = threadIdx.x;
+  const int kx0 = bx * TX;
+  const int w = by;
+  const WlConst c = load_uniform(a.wl + a.w_begin + w);
+  if ((kx0 < M / 2 ? kx0 : M - (kx0 + TX - 1)) > c.radius) return;  // as trim_evanescent
+
+  const uint64_t base = reinterpret_cast<uint64_t>(a.spec + static_cast<size_t>(w) * N * M);
+  const uint64_t base_lo = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base)));
+  const uint64_t base_hi = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(base >> 32)));
+  const auto rs = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>((base_hi << 32) | base_lo), 0, N * M * 8,
+                                                    kBufferRsrcWord3);
+  constexpr unsigned kNowhere = 0x80000000u;  // beyond every plane: loads give zero, stores drop
+  float2 x[R1], acc[R1];
+  {
+    const int t = opaque_lane_row(tid), j = t / TX;
+    const unsigned voff = static_cast<unsigned>((j * M + kx0 + t % TX) * 8);
+#pragma unroll
+    for (int r = 0; r < R1; ++r) {
+      const int y = j + L * r;
+      const unsigned off = (FULL || (y >= a.in_lo && y < a.in_hi)) ? voff : kNowhere;
+      x[r] = buffer_load_c64(rs, off, L * r * M * 8);
+    }
+  }
+  static_for<0, 2>([&](auto hc) {
+    constexpr int h = decltype(hc)::value;
+    {
+      float2 v[R1];
+#pragma unroll
+      for (int r = 0; r < R1; ++r) v[r] = x[r];
+      if constexpr (h == 1) dft_odd<R1>(v);
+      else DFT<R1, false, false>::run(v);
+      const int t = opaque_lane_row(tid);
+      float2* const own = tile + t % TX * G::REG + t / TX;
+#pragma unroll
+      for (int k = 0; k < R1; ++k) own[G::slot(k, 0)] = v[k];
+    }
+    __syncthreads();
+    {
+      const int t = opaque_lane_row(tid), k1 = t % 32, cb = t / 32;
+      if (k1 < R1) {
+        float2* const freq = tile + cb * G::REG + G::slot(k1, 0);
+        const float2* const tab = a.tw + h * 32 + k1;
+        float2 f[R2];
+        {
+          float2 p[R2 / 4], even[R2 / 2], odd[R2 / 2];
+#pragma unroll
+          for (int e = 0; e < R2 / 4; ++e) p[e] = tab[e * G::NH * 32];
+#pragma unroll
+          for (int i = 0; i < R2; ++i) (i % 2 ? odd : even)[i / 2] = freq[i];
+          dft_fused<R2 / 2, false>(even, p);
+          dft_fused<R2 / 2, false>(odd, p);
+          schedule_fence();  // the last level's factors take the registers of the others
+#pragma unroll
+          for (int k = 0; k < R2 / 4; ++k) p[k] = tab[(R2 / 4 + k) * G::NH * 32];
+          dft_fused_join<R2, false>(even, odd, p, f);
+        }
+        apply_transfer<M, PAD, CONJ, HM, h, R1, R2>(f, a, c, w, kx0 + cb, h, k1);
+        DFT<R2, true, false>::run(f);
+#pragma unroll
+        for (int i = 0; i < R2; ++i) freq[i] = f[i];
+      }
+    }
+    __syncthreads();
+    {
+      float2 y[R1];
+      const int t = opaque_lane_row(tid), j = t / TX;
+      const float2* const own = tile + t % TX * G::REG + j;
+#pragma unroll
+      for (int k = 0; k < R1; ++k) y[k] = own[G::slot(k, 0)];
+#pragma unroll
+      for (int k = 1; k < R1; ++k) y[k] = cmulc(y[k], a.tw[G::OFF_C + (k - 1) * 32 + j]);
+      schedule_fence();  // the factors of the odd half wait until the transform has let go of its own
+      DFT<R1, true, false>::run(y);
+      schedule_fence();
+      if constexpr (h == 0) {
+#pragma unroll
+        for (int r = 0; r < R1; ++r) acc[r] = y[r];
+      } else {  // the odd half turned by the conjugate of w_M^n
+#pragma unroll
+        for (int r = 0; r < R1; ++r) {
+          const float2 q = a.tw[G::OFF_W + j + L * r];
+          acc[r] = make_float2(fmaf(q.y, y[r].y, fmaf(q.x, y[r].x, acc[r].x)),
+                               fmaf(-q.y, y[r].x, fmaf(q.x, y[r].y, acc[r].y)));
+        }
+      }
+    }
+  });
+  const int t = opaque_lane_row(tid), jv = t / TX;
+  const unsigned voff = static_cast<unsigned>((jv * M + kx0 + t % TX) * 8);
+#pragma unroll
+  for (int r = 0; r < R1; ++r) {
+    const int row = jv + L * r;
+    const unsigned off = (FULL || (row >= a.out_lo && row < a.out_hi)) ? voff : kNowhere;
+    buffer_store_c64(rs, off, L * r * M * 8, acc[r]);
+  }
+}
+
 // Shape of the column kernels: the split transforms where the length has them (radix plan 0),
 // else the staged form.
 template <int M, int PAD, int TX, int V>
 struct ColShape {
-  static constexpr bool SPLIT3 = V == 0 && ColSplit3<M, PAD>::BUILT;  // TX = 8
+  static constexpr bool SPLIT800 = V == 0 && ColSplit800<M, PAD>::BUILT;  // TX = 8
+  static constexpr bool SPLIT3 = V == 0 && ColSplit3<M, PAD>::BUILT;      // TX = 8
   static constexpr bool SPLIT = V == 0 && ColSplit<M, PAD>::BUILT;
-  static constexpr int THREADS =
-      SPLIT3 ? TX * ColSplit3<M, PAD>::L : SPLIT ? ColSplit<M, PAD>::threads(TX) : TX * Geo<M>::P;
-  static constexpr int SLOTS = SPLIT3  ? TX * ColSplit3<M, PAD>::REG
-                               : SPLIT ? PAD * TX * ColSplit<M, PAD>::region(TX)
-                                       : TX * Geo<M>::COL_REGION;
-  static constexpr int TABLE =
-      SPLIT3 ? ColSplit3<M, PAD>::COUNT : SPLIT ? ColSplit<M, PAD>::COUNT : twiddle_count<M, V>();
+  static constexpr int THREADS = SPLIT800  ? TX * ColSplit800<M, PAD>::L
+                                 : SPLIT3 ? TX * ColSplit3<M, PAD>::L
+                                 : SPLIT  ? ColSplit<M, PAD>::threads(TX)
+                                          : TX * Geo<M>::P;
+  static constexpr int SLOTS = SPLIT800  ? TX * ColSplit800<M, PAD>::REG
+                               : SPLIT3 ? TX * ColSplit3<M, PAD>::REG
+                               : SPLIT  ? PAD * TX * ColSplit<M, PAD>::region(TX)
+                                        : TX * Geo<M>::COL_REGION;
+  static constexpr int TABLE = SPLIT800  ? 1
+                               : SPLIT3 ? ColSplit3<M, PAD>::COUNT
+                               : SPLIT  ? ColSplit<M, PAD>::COUNT
+                                        : twiddle_count<M, V>();
   // wavefronts per SIMD the registers are held to: three blocks of eight wavefronts per CU for the
-  // halves of 512 points, else four
-  static constexpr int WAVES = SPLIT3 ? 6 : 4;
+  // halves of 512 points; three of four for those of 800, two where each frequency evaluates a
+  // transfer function of its own (60 bytes of spills at three mirrored, 480 unmirrored); else four
+  static constexpr int waves(int hm) { return SPLIT800 ? (hm == kHMirror || hm == kHTable ? 3 : 2) : SPLIT3 ? 6 : 4; }
 };
 
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V>
 __device__ __forceinline__ void col_any_body(const ColArgs& a, int bx, int by, float2* tile, float2* tw) {
-  if constexpr (ColShape<M, PAD, TX, V>::SPLIT3) col_split3_body<M, PAD, CONJ, HM, FULL>(a, bx, by, tile, tw);
+  if constexpr (ColShape<M, PAD, TX, V>::SPLIT800) col_split800_body<M, PAD, CONJ, HM, FULL>(a, bx, by, tile);
+  else if constexpr (ColShape<M, PAD, TX, V>::SPLIT3) col_split3_body<M, PAD, CONJ, HM, FULL>(a, bx, by, tile, tw);
   else if constexpr (ColShape<M, PAD, TX, V>::SPLIT) col_split_body<M, PAD, CONJ, TX, HM, FULL>(a, bx, by, tile, tw);
   else col_body<M, PAD, CONJ, TX, HM, FULL, V>(a, bx, by, tile, tw);
 }
 
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL, int V = 0>
-__global__ void __launch_bounds__((ColShape<M, PAD, TX, V>::THREADS)) __attribute__((amdgpu_waves_per_eu((ColShape<M, PAD, TX, V>::WAVES))))
+__global__ void __launch_bounds__((ColShape<M, PAD, TX, V>::THREADS)) __attribute__((amdgpu_waves_per_eu((ColShape<M, PAD, TX, V>::waves(HM)))))
 col_kernel(ColArgs a) {
   __shared__ float2 tile[ColShape<M, PAD, TX, V>::SLOTS];
   __shared__ float2 tw[ColShape<M, PAD, TX, V>::TABLE];
@@ -990,7 +1104,7 @@ col_kernel(ColArgs a) {
 // One launch of a column pass for several designs of the same transform length (see
 // row_group_kernel); every task starts at a multiple of 16 blocks.
 template <int M, int PAD, bool CONJ, int TX, int HM, bool FULL>
-__global__ void __launch_bounds__((ColShape<M, PAD, TX, 0>::THREADS)) __attribute__((amdgpu_waves_per_eu((ColShape<M, PAD, TX, 0>::WAVES))))
+__global__ void __launch_bounds__((ColShape<M, PAD, TX, 0>::THREADS)) __attribute__((amdgpu_waves_per_eu((ColShape<M, PAD, TX, 0>::waves(HM)))))
 col_group_kernel(GroupArgs g) {
   __shared__ float2 tile[ColShape<M, PAD, TX, 0>::SLOTS];
   __shared__ float2 tw[ColShape<M, PAD, TX, 0>::TABLE];
