@@ -27,7 +27,8 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 # the sources that define the pass kernels (their code, launch shapes and argument structs); a
 # traffic record taken on other versions of them no longer describes the kernel
 KERNEL_SOURCES = ["paper_2604_02624_amd/csrc/pass_kernels.hpp", "paper_2604_02624_amd/csrc/dpx_pass.hip",
-                  "paper_2604_02624_amd/csrc/fft.hpp", "paper_2604_02624_amd/csrc/phase.hpp",
+                  "paper_2604_02624_amd/csrc/fft.hpp", "paper_2604_02624_amd/csrc/col_fft.hpp",
+                  "paper_2604_02624_amd/csrc/phase.hpp",
                   "paper_2604_02624_amd/csrc/dpx_internal.hpp"]
 
 
