@@ -100,6 +100,18 @@ hipError_t col_launch(bool conj, const ColArgs& a, int w_count, hipStream_t s) {
   constexpr int THREADS = ColShape<M, PAD, TX, V>::THREADS;
   dim3 grid(M / TX, (w_count + a.col_wpb - 1) / a.col_wpb);
   const bool full = full_rows(a);
+  if constexpr (ColShape<M, PAD, TX, V>::SPLIT800) {
+    if (grid.x * grid.y <= 256) {  // see col800_few_kernel
+      if (conj) {
+        if (full) col800_few_kernel<M, PAD, true, HM, true><<<grid, 512, 0, s>>>(a);
+        else col800_few_kernel<M, PAD, true, HM, false><<<grid, 512, 0, s>>>(a);
+      } else {
+        if (full) col800_few_kernel<M, PAD, false, HM, true><<<grid, 512, 0, s>>>(a);
+        else col800_few_kernel<M, PAD, false, HM, false><<<grid, 512, 0, s>>>(a);
+      }
+      return hipGetLastError();
+    }
+  }
   if (conj) {
     if (full) col_kernel<M, PAD, true, TX, HM, true, V><<<grid, THREADS, 0, s>>>(a);
     else col_kernel<M, PAD, true, TX, HM, false, V><<<grid, THREADS, 0, s>>>(a);

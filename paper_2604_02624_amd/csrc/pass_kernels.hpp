@@ -951,6 +951,50 @@ __device__ __forceinline__ void col_split3_body(const ColArgs& a, int bx, int by
   }
 }
 
+// Frequencies of half h of a tile of halves of 800 points: the second phase, H and its inverse in place
+template <int M, int PAD, bool CONJ, int HM, int h>
+__device__ __forceinline__ void col800_freq(const ColArgs& a, const WlConst& c, int w, int kx0, float2* tile, int tid) {
+  using G = ColSplit800<M, PAD>;
+  constexpr int R1 = G::R1, R2 = G::R2;
+  const int t = opaque_lane_row(tid), k1 = t % 32, cb = t / 32;
+  if (k1 < R1) {
+    float2* const freq = tile + cb * G::REG + G::slot(k1, 0);
+    const float2* const tab = a.tw + h * 32 + k1;
+    float2 f[R2];
+    {
+      float2 p[R2 / 4], even[R2 / 2], odd[R2 / 2];
+#pragma unroll
+      for (int e = 0; e < R2 / 4; ++e) p[e] = tab[e * G::NH * 32];
+#pragma unroll
+      for (int i = 0; i < R2; ++i) (i % 2 ? odd : even)[i / 2] = freq[i];
+      dft_fused<R2 / 2, false>(even, p);
+      dft_fused<R2 / 2, false>(odd, p);
+      schedule_fence();  // the last level's factors take the registers of the others
+#pragma unroll
+      for (int k = 0; k < R2 / 4; ++k) p[k] = tab[(R2 / 4 + k) * G::NH * 32];
+      dft_fused_join<R2, false>(even, odd, p, f);
+    }
+    apply_transfer<M, PAD, CONJ, HM, h, R1, R2>(f, a, c, w, kx0 + cb, h, k1);
+    DFT<R2, true, false>::run(f);
+#pragma unroll
+    for (int i = 0; i < R2; ++i) freq[i] = f[i];
+  }
+}
+
+// The last phase: row j's 25 values of one half from the tile
+template <int M, int PAD>
+__device__ __forceinline__ void col800_rows(const ColArgs& a, const float2* own, int j, float2* y) {
+  using G = ColSplit800<M, PAD>;
+  constexpr int R1 = G::R1;
+#pragma unroll
+  for (int k = 0; k < R1; ++k) y[k] = own[G::slot(k, 0)];
+#pragma unroll
+  for (int k = 1; k < R1; ++k) y[k] = cmulc(y[k], a.tw[G::OFF_C + (k - 1) * 32 + j]);
+  schedule_fence();  // the factors of the odd half wait until the transform has let go of its own
+  DFT<R1, true, false>::run(y);
+  schedule_fence();
+}
+
 // The same for halves of 800 points (ColSplit800): eight columns on 256 threads.  Bound by issue
 // and by the registers: 25 inputs, 25 sums and 32 frequencies per lane hold it to 12 wavefronts per CU,
 // where the staged form ran 10 on twice the points.  128 wavelengths of the glass design's discs,
@@ -997,43 +1041,12 @@ __device__ __forceinline__ void col_split800_body(const ColArgs& a, int bx, int 
       for (int k = 0; k < R1; ++k) own[G::slot(k, 0)] = v[k];
     }
     __syncthreads();
-    {
-      const int t = opaque_lane_row(tid), k1 = t % 32, cb = t / 32;
-      if (k1 < R1) {
-        float2* const freq = tile + cb * G::REG + G::slot(k1, 0);
-        const float2* const tab = a.tw + h * 32 + k1;
-        float2 f[R2];
-        {
-          float2 p[R2 / 4], even[R2 / 2], odd[R2 / 2];
-#pragma unroll
-          for (int e = 0; e < R2 / 4; ++e) p[e] = tab[e * G::NH * 32];
-#pragma unroll
-          for (int i = 0; i < R2; ++i) (i % 2 ? odd : even)[i / 2] = freq[i];
-          dft_fused<R2 / 2, false>(even, p);
-          dft_fused<R2 / 2, false>(odd, p);
-          schedule_fence();  // the last level's factors take the registers of the others
-#pragma unroll
-          for (int k = 0; k < R2 / 4; ++k) p[k] = tab[(R2 / 4 + k) * G::NH * 32];
-          dft_fused_join<R2, false>(even, odd, p, f);
-        }
-        apply_transfer<M, PAD, CONJ, HM, h, R1, R2>(f, a, c, w, kx0 + cb, h, k1);
-        DFT<R2, true, false>::run(f);
-#pragma unroll
-        for (int i = 0; i < R2; ++i) freq[i] = f[i];
-      }
-    }
+    col800_freq<M, PAD, CONJ, HM, h>(a, c, w, kx0, tile, tid);
     __syncthreads();
     {
       float2 y[R1];
       const int t = opaque_lane_row(tid), j = t / TX;
-      const float2* const own = tile + t % TX * G::REG + j;
-#pragma unroll
-      for (int k = 0; k < R1; ++k) y[k] = own[G::slot(k, 0)];
-#pragma unroll
-      for (int k = 1; k < R1; ++k) y[k] = cmulc(y[k], a.tw[G::OFF_C + (k - 1) * 32 + j]);
-      schedule_fence();  // the factors of the odd half wait until the transform has let go of its own
-      DFT<R1, true, false>::run(y);
-      schedule_fence();
+      col800_rows<M, PAD>(a, tile + t % TX * G::REG + j, j, y);
       if constexpr (h == 0) {
 #pragma unroll
         for (int r = 0; r < R1; ++r) acc[r] = y[r];
@@ -1054,6 +1067,57 @@ __device__ __forceinline__ void col_split800_body(const ColArgs& a, int bx, int 
     const int row = jv + L * r;
     const unsigned off = (FULL || (row >= a.out_lo && row < a.out_hi)) ? voff : kNowhere;
     buffer_store_c64(rs, off, L * r * M * 8, acc[r]);
+  }
+}
+
+// Launches of at most a block per CU: the halves on different wavefronts, which halves the chain that
+// such a launch waits for; the sums are the same.  One wavelength, forward of two layers: 85.7 us with
+// the halves in turn, 77.6 here (78.4 staged); from two wavelengths on the other form is faster.
+template <int M, int PAD, bool CONJ, int HM, bool FULL>
+__global__ void __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) col800_few_kernel(ColArgs a) {
+  using G = ColSplit800<M, PAD>;
+  constexpr int N = M / PAD, TX = 8, R1 = G::R1, L = G::L, CUT = R1 / 2 + 1;
+  __shared__ float2 tiles[G::NH * TX * G::REG];
+  int bx, w;
+  col_block_item(static_cast<int>(blockIdx.x + gridDim.x * blockIdx.y), static_cast<int>(gridDim.x * gridDim.y),
+                 static_cast<int>(gridDim.x), bx, w);
+  const int tid = threadIdx.x % 256, half = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) / 256);
+  const int kx0 = bx * TX, j = tid / TX;
+  const WlConst c = load_uniform(a.wl + a.w_begin + w);
+  if ((kx0 < M / 2 ? kx0 : M - (kx0 + TX - 1)) > c.radius) return;  // as trim_evanescent
+  float2* const spec = a.spec + static_cast<size_t>(w) * N * M + kx0 + tid % TX;
+  float2* const tile = tiles + half * TX * G::REG;
+  float2* const own = tile + tid % TX * G::REG + j;  // slots of this thread alone in the row phases
+  float2 v[R1];
+#pragma unroll
+  for (int r = 0; r < R1; ++r) {
+    const int y = j + L * r;
+    v[r] = (FULL || (y >= a.in_lo && y < a.in_hi)) ? spec[static_cast<size_t>(y) * M] : make_float2(0.f, 0.f);
+  }
+  if (half) dft_odd<R1>(v);
+  else DFT<R1, false, false>::run(v);
+#pragma unroll
+  for (int k = 0; k < R1; ++k) own[G::slot(k, 0)] = v[k];
+  __syncthreads();
+  if (half) col800_freq<M, PAD, CONJ, HM, 1>(a, c, w, kx0, tile, tid);
+  else col800_freq<M, PAD, CONJ, HM, 0>(a, c, w, kx0, tile, tid);
+  __syncthreads();
+  col800_rows<M, PAD>(a, own, j, v);
+  // the even half's threads finish the first CUT rows, the odd half's the others
+#pragma unroll
+  for (int r = 0; r < R1; ++r)
+    if ((r < CUT) == (half == 1)) own[G::slot(r, 0)] = v[r];
+  __syncthreads();
+  const float2* const other = tiles + (1 - half) * TX * G::REG + tid % TX * G::REG + j;
+#pragma unroll
+  for (int r = 0; r < R1; ++r) {
+    const int row = j + L * r;
+    if ((r < CUT) == (half == 1)) continue;
+    const float2 o = other[G::slot(r, 0)], q = a.tw[G::OFF_W + row];
+    const float2 even = half ? o : v[r], odd = half ? v[r] : o;
+    if (FULL || (row >= a.out_lo && row < a.out_hi))
+      spec[static_cast<size_t>(row) * M] = make_float2(fmaf(q.y, odd.y, fmaf(q.x, odd.x, even.x)),
+                                                       fmaf(-q.y, odd.x, fmaf(q.x, odd.y, even.y)));
   }
 }
 
