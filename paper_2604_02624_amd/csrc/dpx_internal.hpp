@@ -286,7 +286,7 @@ hipError_t launch_col(int M, int pad, bool conj, int variant, int plan, const Co
 hipError_t launch_transfer_table(int M, const WlConst* wl, int W, double zrev, float2* out, hipStream_t s);
 hipError_t launch_bin_intensity(const float2* ofov, float* out, int w_count, int fov, int bin,
                                 hipStream_t s);
-// arrived / loss: null, or a zeroed count that the launch leaves zeroed and the design's loss: then
+// arrived / loss: null, or a count modulo W that every launch advances by W and the design's loss: then
 // the last block also sums the wavelengths (else launch_loss_sum does)
 hipError_t launch_loss(const float* I, const float* tau, float* dl_di, double* per_wl, int W, int T,
                        unsigned* arrived, double* loss, hipStream_t s);

@@ -172,7 +172,9 @@ __device__ __forceinline__ void loss_sum_body(const double* __restrict__ per_wl,
 }
 
 // arrived: null, or the design's count of finished blocks; then the block that finishes last also
-// sums the wavelengths' losses (and returns the count to zero), which saves the launch that would.
+// sums the wavelengths' losses, which saves the launch that would.  The count wraps to zero by itself
+// after W blocks, so that calls which overlap on several streams leave it at zero too: every call
+// adds W to a count modulo W.
 template <int THREADS>
 __global__ void __launch_bounds__(THREADS)
 loss_kernel(const float* __restrict__ I, const float* __restrict__ tau, float* __restrict__ dl_di,
@@ -183,12 +185,11 @@ loss_kernel(const float* __restrict__ I, const float* __restrict__ tau, float* _
   if (!arrived) return;
   if (threadIdx.x == 0) {
     __threadfence();  // per_wl[w] before the count, for the block on another XCD that reads it
-    last = atomicAdd(arrived, 1u) == static_cast<unsigned>(W) - 1u;
+    last = atomicInc(arrived, static_cast<unsigned>(W) - 1u) == static_cast<unsigned>(W) - 1u;
   }
   __syncthreads();
   if (!last) return;
   __threadfence();
-  if (threadIdx.x == 0) *arrived = 0;
   loss_sum_body<THREADS>(per_wl, loss, W, sh);
 }
 
