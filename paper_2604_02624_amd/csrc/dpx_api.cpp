@@ -402,6 +402,12 @@ dpx_status check_ptr(const void* p, size_t align, const char* name) {
   return DPX_OK;
 }
 
+// whether two device arrays share an address
+bool overlap(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return a && b && x < y + static_cast<uintptr_t>(b_bytes) && y < x + static_cast<uintptr_t>(a_bytes);
+}
+
 dpx_status sticky_check() {
   hipError_t e = hipPeekAtLastError();
   if (e != hipSuccess) {
@@ -1839,13 +1845,21 @@ dpx_status dpx_backward(dpx_plan* p, const float* h, const float* u_in, const fl
                 "store-mode backward needs a preceding dpx_forward on this plan with the same h and "
                 "u_in");
   hipStream_t caller = static_cast<hipStream_t>(stream);
+  // With one gradient slot the passes write dL/dh themselves (direct), layer by layer while they still
+  // read the inputs; a caller who puts it in place of an input gets it from the slot at the end.
+  int64_t u_total = 0;
+  for (const auto& d : p->designs) u_total += static_cast<int64_t>(d.N) * d.N;
+  float* const direct = overlap(dl_dh, p->h_total * 4, h, p->h_total * 4) ||
+                                overlap(dl_dh, p->h_total * 4, u_in, u_total * 8) ||
+                                overlap(dl_dh, p->h_total * 4, dl_di, p->img_total * 4)
+                            ? nullptr : dl_dh;
   auto enqueue = [&](hipStream_t s0) -> dpx_status {
     if (p->grouped)
       return run_group_parts(p, p->g_bwd, {h, reinterpret_cast<const float2*>(u_in), dl_di}, dl_dh, s0);
     return for_each_design(p, s0, [&](const Design& d, int, hipStream_t s) -> dpx_status {
       if (lds_now(d)) {
-        DPX_TRY(run_lds(p, d, true, h, u_in, nullptr, dl_di, dl_dh, s));
-        if (d.W == 1) return DPX_OK;  // one slot: the launch wrote dl_dh
+        DPX_TRY(run_lds(p, d, true, h, u_in, nullptr, dl_di, direct, s));
+        if (d.W == 1 && direct) return DPX_OK;  // one slot: the launch wrote dl_dh
         hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.W,
                                              static_cast<int64_t>(d.K) * d.N * d.N, s);
         if (e != hipSuccess) return fail(DPX_E_DEVICE, "gradient reduction launch failed: %s", hipGetErrorString(e));
@@ -1875,11 +1889,11 @@ dpx_status dpx_backward(dpx_plan* p, const float* h, const float* u_in, const fl
             if (e != hipSuccess) return fail(DPX_E_DEVICE, "slot clearing launch failed: %s", hipGetErrorString(e));
           }
         }
-        DPX_TRY(adjoint_chunk(p, d, h, u_in, dl_di, d.nslots == 1 ? dl_dh : nullptr, w0, wc, lane, c >= d.lanes, ls,
+        DPX_TRY(adjoint_chunk(p, d, h, u_in, dl_di, d.nslots == 1 ? direct : nullptr, w0, wc, lane, c >= d.lanes, ls,
                               first_ev));
       }
       DPX_TRY(join_lanes(p, d, s));
-      if (d.nslots == 1) return DPX_OK;  // the row passes wrote dl_dh
+      if (d.nslots == 1 && direct) return DPX_OK;  // the row passes wrote dl_dh
       const int64_t per = static_cast<int64_t>(d.K) * d.N * d.N;
       hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.nslots, per, s);
       if (e != hipSuccess) return fail(DPX_E_DEVICE, "gradient reduction launch failed: %s", hipGetErrorString(e));
