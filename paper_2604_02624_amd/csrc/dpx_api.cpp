@@ -120,6 +120,7 @@ struct GroupLaunch {
   bool conj = false;
   bool table = false;      // column launches: the tasks read transfer tables
   bool full = false;       // column launches: every task reads and keeps all aperture rows
+  bool large = false;      // loss launches: images of large_image
   dpx::GroupArgs g{};
   int pass = -1;           // DPX_PASS_* of row / column launches (timers)
   int64_t bytes = 0;       // algorithmic bytes (without the input field)
@@ -981,14 +982,20 @@ dpx_status build_groups(dpx_plan* p) {
       if ((p->design_stream.empty() ? 0 : p->design_stream[i]) == k) ids.push_back(i);
     if (!ids.empty()) build_group_lists(p, ids, p->g_fwd[k], p->g_bwd[k], blob);
   }
-  // loss: the task array in design order doubles as the table of the per-design sums
-  std::vector<dpx::LossTask> losses;
-  std::vector<int> lnb;
+  // loss: one launch for small and one for large images (large_image); the task array in design order
+  // is the table of the per-design sums
+  std::vector<dpx::LossTask> losses, by_size[2];
+  std::vector<int> lnb[2];
   for (const auto& d : p->designs) {
     losses.push_back({d.img_off, d.per_wl, d.W, d.T});
-    lnb.push_back(d.W);
+    by_size[dpx::large_image(d.T)].push_back(losses.back());
+    lnb[dpx::large_image(d.T)].push_back(d.W);
   }
-  add_simple_group(p->g_loss, GK_LOSS, losses, lnb, blob);
+  for (int large = 0; large < 2; ++large) {
+    const size_t first = p->g_loss.size();
+    add_simple_group(p->g_loss, GK_LOSS, by_size[large], lnb[large], blob);
+    for (size_t i = first; i < p->g_loss.size(); ++i) p->g_loss[i].large = large != 0;
+  }
   const size_t loss_table = blob.put(losses.data(), losses.size() * sizeof(dpx::LossTask));
   if (blob.too_many_blocks)
     return fail(DPX_E_UNSUPPORTED, "a grouped launch would exceed the grid limit; use schedule 1");
@@ -1804,7 +1811,7 @@ dpx_status dpx_loss(dpx_plan* p, const float* intensity, const float* target, do
   auto enqueue = [&](hipStream_t s0) -> dpx_status {
     if (p->grouped) {
       for (const auto& L : p->g_loss) {
-        hipError_t e = dpx::launch_loss_group(L.g, intensity, target, dl_di, s0);
+        hipError_t e = dpx::launch_loss_group(L.g, L.large, intensity, target, dl_di, s0);
         if (e != hipSuccess) return fail(DPX_E_DEVICE, "loss launch failed: %s", hipGetErrorString(e));
       }
       hipError_t e = dpx::launch_loss_sum_group(p->d_loss_tasks, static_cast<int>(p->designs.size()), loss, s0);

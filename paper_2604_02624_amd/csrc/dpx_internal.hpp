@@ -202,6 +202,11 @@ struct BinTask {
   int w_count, fov, bin;
 };
 
+// Images of more than 8192 pixels take a block of 1024 threads in the loss and the PSNR (else 256; 512 x
+// 512 pixels, one wavelength: 363 -> 85 us).  The order of the sums, and so the last bits, follows from
+// this, so every schedule decides by it.
+constexpr bool large_image(int T) { return T * T > 8192; }
+
 struct LossTask {
   int64_t img_off;           // offset of the design's images in the packed buffers
   double* per_wl;            // [W] per-wavelength loss of the design
@@ -258,7 +263,8 @@ hipError_t launch_row_group(int M, int pad, int mode, const GroupArgs& g, hipStr
 hipError_t launch_col_group(int M, int pad, bool conj, int variant, bool table, bool full, const GroupArgs& g,
                             hipStream_t s);
 hipError_t launch_bin_group(const GroupArgs& g, float* out, hipStream_t s);
-hipError_t launch_loss_group(const GroupArgs& g, const float* I, const float* tau, float* dl_di,
+// large: every task's images are large_image, else none's
+hipError_t launch_loss_group(const GroupArgs& g, bool large, const float* I, const float* tau, float* dl_di,
                              hipStream_t s);
 hipError_t launch_loss_sum_group(const LossTask* tasks, int ntasks, double* loss, hipStream_t s);
 hipError_t launch_dh_group(const GroupArgs& g, float* dl_dh, hipStream_t s);

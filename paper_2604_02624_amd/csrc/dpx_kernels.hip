@@ -30,7 +30,7 @@ __global__ void bin_group_kernel(GroupArgs g, float* __restrict__ out) {
 }
 
 constexpr int kLossThreads = 256;
-constexpr int kLossThreadsLarge = 1024;  // images of more than 8192 pixels, one design per launch
+constexpr int kLossThreadsLarge = 1024;  // large_image
 constexpr int kLossCache = 16;           // pixels a thread keeps in registers
 
 // v plus its neighbour's value under the DPP control CTRL (0 where there is none)
@@ -193,16 +193,17 @@ loss_kernel(const float* __restrict__ I, const float* __restrict__ tau, float* _
   loss_sum_body<THREADS>(per_wl, loss, W, sh);
 }
 
-// grouped: task = one design, one block per wavelength of every design
-__global__ void __launch_bounds__(kLossThreads)
+// grouped: task = one design, one block per wavelength of every design; the designs of a launch have
+// images of one size class, since the order of the sums goes with the block's size
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS)
 loss_group_kernel(GroupArgs g, const float* __restrict__ I, const float* __restrict__ tau,
                   float* __restrict__ dl_di) {
-  __shared__ double sh[4 * (kLossThreads / 64)];
+  __shared__ double sh[4 * (THREADS / 64)];
   const int ti = group_task(g, blockIdx.x);
   const LossTask& t = static_cast<const LossTask*>(g.tasks)[ti];
   const int w = static_cast<int>(blockIdx.x) - g.block0[ti];
-  loss_body<kLossThreads>(I + t.img_off, tau + t.img_off, dl_di ? dl_di + t.img_off : nullptr, t.per_wl, t.W, t.T, w,
-                          sh);
+  loss_body<THREADS>(I + t.img_off, tau + t.img_off, dl_di ? dl_di + t.img_off : nullptr, t.per_wl, t.W, t.T, w, sh);
 }
 
 __global__ void __launch_bounds__(kLossThreads)
@@ -693,11 +694,9 @@ hipError_t launch_bin_intensity(const float2* ofov, float* out, int w_count, int
   return hipGetLastError();
 }
 
-constexpr int kLargeImage = 8192;  // pixels beyond which an image takes a block of 1024 threads
-
 hipError_t launch_loss(const float* I, const float* tau, float* dl_di, double* per_wl, int W, int T,
                        unsigned* arrived, double* loss, hipStream_t s) {
-  if (T * T > kLargeImage)
+  if (large_image(T))
     loss_kernel<kLossThreadsLarge><<<W, kLossThreadsLarge, 0, s>>>(I, tau, dl_di, per_wl, W, T, arrived, loss);
   else
     loss_kernel<kLossThreads><<<W, kLossThreads, 0, s>>>(I, tau, dl_di, per_wl, W, T, arrived, loss);
@@ -726,10 +725,11 @@ hipError_t launch_bin_group(const GroupArgs& g, float* out, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_loss_group(const GroupArgs& g, const float* I, const float* tau, float* dl_di,
+hipError_t launch_loss_group(const GroupArgs& g, bool large, const float* I, const float* tau, float* dl_di,
                              hipStream_t s) {
   if (g.ntasks < 1 || g.ntasks > kMaxGroupTasks) return hipErrorInvalidValue;
-  loss_group_kernel<<<group_grid(g), kLossThreads, 0, s>>>(g, I, tau, dl_di);
+  if (large) loss_group_kernel<kLossThreadsLarge><<<group_grid(g), kLossThreadsLarge, 0, s>>>(g, I, tau, dl_di);
+  else loss_group_kernel<kLossThreads><<<group_grid(g), kLossThreads, 0, s>>>(g, I, tau, dl_di);
   return hipGetLastError();
 }
 
@@ -763,7 +763,7 @@ hipError_t launch_adam_sigmoid(float* theta, float* h, const float* dl_dh, float
 
 hipError_t launch_psnr(const float* I, const float* tau, double* out, int W, int T, hipStream_t s) {
   if (W <= 0) return hipSuccess;
-  if (T * T > kLargeImage) psnr_kernel<kLossThreadsLarge><<<W, kLossThreadsLarge, 0, s>>>(I, tau, out, T);
+  if (large_image(T)) psnr_kernel<kLossThreadsLarge><<<W, kLossThreadsLarge, 0, s>>>(I, tau, out, T);
   else psnr_kernel<kLossThreads><<<W, kLossThreads, 0, s>>>(I, tau, out, T);
   return hipGetLastError();
 }
