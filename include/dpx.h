@@ -174,8 +174,8 @@ typedef struct dpx_opts {
                                store mode, per-design schedule, one stream, no forced column
                                variant and no transfer tables, each wavelength's plane stays in
                                LDS and the forward (with the binning) and the adjoint (with the
-                               dL/dh partials, one slot per wavelength) are one launch each.  Same
-                               bits either way (dL/dh to rounding: its slots differ).
+                               dL/dh partials, in the slots of the multi-pass kernels) are one
+                               launch each.  Same bits either way.
                                0 = automatic: that path for a plan of one design without other
                                requests (schedule, wl_chunk, autotune, variants, radix plans,
                                tables, band limit, input gap) where it is the faster one on

@@ -252,10 +252,8 @@ dpx_status validate(const dpx_design* ds, int32_t nd, const dpx_opts* o) {
   return DPX_OK;
 }
 
-// slabs of checkpoints and slots of gradient partials a design holds: the LDS-resident kernels store
-// every layer's field and take one slot per wavelength
+// slabs of checkpoints a design holds: the LDS-resident kernels store every layer's field
 int ckpt_slabs(const Design& d) { return d.lds_auto ? d.K : d.K - d.ck_first; }
-int gradient_slots(const Design& d) { return d.lds_auto ? std::max(d.nslots, d.W) : d.nslots; }
 // whether the next calls run the design LDS-resident
 bool lds_now(const Design& d) { return d.lds || (d.lds_auto && !d.misaligned); }
 
@@ -288,20 +286,22 @@ void layout_design(const dpx_design& src, const dpx_opts& o, bool single, Design
   if (lanes_wanted == 1 && o.wl_chunk <= 0 && o.checkpoint_mode == 0) chunk = d.W;
   chunk = std::max(1, std::min(chunk, d.W));
   // wavelengths per row-pass block: enough blocks to fill the chip (about 2048), at most 16
-  int wpb = static_cast<int>(std::max<int64_t>(1, static_cast<int64_t>(chunk) * row_blocks / 2048));
-  wpb = std::min(wpb, 16);
+  auto wavelengths_per_block = [&](int w) {
+    return static_cast<int>(std::min<int64_t>(16, std::max<int64_t>(1, static_cast<int64_t>(w) * row_blocks / 2048)));
+  };
+  int wpb = wavelengths_per_block(chunk);
   if (chunk < d.W) {
     // chunks must hold whole blocks so every chunk maps onto the same partial slots
     chunk = std::max(wpb, chunk / wpb * wpb);
   }
-  // LDS-resident path for short transforms (opts.small_path = 1): every wavelength is one
-  // block with one dL/dh slot, the whole design one chunk
+  // LDS-resident path for short transforms (opts.small_path = 1): the whole design is one chunk, every
+  // wavelength (forward) or dL/dh slot (adjoint) one block
   d.lds = o.small_path == 1 && o.checkpoint_mode == 0 && o.streams <= 1 && o.force_variant < 0 &&
           src.z_in == 0.0 && src.band_limited == 0 &&
           o.transfer_table != 2 && dpx::lds_path_supported(d.M, d.pad);
   if (d.lds) {
     chunk = d.W;
-    wpb = 1;
+    wpb = wavelengths_per_block(d.W);
   }
   // and where it is the faster one and nothing asks for a form that only the passes have.  The plan
   // then has room for both: a misalignment, which the LDS-resident kernels cannot apply, sends the
@@ -345,7 +345,7 @@ void layout_design(const dpx_design& src, const dpx_opts& o, bool single, Design
   d.bytes = static_cast<int64_t>(d.lanes) * d.wl_chunk * d.N * d.M * 8  // spec
             + static_cast<int64_t>(ckpt_slabs(d)) * ck_w * nn * 8  // checkpoints
             + static_cast<int64_t>(of_w) * d.F * d.F * 8      // output field
-            + static_cast<int64_t>(gradient_slots(d)) * d.K * nn * 4   // dL/dh partials
+            + static_cast<int64_t>(d.nslots) * d.K * nn * 4   // dL/dh partials
             + static_cast<int64_t>(d.W) * 8                   // per-wavelength loss
             + static_cast<int64_t>(d.W) * sizeof(WlConst)
             + static_cast<int64_t>(d.K) * 8;                  // gap table
@@ -1056,11 +1056,12 @@ dpx_status run_lds(dpx_plan* p, const Design& d, bool adjoint, const float* h, c
   a.ofov = d.ofov;
   a.intensity = intensity ? intensity + d.img_off : nullptr;
   a.dl_di = dl_di ? dl_di + d.img_off : nullptr;
-  a.dh_part = d.W == 1 && dl_dh ? dl_dh + d.h_off : d.dh_part;
+  a.dh_part = d.nslots == 1 && dl_dh ? dl_dh + d.h_off : d.dh_part;
   a.K = d.K;
   a.fov = d.F;
   a.bin = d.b;
   a.W = d.W;
+  a.w_per_block = d.w_per_block;
   // algorithmic work: every pass of the multi-kernel path, without its spectrum traffic
   double flops = 0.0;
   int64_t bytes = static_cast<int64_t>(d.K) * d.N * d.N * 4 + (u_in ? 8LL * d.N * d.N : 0);
@@ -1072,7 +1073,8 @@ dpx_status run_lds(dpx_plan* p, const Design& d, bool adjoint, const float* h, c
   } else {
     flops += row_flops(d, dpx::ROW_ADJ_SEED, d.W, d.F) + (d.K - 1) * row_flops(d, dpx::ROW_ADJ_MID, d.W, d.N) +
              row_flops(d, dpx::ROW_ADJ_LAST, d.W, d.N) + d.K * col_flops(d, d.W);
-    bytes += static_cast<int64_t>(d.W) * (d.K * nn * 8 + d.F * d.F * 8 + d.T * d.T * 4 + d.K * nn * 4);
+    bytes += static_cast<int64_t>(d.W) * (d.K * nn * 8 + d.F * d.F * 8 + d.T * d.T * 4) +
+             static_cast<int64_t>(d.nslots) * d.K * nn * 4;
   }
   TimedLaunch t{adjoint ? DPX_PASS_LDS_ADJ : DPX_PASS_LDS_FWD, nullptr, nullptr, bytes, flops};
   DPX_TRY(timer_begin(p, s, t));
@@ -1483,7 +1485,7 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
     if ((st = dev_alloc(&d.spec, static_cast<int64_t>(d.lanes) * d.wl_chunk * d.N * d.M * 8, "spectra")) != DPX_OK) break;
     if ((st = dev_alloc(&d.ckpt, static_cast<int64_t>(ckpt_slabs(d)) * ck_w * nn * 8, "checkpoints")) != DPX_OK) break;
     if ((st = dev_alloc(&d.ofov, static_cast<int64_t>(ck_w) * d.F * d.F * 8, "output field")) != DPX_OK) break;
-    if ((st = dev_alloc(&d.dh_part, static_cast<int64_t>(gradient_slots(d)) * d.K * nn * 4, "gradient partials")) != DPX_OK) break;
+    if ((st = dev_alloc(&d.dh_part, static_cast<int64_t>(d.nslots) * d.K * nn * 4, "gradient partials")) != DPX_OK) break;
     if ((st = dev_alloc(&d.per_wl, d.W * 8, "per-wavelength loss")) != DPX_OK) break;
     if ((st = dev_alloc(&d.htab, d.table_bytes, "transfer tables")) != DPX_OK) break;
     if ((st = dev_alloc(&d.d_zrev, static_cast<int64_t>(d.K) * 8, "gap table")) != DPX_OK) break;
@@ -1866,8 +1868,8 @@ dpx_status dpx_backward(dpx_plan* p, const float* h, const float* u_in, const fl
     return for_each_design(p, s0, [&](const Design& d, int, hipStream_t s) -> dpx_status {
       if (lds_now(d)) {
         DPX_TRY(run_lds(p, d, true, h, u_in, nullptr, dl_di, direct, s));
-        if (d.W == 1 && direct) return DPX_OK;  // one slot: the launch wrote dl_dh
-        hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.W,
+        if (d.nslots == 1 && direct) return DPX_OK;  // one slot: the launch wrote dl_dh
+        hipError_t e = dpx::launch_dh_reduce(d.dh_part, dl_dh + d.h_off, d.nslots,
                                              static_cast<int64_t>(d.K) * d.N * d.N, s);
         if (e != hipSuccess) return fail(DPX_E_DEVICE, "gradient reduction launch failed: %s", hipGetErrorString(e));
         return DPX_OK;

@@ -123,8 +123,9 @@ struct LdsArgs {
   float2* ofov;              // [W][F][F] output field on the field of view
   float* intensity;          // [W][T][T] (forward)
   const float* dl_di;        // [W][T][T] (adjoint)
-  float* dh_part;            // [W][K][N][N] dL/dh of each wavelength (adjoint)
+  float* dh_part;            // [slots][K][N][N] dL/dh of each run of w_per_block wavelengths (adjoint)
   int K, fov, bin, W;
+  int w_per_block;           // as in RowArgs: the slots, and so the bits of dL/dh, are the row passes'
 };
 
 // Sum of |o|^2 over the b x b bin at o (row stride `stride`), fused multiply-adds in a fixed order

@@ -301,8 +301,10 @@ hipError_t DPX_NAME(launch_lds_)(int pad, bool adjoint, const LdsArgs& a, hipStr
     auto go = [&](auto padc) -> hipError_t {
       constexpr int PD = decltype(padc)::value;
       if constexpr (LdsGeo<M, PD>::FITS) {
-        if (adjoint)
-          lds_adjoint_kernel<M, PD><<<a.W, kLdsThreads, 0, s>>>(a);
+        if (adjoint && a.w_per_block > 1)
+          lds_adjoint_kernel<M, PD, true><<<(a.W + a.w_per_block - 1) / a.w_per_block, kLdsThreads, 0, s>>>(a);
+        else if (adjoint)
+          lds_adjoint_kernel<M, PD, false><<<a.W, kLdsThreads, 0, s>>>(a);
         else
           lds_forward_kernel<M, PD><<<a.W, kLdsThreads, 0, s>>>(a);
         return hipGetLastError();

@@ -1387,14 +1387,14 @@ __device__ __forceinline__ void lds_rows_forward(const LdsArgs& a, const WlConst
 // follow each other.
 template <int M, int PAD, bool CONJ>
 __device__ __forceinline__ void lds_columns(const WlConst& c, const ColArgs& ca, int in_lo, int in_hi,
-                                            float2* plane, const float2* tab) {
+                                            float2* plane, const float2* tab, int tid) {
   using G = LdsGeo<M, PAD>;
   using S = ColSplit<M, PAD>;
   constexpr int R1 = S::R1, R2 = S::R2, L = S::L, RS = G::RS;
   constexpr int GL = pow2_at_least(L > S::GP ? L : S::GP);
   constexpr int CB = kLdsThreads / GL;
-  const int lane = threadIdx.x % GL;
-  for (int kx = threadIdx.x / GL; kx < M; kx += CB) {
+  const int lane = tid % GL;
+  for (int kx = tid / GL; kx < M; kx += CB) {
     float2* col = plane + kx;
     const bool rows = lane < L, freq = lane < R1;
     float2 x[R1], b[S::NH][R1];
@@ -1468,7 +1468,7 @@ __global__ void __launch_bounds__(kLdsThreads) lds_forward_kernel(LdsArgs a) {
   __syncthreads();
   for (int l = 0; l < a.K; ++l) {
     gap.zrev = a.zrev[l];
-    lds_columns<M, PAD, false>(c, gap, 0, N, plane, tab);
+    lds_columns<M, PAD, false>(c, gap, 0, N, plane, tab, threadIdx.x);
     __syncthreads();
     if (l + 1 < a.K) {
       lds_rows_forward<M, PAD, false>(a, c, w, l + 1, plane, tw);
@@ -1501,8 +1501,12 @@ __global__ void __launch_bounds__(kLdsThreads) lds_forward_kernel(LdsArgs a) {
         bin_sum(plane + (x0 + i / T * a.bin) * G::RS + x0 + i % T * a.bin, G::RS, a.bin);
 }
 
-template <int M, int PAD>
-__global__ void __launch_bounds__(kLdsThreads) lds_adjoint_kernel(LdsArgs a) {
+// RUNS: a gradient slot holds several wavelengths, which a block takes in turn and adds in the order of
+// the row passes (else w_per_block is 1).  Four wavefronts per SIMD where the LDS has room for two blocks.
+template <int M, int PAD, bool RUNS>
+__global__ void __launch_bounds__(kLdsThreads)
+__attribute__((amdgpu_waves_per_eu(2 * LdsGeo<M, PAD>::LDS_BYTES <= 160 * 1024 ? 4 : 2)))
+lds_adjoint_kernel(LdsArgs a) {
   using G = LdsGeo<M, PAD>;
   constexpr int E = Geo<M>::E, P = G::P, N = G::N, EN = E / PAD;
   constexpr bool HALF = (PAD == 2);
@@ -1513,64 +1517,70 @@ __global__ void __launch_bounds__(kLdsThreads) lds_adjoint_kernel(LdsArgs a) {
   for (int i = threadIdx.x; i < G::TABLE; i += kLdsThreads) tab[i] = a.col_tab[i];
   __syncthreads();
   ColArgs gap{};  // what the transfer function of a column needs
-  const int w = blockIdx.x;
-  const WlConst c = a.wl[w];
   const int F = a.fov, b = a.bin, T = F / b, x0 = (N - F) / 2;
-  const int g = threadIdx.x / P, j0 = threadIdx.x % P;
   const size_t nn = static_cast<size_t>(N) * N;
-  // seed 2 (dL/dI) o on the window rows, forward row transform
-  for (int y = x0 + g; y < x0 + F; y += G::RB) {
-    float2* row = plane + y * G::RS;
-    const float2* o = a.ofov + static_cast<size_t>(w) * F * F + static_cast<size_t>(y - x0) * F;
-    const float* d = a.dl_di + static_cast<size_t>(w) * T * T + static_cast<size_t>((y - x0) / b) * T;
-    float2 reg[E];
-#pragma unroll
-    for (int t = 0; t < EN; ++t) {
-      const int x = j0 + P * t;
-      if (x >= x0 && x < x0 + F) {
-        const float s = 2.0f * d[(x - x0) / b];
-        reg[t] = cscale(o[x - x0], s);
-      } else {
-        reg[t] = make_float2(0.f, 0.f);
-      }
-    }
-    fft<M, false, HALF>(reg, row, j0, tw);
-#pragma unroll
-    for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
-  }
-  __syncthreads();
-  const float ct = c.ct, ca = static_cast<float>(c.ca);
-  for (int l = a.K - 1; l >= 0; --l) {
-    gap.zrev = a.zrev[l];
-    lds_columns<M, PAD, true>(c, gap, l == a.K - 1 ? x0 : 0, l == a.K - 1 ? x0 + F : N, plane, tab);
-    __syncthreads();
-    for (int y = g; y < N; y += G::RB) {
+  const int wb = blockIdx.x * (RUNS ? a.w_per_block : 1), we = RUNS ? min(wb + a.w_per_block, a.W) : wb + 1;
+  int w = wb;
+  do {
+    // opaque per wavelength (as in opaque_lane_row): what is the same for each of them would otherwise
+    // stay live across the loop (128 points: 166 registers against 116)
+    const int tid = RUNS ? opaque_lane_row(threadIdx.x) & (kLdsThreads - 1) : threadIdx.x;
+    const int g = tid / P, j0 = tid % P;
+    const WlConst c = a.wl[w];
+    // seed 2 (dL/dI) o on the window rows, forward row transform
+    for (int y = x0 + g; y < x0 + F; y += G::RB) {
       float2* row = plane + y * G::RS;
-      const float* hrow = a.h + (static_cast<size_t>(l) * N + y) * N;
-      const float2* ck = a.ckpt + (static_cast<size_t>(l) * a.W + w) * nn + static_cast<size_t>(y) * N;
+      const float2* o = a.ofov + static_cast<size_t>(w) * F * F + static_cast<size_t>(y - x0) * F;
+      const float* d = a.dl_di + static_cast<size_t>(w) * T * T + static_cast<size_t>((y - x0) / b) * T;
       float2 reg[E];
 #pragma unroll
-      for (int t = 0; t < E; ++t) reg[t] = row[j0 + P * t];
-      fft<M, true, false>(reg, row, j0, tw);
-      float* dst = a.dh_part + (static_cast<size_t>(w) * a.K + l) * nn + static_cast<size_t>(y) * N;
-#pragma unroll
       for (int t = 0; t < EN; ++t) {
-        const float2 gv = reg[t];
-        const float2 v = ck[j0 + P * t];
-        // conj(g) v; -ct Im - ca Re
-        const float re = fmaf(gv.x, v.x, gv.y * v.y);
-        const float im = fmaf(gv.x, v.y, -(gv.y * v.x));
-        dst[j0 + P * t] = fmaf(-ct, im, fmaf(-ca, re, 0.f));
-        if (l > 0) reg[t] = cmulc(gv, transmission(hrow[j0 + P * t], c));
+        const int x = j0 + P * t;
+        if (x >= x0 && x < x0 + F) {
+          const float s = 2.0f * d[(x - x0) / b];
+          reg[t] = cscale(o[x - x0], s);
+        } else {
+          reg[t] = make_float2(0.f, 0.f);
+        }
       }
-      if (l > 0) {
-        fft<M, false, HALF>(reg, row, j0, tw);
+      fft<M, false, HALF>(reg, row, j0, tw);
 #pragma unroll
-        for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
-      }
+      for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
     }
     __syncthreads();
-  }
+    const float ct = c.ct, ca = static_cast<float>(c.ca);
+    for (int l = a.K - 1; l >= 0; --l) {
+      gap.zrev = a.zrev[l];
+      lds_columns<M, PAD, true>(c, gap, l == a.K - 1 ? x0 : 0, l == a.K - 1 ? x0 + F : N, plane, tab, tid);
+      __syncthreads();
+      for (int y = g; y < N; y += G::RB) {
+        float2* row = plane + y * G::RS;
+        const float* hrow = a.h + (static_cast<size_t>(l) * N + y) * N;
+        const float2* ck = a.ckpt + (static_cast<size_t>(l) * a.W + w) * nn + static_cast<size_t>(y) * N;
+        float* dst = a.dh_part + (static_cast<size_t>(blockIdx.x) * a.K + l) * nn + static_cast<size_t>(y) * N;
+        float2 reg[E];
+#pragma unroll
+        for (int t = 0; t < E; ++t) reg[t] = row[j0 + P * t];
+        fft<M, true, false>(reg, row, j0, tw);
+#pragma unroll
+        for (int t = 0; t < EN; ++t) {
+          const float2 gv = reg[t];
+          const float2 v = ck[j0 + P * t];
+          // conj(g) v; acc += -ct Im - ca Re
+          const float re = fmaf(gv.x, v.x, gv.y * v.y);
+          const float im = fmaf(gv.x, v.y, -(gv.y * v.x));
+          dst[j0 + P * t] = fmaf(-ct, im, fmaf(-ca, re, RUNS && w > wb ? dst[j0 + P * t] : 0.f));
+          if (l > 0) reg[t] = cmulc(gv, transmission(hrow[j0 + P * t], c));
+        }
+        if (l > 0) {
+          fft<M, false, HALF>(reg, row, j0, tw);
+#pragma unroll
+          for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
+        }
+      }
+      __syncthreads();
+    }
+  } while (RUNS && ++w < we);
 }
 
 }  // namespace dpx

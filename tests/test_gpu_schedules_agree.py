@@ -48,3 +48,16 @@ def test_grouped_and_per_design_losses(torch_dev, fovs, n_wl):
     assert (kind2[0], kind1[0]) == (2, 1)
     for a, b in zip(grouped, single):
         assert np.array_equal(a, b)
+
+
+# plans that run LDS-resident by themselves or on request against the passes: slots of one
+# wavelength, and of several with a short last one
+@pytest.mark.parametrize("n,pad,n_wl,small", [(32, 2, 2048, 0), (64, 2, 300, 0), (64, 2, 4096, 0), (64, 2, 9001, 0), (64, 1, 4099, 0),
+                                              (64, 1, 6500, 0), (32, 2, 4500, 1), (48, 2, 6145, 1), (96, 1, 2500, 1)])
+def test_lds_resident_plans_and_passes(torch_dev, n, pad, n_wl, small):
+    d = design(n, pad, n_wl, 2, n // 2)
+    lds, kind = results(torch_dev, [d], n_wl, small_path=small)
+    passes, kind1 = results(torch_dev, [d], n_wl, schedule=1)
+    assert (kind[1], kind1) == (True, (1, False))
+    for a, b in zip(lds, passes):
+        assert np.array_equal(a, b)
