@@ -114,8 +114,8 @@ typedef struct dpx_opts {
   int32_t checkpoint_mode;  /* 0: forward stores the field after every transmission
                                ((K-1)*W*N*N complex per design, K*W*N*N with an input gap
                                z_in > 0: without one, the field after the first layer is
-                               u_in t_0(h), which the backward rebuilds from u_in and h) for
-                               the backward;
+                               u_in t_0(h), which the backward rebuilds from u_in and h;
+                               LDS-resident plans store it too) for the backward;
                                1: backward recomputes the forward chunk by chunk */
   int32_t wl_chunk;         /* wavelengths per chunk (0 = automatic) */
   int32_t use_graph;        /* nonzero: the first dpx_forward / dpx_loss / dpx_backward with a
@@ -181,7 +181,8 @@ typedef struct dpx_opts {
                                tables, band limit, input gap) where it is the faster one on
                                MI355X (64 points without padding always and with it up to 2048
                                wavelengths, 96 points from 96 to 1024, 128 points from 64 on),
-                               if max_workspace_bytes leaves room for its slots.  A misalignment
+                               if max_workspace_bytes and the device leave room for one more
+                               checkpoint slab, that of layer 0 (W*N*N complex).  A misalignment
                                sends an automatic plan's calls through the multi-pass kernels
                                while it is set. */
   int32_t check_finite;     /* nonzero (a debugging aid): dpx_forward, dpx_loss and

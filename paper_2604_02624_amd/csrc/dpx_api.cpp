@@ -1437,21 +1437,11 @@ dpx_status upload_wavelengths(Design& d) {
   return DPX_OK;
 }
 
-}  // namespace
-
-dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opts, dpx_plan** out) {
-  if (!out) return fail(DPX_E_ARG, "out is NULL");
-  *out = nullptr;
-  dpx_opts o;
-  dpx_opts_default(&o);
-  if (opts) o = *opts;
-  DPX_TRY(validate(ds, nd, &o));
-  int64_t need = 0;
-  DPX_TRY(dpx_plan_query(ds, nd, &o, &need));
-  if (o.max_workspace_bytes > 0 && need > o.max_workspace_bytes)
-    return fail(DPX_E_NOMEM, "plan needs %lld device bytes, limit is %lld", static_cast<long long>(need),
-                static_cast<long long>(o.max_workspace_bytes));
-
+// Creates a validated plan.  lds_wanted: false leaves the automatic LDS-resident path out; *lds_auto: a
+// design has it.
+dpx_status create_plan(const dpx_design* ds, int32_t nd, const dpx_opts& o, bool lds_wanted, bool* lds_auto,
+                       dpx_plan** out) {
+  *lds_auto = false;
   dpx_plan* p = new dpx_plan();
   p->opts = o;
   if (hipGetDevice(&p->device) != hipSuccess) {
@@ -1464,7 +1454,8 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
   for (int i = 0; i < nd && st == DPX_OK; ++i) {
     const dpx_design& src = ds[i];
     Design& d = p->designs[i];
-    layout_design(src, o, nd == 1, d);
+    layout_design(src, o, nd == 1, d, lds_wanted);
+    *lds_auto = *lds_auto || d.lds_auto;
     d.wl.assign(src.wl, src.wl + src.n_wl);
     d.n_mat.assign(src.n_mat, src.n_mat + src.n_wl);
     d.kappa.assign(src.n_wl, 0.0);
@@ -1634,6 +1625,27 @@ dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opt
   }
   *out = p;
   return ok();
+}
+
+}  // namespace
+
+dpx_status dpx_plan_create(const dpx_design* ds, int32_t nd, const dpx_opts* opts, dpx_plan** out) {
+  if (!out) return fail(DPX_E_ARG, "out is NULL");
+  *out = nullptr;
+  dpx_opts o;
+  dpx_opts_default(&o);
+  if (opts) o = *opts;
+  DPX_TRY(validate(ds, nd, &o));
+  int64_t need = 0;
+  DPX_TRY(dpx_plan_query(ds, nd, &o, &need));
+  if (o.max_workspace_bytes > 0 && need > o.max_workspace_bytes)
+    return fail(DPX_E_NOMEM, "plan needs %lld device bytes, limit is %lld", static_cast<long long>(need),
+                static_cast<long long>(o.max_workspace_bytes));
+  bool lds_auto = false;
+  const dpx_status st = create_plan(ds, nd, o, true, &lds_auto, out);
+  // the passes alone need less memory than an automatic LDS-resident plan, which has room for both
+  if (st == DPX_E_NOMEM && lds_auto) return create_plan(ds, nd, o, false, &lds_auto, out);
+  return st;
 }
 
 dpx_status dpx_plan_destroy(dpx_plan* p) {
