@@ -1416,7 +1416,7 @@ dpx_status upload_wavelengths(Design& d) {
     tab[w].ca = kTwoPi * d.kappa[w] / lam;
     const double r = md * d.n_m / lam;
     tab[w].q0 = r * r;
-    tab[w].ct = static_cast<float>(kTwoPi * (d.n_mat[w] - d.n_m) / lam);
+    tab[w].ct = static_cast<float>(kTwoPi * (d.n_mat[w] - d.n_m) / lam) / dpx::kAdjointScale;
     const double half = d.M / 2;
     int k = static_cast<int>(std::sqrt(std::min(tab[w].q0, half * half + 1.0)));
     if (static_cast<double>(k) * k >= tab[w].q0) --k;  // q0 = kx^2 is outside the disc

@@ -14,11 +14,16 @@ namespace dpx {
 //   ca = 2 pi kappa / lambda                [1/m]   absorption of t per metre
 //   q0 = (M dx n_m / lambda)^2              [-]     squared radius of the propagating disc
 //                                                   in units of the frequency grid step
-//   ct = 2 pi (n - n_m) / lambda            [1/m]   phase per metre (gradient)
+//   ct = 2 pi (n - n_m) / lambda            [1/m]   phase per metre (gradient), over kAdjointScale
 //   radius                                  [-]     largest |kx| with kx^2 < q0, at most M / 2: the
 //                                                   spectrum columns that carry anything.  H is zero
 //                                                   on every other column, which is neither written
 //                                                   nor read
+// The adjoint field is carried as this power of two of itself, so that large dL/dI do not overflow in
+// the column transforms' fused butterflies, whose inner sums reach 2^30 times the spectrum (col_fft.hpp);
+// the seeds are scaled by it and the gradient's factors by its inverse, all exactly.
+constexpr float kAdjointScale = 0x1p-14f;
+
 struct WlConst {
   double rt, ca, q0;
   float ct;

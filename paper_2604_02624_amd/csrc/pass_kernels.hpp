@@ -284,7 +284,7 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
       for (int t = 0; t < EN; ++t) {
         const int x = j0 + P * t;
         if (x >= x0 && x < x0 + F) {
-          const float s = 2.0f * d[(x - x0) / b];
+          const float s = 2.0f * kAdjointScale * d[(x - x0) / b];
           reg[t] = cscale(o[x - x0], s);
         } else {
           reg[t] = make_float2(0.f, 0.f);
@@ -315,7 +315,7 @@ __device__ __forceinline__ void row_body(const RowArgs& a, int bx, int by, float
                                        static_cast<size_t>(y) * N;
       fft<M, true, false, V, XPad<M>::ROWS>(reg, lds, j0, tw);
       const float ct = c.ct;
-      const float ca = static_cast<float>(c.ca);
+      const float ca = static_cast<float>(c.ca) / kAdjointScale;
 #pragma unroll
       for (int t = 0; t < EN; ++t) {
         const float2 gv = reg[t];
@@ -1537,7 +1537,7 @@ lds_adjoint_kernel(LdsArgs a) {
       for (int t = 0; t < EN; ++t) {
         const int x = j0 + P * t;
         if (x >= x0 && x < x0 + F) {
-          const float s = 2.0f * d[(x - x0) / b];
+          const float s = 2.0f * kAdjointScale * d[(x - x0) / b];
           reg[t] = cscale(o[x - x0], s);
         } else {
           reg[t] = make_float2(0.f, 0.f);
@@ -1548,7 +1548,7 @@ lds_adjoint_kernel(LdsArgs a) {
       for (int t = 0; t < E; ++t) row[j0 + P * t] = reg[t];
     }
     __syncthreads();
-    const float ct = c.ct, ca = static_cast<float>(c.ca);
+    const float ct = c.ct, ca = static_cast<float>(c.ca) / kAdjointScale;
     for (int l = a.K - 1; l >= 0; --l) {
       gap.zrev = a.zrev[l];
       lds_columns<M, PAD, true>(c, gap, l == a.K - 1 ? x0 : 0, l == a.K - 1 ? x0 + F : N, plane, tab, tid);
