@@ -145,7 +145,9 @@ inline float2 fused_pair(long long num, long long den) {
     return make_float2(9.31322574615478515625e-10f, s * 1073741824.f);
   }
   const double ang = 6.283185307179586476925286766559 * static_cast<double>(m) / static_cast<double>(den);
-  return make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(-std::tan(ang)));
+  // t over the rounded c: the sine c t that the butterfly forms is then off by t's own rounding alone
+  const float c = static_cast<float>(std::cos(ang));
+  return make_float2(c, static_cast<float>(-std::sin(ang) / c));
 }
 // entry e of the input twiddles of radix R with base exp(-2 pi i num / den)
 inline float2 input_twiddle(int R, int e, long long num, long long den) {
@@ -268,14 +270,23 @@ __device__ __forceinline__ void dft_input_twiddled(float2* v, const float2* p) {
   }
 }
 
-// Forward transform to the odd multiples of half a bin: sum_r v[r] w_(2R)^(r (2 k + 1)).
+// Forward transform to the odd multiples of half a bin: sum_r v[r] w_(2R)^(r (2 k + 1)).  Even R joins
+// the transforms of the even and odd inputs; for R = 3 the odd multiples are a permutation of the plain
+// transform with the sign of v[1] turned, w_6^(2 k + 1) = -w_3^-(2 k + 1).
 template <int R>
 __device__ __forceinline__ void dft_odd(float2* v) {
   if constexpr (R == 2) {
     const float2 a = v[0], b = mul_negi(v[1]);
     v[0] = cadd(a, b);
     v[1] = csub(a, b);
-  } else if constexpr (pow2(R)) {
+  } else if constexpr (R == 3) {
+    v[1] = make_float2(-v[1].x, -v[1].y);
+    DFT<3, false, false>::run(v);
+    const float2 x0 = v[2], x1 = v[0];
+    v[2] = v[1];
+    v[0] = x0;
+    v[1] = x1;
+  } else if constexpr (pow2(R) || R == 6) {
     float2 e[R / 2], o[R / 2];
 #pragma unroll
     for (int i = 0; i < R / 2; ++i) {
@@ -284,12 +295,21 @@ __device__ __forceinline__ void dft_odd(float2* v) {
     }
     dft_odd<R / 2>(e);
     dft_odd<R / 2>(o);
-    static_for<0, R / 4>([&](auto kc) {
+    // the factor w_(2R)^(2 k + 1); of a power of two the upper half of them is the lower half turned by a
+    // quarter, of 6 the one in the middle is a quarter itself
+    static_for<0, R == 6 ? 3 : R / 4>([&](auto kc) {
       constexpr int k = decltype(kc)::value;
-      constexpr float c = static_cast<float>(cos2pi(2 * k + 1, 2 * R));
-      constexpr float t = static_cast<float>(-sin2pi(2 * k + 1, 2 * R) / cos2pi(2 * k + 1, 2 * R));
-      fused_butterfly<false>(e[k], o[k], c, t, v[k], v[k + R / 2]);
-      fused_butterfly_quarter<false>(e[k + R / 4], o[k + R / 4], c, t, v[k + R / 4], v[k + 3 * R / 4]);
+      if constexpr (R == 6 && k == 1) {
+        const float2 b = mul_negi(o[k]);
+        v[k] = cadd(e[k], b);
+        v[k + R / 2] = csub(e[k], b);
+      } else {
+        constexpr float c = static_cast<float>(cos2pi(2 * k + 1, 2 * R));
+        constexpr float t = static_cast<float>(-sin2pi(2 * k + 1, 2 * R) / c);
+        fused_butterfly<false>(e[k], o[k], c, t, v[k], v[k + R / 2]);
+        if constexpr (R != 6)
+          fused_butterfly_quarter<false>(e[k + R / 4], o[k + R / 4], c, t, v[k + R / 4], v[k + 3 * R / 4]);
+      }
     });
   } else {
     static_for<1, R>([&](auto rc) {
