@@ -1,5 +1,6 @@
 """Rounding of the transforms against double precision (host build of csrc/fft.hpp and col_fft.hpp): the
-split column transforms stay as accurate as the staged ones; the split of 800-point halves phase by phase."""
+split column transforms stay as accurate as the staged ones, and the plans of 64 and 96 points as other
+radices; the split of 800-point halves phase by phase."""
 import os
 import shutil
 import subprocess
@@ -28,6 +29,12 @@ def test_split_columns_round_no_more_than_staged_ones(figures):
     ratios = {k: v for k, v in figures.items() if k.startswith("split")}
     assert len(ratios) == 16
     assert all(v < 1.02 for v in ratios.values()), ratios
+
+
+def test_plans_of_short_lengths(figures):
+    ratios = {k: v for k, v in figures.items() if k.startswith("plan")}
+    assert len(ratios) == 4
+    assert all(v < 1.01 for v in ratios.values()), ratios
 
 
 def test_halves_of_800_points(figures):
