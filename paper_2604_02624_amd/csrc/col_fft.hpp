@@ -132,82 +132,75 @@ struct ColSplit800 {
   static __host__ __device__ constexpr int slot(int k1, int j) { return k1 * 33 + j; }
 };
 
-// exp(-2 pi i num / den) with the numerator reduced first
-inline float2 unit_root(long long num, long long den) {
-  const double ang = 6.283185307179586476925286766559 * static_cast<double>(num % den) / static_cast<double>(den);
-  return make_float2(static_cast<float>(std::cos(ang)), static_cast<float>(-std::sin(ang)));
-}
-// the pair (c, t) of exp(-2 pi i num / den) = c (1 + i t)
-inline float2 fused_pair(long long num, long long den) {
-  const long long m = num % den;
-  if (4 * m == den || 4 * m == 3 * den) {
-    const float s = 4 * m == den ? -1.f : 1.f;
+// the pair (c, t) of exp(-2 pi i k / M) = c (1 + i t)
+inline float2 fused_pair(const UnitRoots& u, int k) {
+  if (4 * k == u.length() || 4 * k == 3 * u.length()) {
+    const float s = 4 * k == u.length() ? -1.f : 1.f;
     return make_float2(9.31322574615478515625e-10f, s * 1073741824.f);
   }
-  const double ang = 6.283185307179586476925286766559 * static_cast<double>(m) / static_cast<double>(den);
   // t over the rounded c: the sine c t that the butterfly forms is then off by t's own rounding alone
-  const float c = static_cast<float>(std::cos(ang));
-  return make_float2(c, static_cast<float>(-std::sin(ang) / c));
+  const float c = static_cast<float>(u.cos(k));
+  return make_float2(c, static_cast<float>(-u.sin(k) / c));
 }
 // entry e of the input twiddles of radix R with base exp(-2 pi i num / den)
-inline float2 input_twiddle(int R, int e, long long num, long long den) {
-  if (!pow2(R)) return unit_root((e + 1) * num, den);
+inline float2 input_twiddle(const UnitRoots& u, int R, int e, long long num, long long den) {
+  if (!pow2(R)) return unit_root(u, (e + 1) * num, den);
   int S = 2;
   while (S < R && pair_index(2 * S, 0) <= e) S *= 2;
   const int k = e - pair_index(S, 0);
   // base^(R / S) w_S^k
-  return fused_pair(num * (R / S) * S + k * den, den * S);
+  return fused_pair(u, (u.index(num * (R / S), den) + u.index(k, S)) % u.length());
 }
 
 template <int M, int PAD>
-inline void col_table_host(std::vector<float2>& out) {
+inline void col_table_host(std::vector<float2>& out, const UnitRoots& u = UnitRoots(M)) {
   using G = ColSplit<M, PAD>;
   out.assign(G::COUNT > 0 ? G::COUNT : 1, make_float2(1.f, 0.f));
   if constexpr (G::BUILT) {
     for (int e = 0; e < G::NB; ++e)
       for (int h = 0; h < G::NH; ++h)
         for (int k1 = 0; k1 < G::R1; ++k1)
-          out[(e * G::NH + h) * G::R1 + k1] = input_twiddle(G::R2, e, G::NH * k1 + h, M);
+          out[(e * G::NH + h) * G::R1 + k1] = input_twiddle(u, G::R2, e, G::NH * k1 + h, M);
     for (int e = 0; e < G::NC; ++e)
       for (int p = 0; p < G::NH; ++p)
         for (int j = 0; j < G::L; ++j)  // w_LEN^j, turned by w_R1 for the odd rows
           out[G::OFF_C + (e * G::NH + p) * G::L + j] =
-              input_twiddle(G::RC, e, j + p * (G::LEN / G::R1), G::LEN);
+              input_twiddle(u, G::RC, e, j + p * (G::LEN / G::R1), G::LEN);
     if constexpr (G::NH == 2) {
       for (int j = 0; j < G::L; ++j)
-        out[G::OFF_0 + j] = unit_root(static_cast<long long>(j) * (G::R1 / 2), G::LEN);
-      for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
+        out[G::OFF_0 + j] = unit_root(u, static_cast<long long>(j) * (G::R1 / 2), G::LEN);
+      for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(u, n, M);
     }
   }
 }
 
 template <int M, int PAD>
-inline void col3_table_host(std::vector<float2>& out) {
+inline void col3_table_host(std::vector<float2>& out, const UnitRoots& u = UnitRoots(M)) {
   using G = ColSplit3<M, PAD>;
   out.assign(G::COUNT, make_float2(1.f, 0.f));
   for (int e = 0; e < 4; ++e) {
     for (int h = 0; h < G::NH; ++h) {
-      for (int k1 = 0; k1 < 8; ++k1) out[(e * G::NH + h) * 8 + k1] = input_twiddle(8, e, 8 * (G::NH * k1 + h), M);
+      for (int k1 = 0; k1 < 8; ++k1) out[(e * G::NH + h) * 8 + k1] = input_twiddle(u, 8, e, 8 * (G::NH * k1 + h), M);
       for (int l = 0; l < 64; ++l)  // l = k1 + 8 m
-        out[G::OFF_B2 + (e * G::NH + h) * 64 + l] = input_twiddle(8, e, G::NH * l + h, M);
+        out[G::OFF_B2 + (e * G::NH + h) * 64 + l] = input_twiddle(u, 8, e, G::NH * l + h, M);
     }
-    for (int j = 0; j < 8; ++j) out[G::OFF_R + e * 8 + j] = input_twiddle(8, e, j, 64);
-    for (int j = 0; j < 64; ++j) out[G::OFF_C + e * 64 + j] = input_twiddle(8, e, j, G::LEN);
+    for (int j = 0; j < 8; ++j) out[G::OFF_R + e * 8 + j] = input_twiddle(u, 8, e, j, 64);
+    for (int j = 0; j < 64; ++j) out[G::OFF_C + e * 64 + j] = input_twiddle(u, 8, e, j, G::LEN);
   }
   if constexpr (G::NH == 2)
-    for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
+    for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(u, n, M);
 }
 
 template <int M, int PAD>
-inline void col800_table_host(std::vector<float2>& out) {
+inline void col800_table_host(std::vector<float2>& out, const UnitRoots& u = UnitRoots(M)) {
   using G = ColSplit800<M, PAD>;
   out.assign(G::COUNT, make_float2(1.f, 0.f));
   for (int e = 0; e < 16; ++e)
     for (int h = 0; h < G::NH; ++h)
-      for (int k1 = 0; k1 < G::R1; ++k1) out[(e * G::NH + h) * 32 + k1] = input_twiddle(32, e, G::NH * k1 + h, M);
+      for (int k1 = 0; k1 < G::R1; ++k1) out[(e * G::NH + h) * 32 + k1] = input_twiddle(u, 32, e, G::NH * k1 + h, M);
   for (int e = 0; e < 24; ++e)
-    for (int j = 0; j < 32; ++j) out[G::OFF_C + e * 32 + j] = input_twiddle(25, e, j, G::LEN);
-  for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(n, M);
+    for (int j = 0; j < 32; ++j) out[G::OFF_C + e * 32 + j] = input_twiddle(u, 25, e, j, G::LEN);
+  for (int n = 0; n < G::LEN; ++n) out[G::OFF_W + n] = unit_root(u, n, M);
 }
 
 // ------------------------------------------------------------------------------------------

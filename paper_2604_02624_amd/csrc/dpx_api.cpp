@@ -12,6 +12,7 @@
 #include <limits>
 #include <array>
 #include <map>
+#include <memory>
 #include <string>
 #include <vector>
 
@@ -1495,8 +1496,10 @@ dpx_status create_plan(const dpx_design* ds, int32_t nd, const dpx_opts& o, bool
     // transforms where the length has them, in one allocation and one copy
     std::vector<float2> tables;
     std::vector<std::pair<int, size_t>> parts;  // key, offset
+    std::unique_ptr<dpx::UnitRoots> roots;
     auto add_table = [&](int key, auto&& build) {
       if (p->twiddles.count(key)) return;
+      if (!roots) roots = std::make_unique<dpx::UnitRoots>(d.M);
       std::vector<float2> t;
       build(t);
       parts.push_back({key, tables.size()});
@@ -1504,9 +1507,9 @@ dpx_status create_plan(const dpx_design* ds, int32_t nd, const dpx_opts& o, bool
       tables.resize((tables.size() + 31) / 32 * 32, make_float2(0.f, 0.f));  // 256-byte aligned parts
     };
     for (int pl = 0; pl < dpx::radix_plan_count(d.M); ++pl)
-      add_table(tw_key(d.M, pl), [&](std::vector<float2>& t) { dpx::build_twiddle_table(d.M, pl, t); });
+      add_table(tw_key(d.M, pl), [&](std::vector<float2>& t) { dpx::build_twiddle_table(d.M, pl, *roots, t); });
     if (dpx::col_split(d.M, d.pad))
-      add_table(col_key(d.M, d.pad), [&](std::vector<float2>& t) { dpx::build_col_table(d.M, d.pad, t); });
+      add_table(col_key(d.M, d.pad), [&](std::vector<float2>& t) { dpx::build_col_table(d.M, d.pad, *roots, t); });
     const size_t count_at = tables.size();
     tables.resize(count_at + 32, make_float2(0.f, 0.f));
     {

@@ -6,6 +6,8 @@
 #include <cstdint>
 #include <vector>
 
+#include "unit_roots.hpp"
+
 namespace dpx {
 
 // Per-wavelength constants, built on the host in double precision (paper Eq. 1 and the
@@ -251,8 +253,8 @@ __device__ __forceinline__ int group_task(const GroupArgs& g, int b) {
   hipError_t launch_row_group_##m(int pad, int mode, const GroupArgs& g, hipStream_t s);                \
   hipError_t launch_col_##m(int pad, bool conj, int variant, int plan, const ColArgs& a, int w_count,    \
                             hipStream_t s);                                                             \
-  void twiddle_table_##m(int plan, std::vector<float2>& out);                                           \
-  void col_table_##m(int pad, std::vector<float2>& out);                                                \
+  void twiddle_table_##m(int plan, const UnitRoots& u, std::vector<float2>& out);                       \
+  void col_table_##m(int pad, const UnitRoots& u, std::vector<float2>& out);                            \
   bool col_split_##m(int pad);                                                                          \
   int col_tile_width_##m(int pad, int variant);                                                         \
   hipError_t launch_col_group_##m(int pad, bool conj, int variant, bool table, bool full,               \
@@ -278,7 +280,7 @@ hipError_t launch_dh_group(const GroupArgs& g, float* dl_dh, hipStream_t s);
 int col_tile_width(int M, int pad, int variant);
 // whether radix plan 0's column passes run the split transforms (col_fft.hpp), and their table
 bool col_split(int M, int pad);
-void build_col_table(int M, int pad, std::vector<float2>& out);
+void build_col_table(int M, int pad, const UnitRoots& u, std::vector<float2>& out);
 
 // launchers (dpx_kernels.hip); each returns a hipError_t from the launch
 // plan: the radix plan of the transforms (0 .. radix_plan_count(M) - 1)
@@ -328,7 +330,7 @@ hipError_t launch_psnr(const float* I, const float* tau, double* out, int W, int
 
 bool fft_size_supported(int M);
 // host: per-stage twiddle table of the length-M transform (layout in fft.hpp)
-void build_twiddle_table(int M, int plan, std::vector<float2>& out);
+void build_twiddle_table(int M, int plan, const UnitRoots& u, std::vector<float2>& out);
 // radix plans of a transform length (plan 0 is the built-in one; the others run the evaluated
 // and mirrored transfer functions of untranslated full-spectrum gaps, per-design schedule only)
 int radix_plan_count(int M);

@@ -443,9 +443,9 @@ void build_dft_table(int M, int pad, std::vector<float2>& out) {
     }
 }
 
-void build_twiddle_table(int M, int plan, std::vector<float2>& out) {
+void build_twiddle_table(int M, int plan, const UnitRoots& u, std::vector<float2>& out) {
   switch (M) {
-#define DPX_CASE(m) case m: twiddle_table_##m(plan, out); return;
+#define DPX_CASE(m) case m: twiddle_table_##m(plan, u, out); return;
     DPX_FOR_EACH_M(DPX_CASE)
 #undef DPX_CASE
     default:
@@ -576,9 +576,9 @@ bool col_split(int M, int pad) {
   }
 }
 
-void build_col_table(int M, int pad, std::vector<float2>& out) {
+void build_col_table(int M, int pad, const UnitRoots& u, std::vector<float2>& out) {
   switch (M) {
-#define DPX_CASE(m) case m: col_table_##m(pad, out); return;
+#define DPX_CASE(m) case m: col_table_##m(pad, u, out); return;
     DPX_FOR_EACH_M(DPX_CASE)
 #undef DPX_CASE
     default:

@@ -257,20 +257,20 @@ hipError_t DPX_NAME(launch_col_)(int pad, bool conj, int variant, int plan, cons
   return hipErrorInvalidValue;
 }
 
-void DPX_NAME(twiddle_table_)(int plan, std::vector<float2>& out) {
+void DPX_NAME(twiddle_table_)(int plan, const UnitRoots& u, std::vector<float2>& out) {
   out.clear();
   (void)with_plan(plan, [&](auto vc) -> hipError_t {
-    twiddle_table_host<M, decltype(vc)::value>(out);
+    twiddle_table_host<M, decltype(vc)::value>(out, u);
     return hipSuccess;
   });
 }
 
-void DPX_NAME(col_table_)(int pad, std::vector<float2>& out) {
+void DPX_NAME(col_table_)(int pad, const UnitRoots& u, std::vector<float2>& out) {
   const auto build = [&](auto padc) {
     constexpr int PD = decltype(padc)::value;
-    if constexpr (ColSplit800<M, PD>::BUILT) col800_table_host<M, PD>(out);
-    else if constexpr (ColSplit3<M, PD>::BUILT) col3_table_host<M, PD>(out);
-    else col_table_host<M, PD>(out);
+    if constexpr (ColSplit800<M, PD>::BUILT) col800_table_host<M, PD>(out, u);
+    else if constexpr (ColSplit3<M, PD>::BUILT) col3_table_host<M, PD>(out, u);
+    else col_table_host<M, PD>(out, u);
   };
   if (pad == 2) build(std::integral_constant<int, 2>{});
   else build(std::integral_constant<int, 1>{});

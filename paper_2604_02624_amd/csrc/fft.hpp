@@ -24,6 +24,8 @@
 #include <utility>
 #include <vector>
 
+#include "unit_roots.hpp"
+
 namespace dpx {
 
 // ------------------------------------------------------------------------------------------
@@ -446,22 +448,22 @@ constexpr int twiddle_count() { return twiddle_offset<M, V>(Radix<M, V>::NST); }
 
 // The table of radix plan V of length M, built on the host in double precision from exact
 // integer indices: W_L^(r k) with the exponent reduced mod L before the angle is formed.
+// exp(-2 pi i num / den) as a table entry
+inline float2 unit_root(const UnitRoots& u, long long num, long long den) {
+  const int k = u.index(num, den);
+  return make_float2(static_cast<float>(u.cos(k)), static_cast<float>(-u.sin(k)));
+}
+
 template <int M, int V>
-inline void twiddle_table_host(std::vector<float2>& out) {
+inline void twiddle_table_host(std::vector<float2>& out, const UnitRoots& u = UnitRoots(M)) {
   out.assign(twiddle_count<M, V>() > 0 ? twiddle_count<M, V>() : 1, make_float2(1.f, 0.f));
   int ns = Radix<M, V>::R[0];
   for (int st = 1; st < Radix<M, V>::NST; ++st) {
     const int R = Radix<M, V>::R[st];
-    const int L = ns * R;
     const int off = twiddle_offset<M, V>(st);
     for (int r = 1; r < R; ++r)
-      for (int k = 0; k < ns; ++k) {
-        const double ang = 6.283185307179586476925286766559 * static_cast<double>((r * k) % L) /
-                           static_cast<double>(L);
-        out[off + (r - 1) * ns + k] = make_float2(static_cast<float>(std::cos(ang)),
-                                                  static_cast<float>(-std::sin(ang)));
-      }
-    ns = L;
+      for (int k = 0; k < ns; ++k) out[off + (r - 1) * ns + k] = unit_root(u, r * k, ns * R);
+    ns *= R;
   }
 }
 

@@ -56,7 +56,7 @@ template <bool INV, bool HALF, int R>
 void given_stage(Column& x, int& ns) {
   Column tw((R - 1) * ns);
   for (int r = 1; r < R; ++r)
-    for (int k = 0; k < ns; ++k) tw[(r - 1) * ns + k] = unit_root(r * k, ns * R);
+    for (int k = 0; k < ns; ++k) tw[(r - 1) * ns + k] = unit_root(UnitRoots(static_cast<int>(x.size())), r * k, ns * R);
   if (ns == 1) stage<R, INV, HALF>(x, ns, tw.data());
   else stage<R, INV, false>(x, ns, tw.data());
 }
