@@ -31,7 +31,7 @@ __global__ void bin_group_kernel(GroupArgs g, float* __restrict__ out) {
 
 constexpr int kLossThreads = 256;
 constexpr int kLossThreadsLarge = 1024;  // large_image
-constexpr int kLossCache = 16;           // pixels a thread keeps in registers
+constexpr int kLossCache = 16;           // most pixels a thread keeps in registers
 
 // v plus its neighbour's value under the DPP control CTRL (0 where there is none)
 template <int CTRL, int ROWS>
@@ -76,18 +76,18 @@ struct Max {
   __device__ __forceinline__ double operator()(double a, double b) const { return fmax(a, b); }
 };
 
-// The pixels of one wavelength's image and target, walked several times: from registers where a
-// thread has at most kLossCache of them, else from memory.
-template <int THREADS, bool CACHED>
+// The pixels of one wavelength's image and target, walked several times: from CACHE registers where a
+// thread has no more of them, else (CACHE = 0) from memory.
+template <int THREADS, int CACHE>
 struct Pixels {
   const float* __restrict__ I;
   const float* __restrict__ tau;
   int P;
-  float iv[CACHED ? kLossCache : 1], tv[CACHED ? kLossCache : 1];
+  float iv[CACHE > 0 ? CACHE : 1], tv[CACHE > 0 ? CACHE : 1];
   __device__ __forceinline__ Pixels(const float* I_, const float* tau_, int P_) : I(I_), tau(tau_), P(P_) {
-    if constexpr (CACHED) {
+    if constexpr (CACHE > 0) {
 #pragma unroll
-      for (int k = 0; k < kLossCache; ++k) {
+      for (int k = 0; k < CACHE; ++k) {
         const int p = threadIdx.x + k * THREADS;
         iv[k] = p < P ? I[p] : 0.f;
         tv[k] = p < P ? tau[p] : 0.f;
@@ -96,9 +96,9 @@ struct Pixels {
   }
   template <typename F>
   __device__ __forceinline__ void each(F&& f) const {
-    if constexpr (CACHED) {
+    if constexpr (CACHE > 0) {
 #pragma unroll
-      for (int k = 0; k < kLossCache; ++k)
+      for (int k = 0; k < CACHE; ++k)
         if (threadIdx.x + k * THREADS < P) f(static_cast<int>(threadIdx.x + k * THREADS), iv[k], tv[k]);
     } else {
 #pragma unroll 4
@@ -111,11 +111,11 @@ struct Pixels {
 // latency: each image is read once into registers and the two rounds of sums cost one block barrier
 // each (a tree of barriers and three walks over memory took 7 us at 6 images of 32 x 32 and 27 us
 // at 1024 of 64 x 64).
-template <int THREADS, bool CACHED>
+template <int THREADS, int CACHE>
 __device__ __forceinline__ void loss_image(const float* __restrict__ Iw, const float* __restrict__ tw,
                                            float* __restrict__ gw, double* __restrict__ out, int W, int P, double* sh) {
   constexpr int WAVES = THREADS / 64;
-  const Pixels<THREADS, CACHED> px(Iw, tw, P);
+  const Pixels<THREADS, CACHE> px(Iw, tw, P);
   double si = 0.0, st = 0.0;
   px.each([&](int, float i, float t) {
     si += i;
@@ -156,8 +156,14 @@ __device__ __forceinline__ void loss_body(const float* __restrict__ I, const flo
   const int P = T * T;
   const size_t o = static_cast<size_t>(w) * P;
   float* gw = dl_di ? dl_di + o : nullptr;
-  if (P <= THREADS * kLossCache) loss_image<THREADS, true>(I + o, tau + o, gw, per_wl + w, W, P, sh);
-  else loss_image<THREADS, false>(I + o, tau + o, gw, per_wl + w, W, P, sh);
+  if constexpr (THREADS == kLossThreads) {
+    // short walks over few pixels: 4096 images of 16 x 16 take 10 us with the loss of one pixel per
+    // thread, 18.7 where each thread steps over fifteen that are not there
+    if (P <= THREADS) return loss_image<THREADS, 1>(I + o, tau + o, gw, per_wl + w, W, P, sh);
+    if (P <= 4 * THREADS) return loss_image<THREADS, 4>(I + o, tau + o, gw, per_wl + w, W, P, sh);
+  }
+  if (P <= kLossCache * THREADS) loss_image<THREADS, kLossCache>(I + o, tau + o, gw, per_wl + w, W, P, sh);
+  else loss_image<THREADS, 0>(I + o, tau + o, gw, per_wl + w, W, P, sh);
 }
 
 template <int THREADS>
@@ -366,11 +372,11 @@ __global__ void adam_sigmoid_kernel(float* __restrict__ theta, float* __restrict
 // Per-wavelength PSNR of the intensity image against its target, both normalised to unit sum
 // (as in the loss): 10 log10(max_p tau^2 / mean_p (I - tau)^2), in double; one block per
 // wavelength of one design ([W][T][T] images, out [W]).
-template <int THREADS, bool CACHED>
+template <int THREADS, int CACHE>
 __device__ __forceinline__ void psnr_image(const float* __restrict__ Iw, const float* __restrict__ tw,
                                            double* __restrict__ out, int P, double* sh) {
   constexpr int WAVES = THREADS / 64;
-  const Pixels<THREADS, CACHED> px(Iw, tw, P);
+  const Pixels<THREADS, CACHE> px(Iw, tw, P);
   double si = 0.0, st = 0.0, mx = 0.0;
   px.each([&](int, float i, float t) {
     si += i;
@@ -405,8 +411,8 @@ psnr_kernel(const float* __restrict__ I, const float* __restrict__ tau, double* 
   __shared__ double sh[4 * (THREADS / 64)];
   const int P = T * T;
   const size_t o = static_cast<size_t>(blockIdx.x) * P;
-  if (P <= THREADS * kLossCache) psnr_image<THREADS, true>(I + o, tau + o, out + blockIdx.x, P, sh);
-  else psnr_image<THREADS, false>(I + o, tau + o, out + blockIdx.x, P, sh);
+  if (P <= kLossCache * THREADS) psnr_image<THREADS, kLossCache>(I + o, tau + o, out + blockIdx.x, P, sh);
+  else psnr_image<THREADS, 0>(I + o, tau + o, out + blockIdx.x, P, sh);
 }
 
 __global__ void fill_zero_kernel(float* p, int64_t n) {
