@@ -578,13 +578,18 @@ dpx_status run_row(dpx_plan* p, const Design& d, int mode, RowArgs a, int row_lo
 // second one's rows are prefetched while the first is transformed; best of 1, 2, 4, 8 on 4096
 // wavelengths of 512 x 512).  Of the split forms, halves of up to 256 points take four, whose blocks
 // also stage a table (512 points, 1024 wavelengths: 647, 620 and 616 us per pass with 2, 4 and 8; 384
-// points, 512 wavelengths: 211, 204, 210), unpadded columns one (128 points, 2048 wavelengths: 108
-// us against 113 and 118 with 2 and 4; 256 points 49, 52, 52) and halves of 512 points one (their
-// kernel runs no more).
+// points, 512 wavelengths: 211, 204, 210), and from 128 points on eight where that still leaves eight
+// blocks per CU (4096 wavelengths, forward of four layers: 256 points 3903 against 3845 us with 4 and 8,
+// 384 points 9836 and 9792, 512 points 16719 and 16579; 64 points 253 and 260).  Unpadded columns take
+// one (128 points, 2048 wavelengths: 108 us against 113 and 118 with 2 and 4; 256 points 49, 52, 52)
+// and halves of 512 and 800 points one (their kernels run no more).
 int col_wavelengths_per_block(const Design& d, int wc, int plan) {
   const int64_t tiles = static_cast<int64_t>(wc) * (d.M / 8);
-  if (plan == 0 && d.col_variant != 4 && dpx::col_split(d.M, d.pad))
-    return d.pad == 2 && d.M / d.pad < 512 && tiles >= 4 * 8192 ? 4 : 1;
+  if (plan == 0 && d.col_variant != 4 && dpx::col_split(d.M, d.pad)) {
+    const int len = d.M / d.pad;
+    if (d.pad != 2 || len >= 512 || tiles < 4 * 8192) return 1;
+    return len >= 128 && tiles >= 8 * 8192 ? 8 : 4;
+  }
   return tiles >= 2 * 8192 ? 2 : 1;
 }
 
