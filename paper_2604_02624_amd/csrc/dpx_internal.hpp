@@ -50,17 +50,20 @@ constexpr int row_pass_kind(int mode) { return 2 + (mode == ROW_ADJ_LAST_U ? ROW
 // such blocks per CU next to their LDS, 256 for the register-heavy adjoint passes with a gradient
 // (136-168 registers at 512 and 1024 points allow three wavefronts per SIMD, of which blocks of
 // 512 threads could use two).
-// So do all passes of unpadded rows with 16 values per lane (131-160 registers at 512 points).
+// So do all passes of unpadded rows with 16 values per lane (131-160 registers at 512 points; at 1024
+// points a forward of three layers and 16 wavelengths takes 392 us against 422 with 512 threads).
 constexpr int row_threads_of_mode(int values, int pad, int mode) {
   return mode >= ROW_ADJ_MID || (pad == 1 && values >= 16) ? 256 : 512;
 }
 // Threads of a row-pass block for P lanes per transform: the mode's count when transforms tile
 // a wavefront; three or so whole transforms (about 256 threads) when one spans wavefronts.
-// small: 128 threads, for launches that would leave CUs without a block (row_blocks_small): two
-// wavefronts on each of many CUs instead of eight on a few, which share a SIMD's issue.
+// small: for launches of few blocks (row_blocks_small) 128 threads: two wavefronts on each of many CUs
+// instead of eight on a few, which share a SIMD's issue.  For unpadded rows of 1024 points it means the
+// larger blocks of 512 (their middle pass of two wavelengths: 17.5 us in blocks of 256 threads, 13.2).
 constexpr int kSmallRowThreads = 128;
 constexpr int row_threads_for(int M, int P, int pad, int mode, bool small = false) {
   if (!(P <= 64 && 64 % P == 0)) return (256 / P) * P;
+  if (small && pad == 1 && M >= 1024) return mode == ROW_ADJ_MID ? 256 : 512;
   return small ? kSmallRowThreads : row_threads_of_mode(M / P, pad, mode);
 }
 // Whether a row pass of `rows` rows and n_w wavelength blocks takes the small blocks

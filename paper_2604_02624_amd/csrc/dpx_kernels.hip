@@ -516,12 +516,16 @@ int row_rows_per_block(int M, int pad, int mode, bool small) {
 // Fewer blocks than the chip has CUs: the rows of 128-thread blocks spread over up to four times as
 // many.  Measured, forward of three layers, us: one wavelength of 96 x 96 39 -> 34, 192 x 192 51 -> 43,
 // 256 x 256 48 -> 42, 512 x 512 63 -> 59; eight of 192 x 192 60 -> 54; from 256 blocks on both forms
-// take the same time and the larger blocks stage the twiddles for more rows.
+// take the same time and the larger blocks stage the twiddles for more rows.  Unpadded rows of 1024 points
+// take their other form (row_threads_for) where theirs would put a second block on CUs: forward of three
+// layers, us, in blocks of 256 and 512 threads: one wavelength 82 and 84, two 100 and 88, three 114 and 115,
+// six 191 and 196.
 bool row_blocks_small(int M, int pad, int mode, int rows, int n_w) {
   const int P = row_lanes_per_transform(M);
   if (P == 0 || P > 64 || 64 % P) return false;
   const int per = row_rows_per_block(M, pad, mode);
-  return static_cast<int64_t>((rows + per - 1) / per) * n_w < 256;
+  const int64_t blocks = static_cast<int64_t>((rows + per - 1) / per) * n_w;
+  return pad == 1 && M >= 1024 ? blocks > 256 && blocks <= 512 : blocks < 256;
 }
 
 namespace {
