@@ -388,14 +388,15 @@ typedef enum dpx_pass {
 
 /* Per-pass timers (measurement support).  While enabled, every launch of the passes above is
  * bracketed by a pair of HIP events recorded on the call's stream, and the launch's
- * algorithmic device-memory traffic (bytes the pass must read and write once) is counted.
+ * algorithmic device-memory traffic (bytes the pass must read and write once: of the spectrum
+ * planes only the columns that carry propagating waves) is counted.
  * Enabling or disabling clears the counters. */
 dpx_status dpx_timing_enable(dpx_plan* plan, int32_t enable);
 
 /* Waits for the recorded events and returns, for pass `pass`, the summed kernel time in
  * milliseconds, the number of launches, the summed algorithmic bytes and the summed
  * algorithmic floating-point operations (each length-M transform counted as 5 M log2 M, each
- * complex product as 6) since the timers were enabled.  Any output pointer may be NULL. */
+ * complex product as 6; column transforms of those columns) since the timers were enabled.  Any output pointer may be NULL. */
 dpx_status dpx_timing_read(dpx_plan* plan, int32_t pass, double* total_ms, int64_t* launches,
                            int64_t* bytes, double* flops);
 

@@ -59,6 +59,7 @@ struct Design {
   std::vector<double> dz, sx, sy;  // per gap: axial jitter, lateral translation (metres)
   double z_in = 0.0;               // input plane -> layer 1 (0: u_in is the field at layer 1)
   bool band = false;               // band-limited angular spectrum
+  std::vector<int64_t> cols;       // [W + 1] spectrum columns inside the discs of the wavelengths before
   int64_t h_off, u_off, img_off;
   // launch geometry
   int wl_chunk;      // wavelengths per chunk (spec buffer depth per lane)
@@ -537,22 +538,30 @@ double row_flops(const Design& d, int mode, int wc, int rows) {
 // checkpoint slab
 int adj_last_mode(const Design& d) { return d.ck_first ? dpx::ROW_ADJ_LAST_U : dpx::ROW_ADJ_LAST; }
 
-// algorithmic bytes of one row-pass launch (every operand read or written once)
-int64_t row_bytes(const Design& d, int mode, int wc, int nwb, bool accumulate, bool has_u) {
+// spectrum columns that the wavelengths [w0, w0 + wc) move: those inside their discs (the matrix-core
+// column pass moves all)
+int64_t spectrum_columns(const Design& d, int w0, int wc) {
+  return d.col_variant == 4 ? static_cast<int64_t>(wc) * d.M : d.cols[w0 + wc] - d.cols[w0];
+}
+
+// algorithmic bytes of one row-pass launch (every operand read or written once); bins: the last forward
+// pass also writes the intensities
+int64_t row_bytes(const Design& d, int mode, int w0, int wc, int nwb, bool accumulate, bool has_u, bool bins) {
   const int64_t nn = static_cast<int64_t>(d.N) * d.N;
-  const int64_t row = static_cast<int64_t>(d.M) * 8;  // one spectrum row
+  const int64_t row = spectrum_columns(d, w0, wc) * 8;  // one spectrum row of every wavelength
+  const int64_t img = static_cast<int64_t>(d.T) * d.T * 4;
   const int64_t fov = static_cast<int64_t>(d.F) * d.F * 8;
   const int64_t part = nwb * nn * 4 * (accumulate ? 2 : 1);
   switch (mode) {
     // the first pass stores no checkpoint (layer 0's is rebuilt, or the pass only carries the
     // input plane to an input gap, reading no heights)
-    case dpx::ROW_FWD_FIRST: return wc * d.N * row + (d.z_in > 0.0 ? 0 : 4 * nn) + (has_u ? 8 * nn : 0);
-    case dpx::ROW_FWD_MID: return wc * (2 * d.N * row + 8 * nn) + 4 * nn;
-    case dpx::ROW_FWD_LAST: return wc * (d.F * row + fov);
-    case dpx::ROW_ADJ_SEED: return wc * (fov + 4 * d.T * d.T + d.F * row);
-    case dpx::ROW_ADJ_MID: return wc * (2 * d.N * row + 8 * nn) + 4 * nn + part;
-    case dpx::ROW_ADJ_LAST: return wc * (d.N * row + 8 * nn) + 4 * nn + part;
-    case dpx::ROW_ADJ_LAST_U: return wc * d.N * row + 4 * nn + part + (has_u ? 8 * nn : 0);
+    case dpx::ROW_FWD_FIRST: return d.N * row + (d.z_in > 0.0 ? 0 : 4 * nn) + (has_u ? 8 * nn : 0);
+    case dpx::ROW_FWD_MID: return 2 * d.N * row + wc * 8 * nn + 4 * nn;
+    case dpx::ROW_FWD_LAST: return d.F * row + wc * (fov + (bins ? img : 0));
+    case dpx::ROW_ADJ_SEED: return d.F * row + wc * (fov + img);
+    case dpx::ROW_ADJ_MID: return 2 * d.N * row + wc * 8 * nn + 4 * nn + part;
+    case dpx::ROW_ADJ_LAST: return d.N * row + wc * 8 * nn + 4 * nn + part;
+    case dpx::ROW_ADJ_LAST_U: return d.N * row + 4 * nn + part + (has_u ? 8 * nn : 0);
     default: return 0;
   }
 }
@@ -565,7 +574,7 @@ dpx_status run_row(dpx_plan* p, const Design& d, int mode, RowArgs a, int row_lo
   const int rg = dpx::row_rows_per_block(d.M, d.pad, mode, small);
   const int nrb = (row_hi - row_lo + rg - 1) / rg;
   TimedLaunch t{dpx::row_pass_kind(mode), nullptr, nullptr,
-                row_bytes(d, mode, a.w_count, nwb, a.accumulate != 0, a.u_in != nullptr),
+                row_bytes(d, mode, a.w_begin, a.w_count, nwb, a.accumulate != 0, a.u_in != nullptr, a.intensity != nullptr),
                 row_flops(d, mode, a.w_count, row_hi - row_lo)};
   DPX_TRY(timer_begin(p, s, t));
   hipError_t e = dpx::launch_row(d.M, d.pad, mode, d.row_plan, small, a, nrb, nwb, s);
@@ -624,23 +633,22 @@ ColArgs col_args(const dpx_plan* p, const Design& d, int lane, int layer, int w0
   return c;
 }
 
-// algorithmic bytes of a column launch: staged rows in and kept rows out, plus every entry of
-// the wavelengths' transfer tables once when the plan has them
-int64_t col_bytes(const Design& d, int wc, int in_lo, int in_hi, int out_lo, int out_hi) {
-  const int64_t hs = d.M / 2 + 1;
-  return static_cast<int64_t>(wc) * d.M * 8 * ((in_hi - in_lo) + (out_hi - out_lo)) +
-         (d.htab ? static_cast<int64_t>(wc) * hs * hs * 8 : 0);
+// algorithmic bytes of a column launch: the rows in and the kept rows out of the columns inside the discs,
+// plus their entries of the wavelengths' transfer tables once when the plan has them
+int64_t col_bytes(const Design& d, int w0, int wc, int in_lo, int in_hi, int out_lo, int out_hi) {
+  const int64_t hs = d.M / 2 + 1, cols = spectrum_columns(d, w0, wc);
+  return cols * 8 * ((in_hi - in_lo) + (out_hi - out_lo)) + (d.htab ? (cols + wc) / 2 * hs * 8 : 0);
 }
 
-double col_flops(const Design& d, int wc) {
-  return static_cast<double>(wc) * d.M * (2 * fft_flops(d.M) + 6.0 * d.M);
+double col_flops(const Design& d, int w0, int wc) {
+  return static_cast<double>(spectrum_columns(d, w0, wc)) * (2 * fft_flops(d.M) + 6.0 * d.M);
 }
 
 dpx_status run_col(dpx_plan* p, const Design& d, int lane, int layer, bool conj, int w0, int wc,
                    int in_lo, int in_hi, int out_lo, int out_hi, hipStream_t s) {
   const ColArgs c = col_args(p, d, lane, layer, w0, wc, in_lo, in_hi, out_lo, out_hi);
   TimedLaunch t{conj ? DPX_PASS_COL_ADJ : DPX_PASS_COL_FWD, nullptr, nullptr,
-                col_bytes(d, wc, in_lo, in_hi, out_lo, out_hi), col_flops(d, wc)};
+                col_bytes(d, w0, wc, in_lo, in_hi, out_lo, out_hi), col_flops(d, w0, wc)};
   if (in_lo == 0 && in_hi == d.N && out_lo == 0 && out_hi == d.N)
     t.instance = conj ? DPX_PASS_COL_ADJ_FULL : DPX_PASS_COL_FWD_FULL;
   DPX_TRY(timer_begin(p, s, t));
@@ -816,7 +824,7 @@ void add_row_position(dpx_plan* p, const std::vector<RowItem>& items, std::vecto
       tasks.push_back(t);
       nb.push_back(t.nblocks);
       al.push_back(1);
-      by.push_back(row_bytes(d, it.mode, d.W, nwb, false, false));
+      by.push_back(row_bytes(d, it.mode, 0, d.W, nwb, false, false, t.bins != 0));
       const bool reads_u = it.mode == dpx::ROW_FWD_FIRST || it.mode == dpx::ROW_ADJ_LAST_U;
       ub.push_back(reads_u ? 8 * static_cast<int64_t>(d.N) * d.N : 0);
       fl.push_back(row_flops(d, it.mode, d.W, it.row_hi - it.row_lo));
@@ -860,9 +868,9 @@ void add_col_position(dpx_plan* p, const std::vector<ColItem>& items, bool conj,
       // column tiles pair up on an XCD in runs of 16 blocks counted from the task's start
       // (col_block_item), which needs an even tile count
       al.push_back(t.gx % 2 == 0 ? 16 : 1);
-      by.push_back(col_bytes(d, d.W, it.in_lo, it.in_hi, it.out_lo, it.out_hi));
+      by.push_back(col_bytes(d, 0, d.W, it.in_lo, it.in_hi, it.out_lo, it.out_hi));
       ub.push_back(0);
-      fl.push_back(col_flops(d, d.W));
+      fl.push_back(col_flops(d, 0, d.W));
     }
     GroupLaunch proto{};
     proto.kind = GK_COL;
@@ -1021,6 +1029,26 @@ dpx_status build_groups(dpx_plan* p) {
   return DPX_OK;
 }
 
+// Brings the byte and operation counts of the grouped launches in line with the designs' wavelengths
+void refresh_group_work(dpx_plan* p) {
+  for (size_t k = 0; k < p->g_fwd.size(); ++k) {
+    std::vector<int> ids;
+    for (size_t i = 0; i < p->designs.size(); ++i)
+      if ((p->design_stream.empty() ? 0 : p->design_stream[i]) == static_cast<int>(k)) ids.push_back(static_cast<int>(i));
+    if (ids.empty()) continue;
+    std::vector<GroupLaunch> fwd, bwd;
+    TaskBlob blob;
+    build_group_lists(p, ids, fwd, bwd, blob);
+    for (auto* lists : {&fwd, &bwd}) {
+      auto& own = lists == &fwd ? p->g_fwd[k] : p->g_bwd[k];
+      for (size_t i = 0; i < own.size(); ++i) {
+        own[i].bytes = (*lists)[i].bytes;
+        own[i].flops = (*lists)[i].flops;
+      }
+    }
+  }
+}
+
 // Enqueues one list of grouped launches on s.  out_f: intensity (binning) or dL/dh (reduction).
 dpx_status run_groups(dpx_plan* p, const std::vector<GroupLaunch>& launches, const dpx::CallBuffers& call,
                       float* out_f, hipStream_t s) {
@@ -1074,11 +1102,11 @@ dpx_status run_lds(dpx_plan* p, const Design& d, bool adjoint, const float* h, c
   const int64_t nn = static_cast<int64_t>(d.N) * d.N;
   if (!adjoint) {
     flops += row_flops(d, dpx::ROW_FWD_FIRST, d.W, d.N) + (d.K - 1) * row_flops(d, dpx::ROW_FWD_MID, d.W, d.N) +
-             row_flops(d, dpx::ROW_FWD_LAST, d.W, d.F) + d.K * col_flops(d, d.W);
+             row_flops(d, dpx::ROW_FWD_LAST, d.W, d.F) + d.K * col_flops(d, 0, d.W);
     bytes += static_cast<int64_t>(d.W) * (d.K * nn * 8 + d.F * d.F * 8 + d.T * d.T * 4);
   } else {
     flops += row_flops(d, dpx::ROW_ADJ_SEED, d.W, d.F) + (d.K - 1) * row_flops(d, dpx::ROW_ADJ_MID, d.W, d.N) +
-             row_flops(d, dpx::ROW_ADJ_LAST, d.W, d.N) + d.K * col_flops(d, d.W);
+             row_flops(d, dpx::ROW_ADJ_LAST, d.W, d.N) + d.K * col_flops(d, 0, d.W);
     bytes += static_cast<int64_t>(d.W) * (d.K * nn * 8 + d.F * d.F * 8 + d.T * d.T * 4) +
              static_cast<int64_t>(d.nslots) * d.K * nn * 4;
   }
@@ -1415,6 +1443,7 @@ namespace {
 // table, and the transfer tables rebuilt from them when the plan keeps tables.  Synchronous.
 dpx_status upload_wavelengths(Design& d) {
   std::vector<WlConst> tab(d.W);
+  d.cols.assign(d.W + 1, 0);
   const double md = static_cast<double>(d.M) * d.dx;
   for (int w = 0; w < d.W; ++w) {
     const double lam = d.wl[w];
@@ -1427,6 +1456,7 @@ dpx_status upload_wavelengths(Design& d) {
     int k = static_cast<int>(std::sqrt(std::min(tab[w].q0, half * half + 1.0)));
     if (static_cast<double>(k) * k >= tab[w].q0) --k;  // q0 = kx^2 is outside the disc
     tab[w].radius = k;
+    d.cols[w + 1] = d.cols[w] + std::min(d.M, 2 * k + 1);
   }
   if (hipMemcpy(d.d_wl, tab.data(), d.W * sizeof(WlConst), hipMemcpyHostToDevice) != hipSuccess)
     return fail(DPX_E_DEVICE, "copy of the wavelength table failed");
@@ -1717,6 +1747,7 @@ dpx_status dpx_plan_set_wavelengths(dpx_plan* p, int32_t i, const double* wl, co
   else
     d.kappa.assign(n_wl, 0.0);
   DPX_TRY(upload_wavelengths(d));
+  if (p->timing && p->grouped) refresh_group_work(p);
   // store-mode checkpoints of an earlier forward belong to the old wavelengths
   p->fwd_valid = false;
   return ok();
@@ -2027,6 +2058,7 @@ dpx_status dpx_timing_enable(dpx_plan* p, int32_t enable) {
   p->pending.clear();
   for (auto& t : p->totals) t = PassTotals{};
   p->timing = enable != 0;
+  if (p->timing && p->grouped) refresh_group_work(p);
   return ok();
 }
 
