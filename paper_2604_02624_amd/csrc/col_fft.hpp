@@ -206,13 +206,13 @@ inline void col800_table_host(std::vector<float2>& out, const UnitRoots& u = Uni
 // ------------------------------------------------------------------------------------------
 // Register transforms
 // ------------------------------------------------------------------------------------------
-// e +- tau o for tau = c (1 + i t); MIRI: tau turned by another quarter (-i forward, +i inverse)
-template <bool INV>
+// e +- tau o for tau = c (1 + i t)
 __device__ __forceinline__ void fused_butterfly(float2 e, float2 o, float c, float t, float2& lo, float2& hi) {
   const float u = fmaf(-t, o.y, o.x), v = fmaf(t, o.x, o.y);
   lo = make_float2(fmaf(c, u, e.x), fmaf(c, v, e.y));
   hi = make_float2(fmaf(-c, u, e.x), fmaf(-c, v, e.y));
 }
+// the same for tau turned by another quarter (-i forward, +i inverse)
 template <bool INV>
 __device__ __forceinline__ void fused_butterfly_quarter(float2 e, float2 o, float c, float t, float2& lo, float2& hi) {
   const float u = fmaf(-t, o.y, o.x), v = fmaf(t, o.x, o.y);
@@ -228,7 +228,7 @@ __device__ __forceinline__ void dft_fused_join(const float2* e, const float2* o,
   for (int k = 0; k < (R > 2 ? R / 4 : 1); ++k) {
     const float2 q = p[k];
     const float t = INV ? -q.y : q.y;
-    fused_butterfly<INV>(e[k], o[k], q.x, t, v[k], v[k + R / 2]);
+    fused_butterfly(e[k], o[k], q.x, t, v[k], v[k + R / 2]);
     if constexpr (R > 2)
       fused_butterfly_quarter<INV>(e[k + R / 4], o[k + R / 4], q.x, t, v[k + R / 4], v[k + 3 * R / 4]);
   }
@@ -299,7 +299,7 @@ __device__ __forceinline__ void dft_odd(float2* v) {
       } else {
         constexpr float c = static_cast<float>(cos2pi(2 * k + 1, 2 * R));
         constexpr float t = static_cast<float>(-sin2pi(2 * k + 1, 2 * R) / c);
-        fused_butterfly<false>(e[k], o[k], c, t, v[k], v[k + R / 2]);
+        fused_butterfly(e[k], o[k], c, t, v[k], v[k + R / 2]);
         if constexpr (R != 6)
           fused_butterfly_quarter<false>(e[k + R / 4], o[k + R / 4], c, t, v[k + R / 4], v[k + 3 * R / 4]);
       }

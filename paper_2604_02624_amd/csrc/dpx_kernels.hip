@@ -659,11 +659,12 @@ bool lds_path_supported(int M, int pad) {
 // A wavelength on one CU costs no launches and no plane traffic between the passes, but takes the CU's
 // own time for all of it, so the passes win where a few wavelengths leave the other CUs idle (128
 // and 96 points) and, for the short transforms whose planes stay in the last-level cache, where
-// there are thousands.  Measured, one forward, loss and gradient of two to six layers, passes
-// against LDS-resident, us: 64 points 53 / 33 (1 wavelength), 89 / 54 (512), 180 / 169 (2048),
-// 287 / 322 (4096); 96 points 85 / 93 (32), 93 / 94 (64), 112 / 97 (128), 300 / 282 (1024), 513 / 537
-// (2048); 128 points 66 / 71 (32), 74 / 72 (64), 128 / 82 (256), 1005 / 780 (4096); 64 points without
-// padding 62 / 52 (1), 117 / 71 (256), 707 / 629 (4096), 96 without padding 83 / 166 (1), 182 / 200 (256).
+// there are thousands.  Measured, one forward, loss and gradient of two layers, passes against
+// LDS-resident, us: 64 points 44 / 30 (1 wavelength), 86 / 51 (512), 177 / 163 (2048), 276 / 304 (4096);
+// 96 points 54 / 64 (32), 59 / 64 (64), 67 / 66 (96), 134 / 104 (512), 201 / 190 (1024), 346 / 362 (2048);
+// 128 points 60 / 68 (32), 66 / 69 (64), 92 / 72 (128), 122 / 80 (256), 980 / 758 (4096); 64 points
+// without padding 41 / 36 (1), 84 / 53 (256), 443 / 435 (4096), 96 without padding 53 / 110 (1),
+// 126 / 137 (256).
 bool lds_path_preferred(int M, int pad, int wavelengths) {
   if (pad == 1) return M == 64;
   if (M == 64) return wavelengths <= 2048;

@@ -330,8 +330,9 @@ struct DFT {
 // radix plans: E registers per lane, radices of each stage (all divide E)
 // ------------------------------------------------------------------------------------------
 // SH: the exchange index i is stored at i + (i >> SH) (one padding slot every 2^SH entries),
-// RX / CX: extra slots between the exchange regions of neighbouring transforms in the row /
-// column kernels.  First chosen with a bank model of 64 four-byte banks serving 32 lanes per
+// RX / CX: extra slots between the exchange regions of neighbouring transforms in the row kernels /
+// the staged column kernels (unpadded 1024 and 1600 points, and the other radix plans of 512 and 1024;
+// the other lengths' column passes are split, col_fft.hpp).  First chosen with a bank model of 64 four-byte banks serving 32 lanes per
 // cycle.  Measured on gfx950 (bank-conflict counters of probes/lds_bank_probe.hip, which
 // writes and reads one lane-address pattern at a time), 8-byte writes follow another model:
 // 16 lanes per cycle over 32 four-byte banks, so a quarter-wavefront's 32 dwords must fall on
@@ -351,10 +352,10 @@ template <int M>
 struct Plan;
 template <> struct Plan<64>   { static constexpr int E = 8,  NST = 2, SH = 3, RX = 0, CX = 0;  static constexpr int R[4] = {8, 8, 0, 0}; };
 template <> struct Plan<96>   { static constexpr int E = 12, NST = 3, SH = 2, RX = 0, CX = 0;  static constexpr int R[4] = {4, 2, 12, 0}; };
-template <> struct Plan<128>  { static constexpr int E = 16, NST = 2, SH = 3, RX = 1, CX = 1;  static constexpr int R[4] = {16, 8, 0, 0}; };
-template <> struct Plan<192>  { static constexpr int E = 12, NST = 3, SH = 2, RX = 0, CX = 2;  static constexpr int R[4] = {12, 4, 4, 0}; };
-template <> struct Plan<256>  { static constexpr int E = 16, NST = 2, SH = 4, RX = 0, CX = 2;  static constexpr int R[4] = {16, 16, 0, 0}; };
-template <> struct Plan<384>  { static constexpr int E = 12, NST = 4, SH = 2, RX = 0, CX = 2;  static constexpr int R[4] = {12, 4, 4, 2}; };
+template <> struct Plan<128>  { static constexpr int E = 16, NST = 2, SH = 3, RX = 1, CX = 0;  static constexpr int R[4] = {16, 8, 0, 0}; };
+template <> struct Plan<192>  { static constexpr int E = 12, NST = 3, SH = 2, RX = 0, CX = 0;  static constexpr int R[4] = {12, 4, 4, 0}; };
+template <> struct Plan<256>  { static constexpr int E = 16, NST = 2, SH = 4, RX = 0, CX = 0;  static constexpr int R[4] = {16, 16, 0, 0}; };
+template <> struct Plan<384>  { static constexpr int E = 12, NST = 4, SH = 2, RX = 0, CX = 0;  static constexpr int R[4] = {12, 4, 4, 2}; };
 template <> struct Plan<512>  { static constexpr int E = 16, NST = 3, SH = 4, RX = 16, CX = 2; static constexpr int R[4] = {8, 8, 8, 0}; };
 template <> struct Plan<1024> { static constexpr int E = 16, NST = 3, SH = 4, RX = 0, CX = 4;  static constexpr int R[4] = {8, 8, 16, 0}; };
 template <> struct Plan<1600> { static constexpr int E = 20, NST = 3, SH = 4, RX = 0, CX = 0;  static constexpr int R[4] = {20, 20, 4, 0}; };

@@ -1326,12 +1326,12 @@ __global__ void __launch_bounds__(gemm_threads(M)) colgemm_kernel(ColArgs a, con
 }
 
 // ------------------------------------------------------------------------------------------
-// LDS-resident path for short transforms.  A block owns one wavelength.  Its N aperture rows
-// live in LDS with a row stride equal to a row transform's exchange region, so every row
-// transforms in place; a batch of CB columns at a time gathers its column from the rows and
-// exchanges through regions of its own.  Every step is the one the multi-kernel path takes
-// (same transforms, transmission, transfer function, products, partial-sum order), so the
-// results are the same bits.
+// LDS-resident path for short transforms.  A block owns one wavelength (the adjoint: the wavelengths of
+// one gradient slot, in turn).  Its N aperture rows live in LDS with a row stride equal to a row
+// transform's exchange region, so every row transforms in place; the columns run the split transforms in
+// place too (lds_columns).  Every step is the one the multi-kernel path takes (same transforms,
+// transmission, transfer function, products, and the same order of the gradient sums), so the results
+// are the same bits.
 // ------------------------------------------------------------------------------------------
 template <int M, int PAD>
 struct LdsGeo {
