@@ -57,7 +57,8 @@
  *     dpx_plan_destroy).  dpx_forward, dpx_loss and dpx_backward allocate no device memory
  *     (with opts.use_graph the first call per pointer set instantiates a HIP graph, and the
  *     per-pass timers create HIP events: runtime objects, not workspace).
- *   - A plan is not thread-safe; distinct plans are independent.
+ *   - A plan is not thread-safe, and its calls share its workspace: results of calls of one plan
+ *     that overlap on several streams are undefined.  Distinct plans are independent.
  */
 #ifndef DPX_H
 #define DPX_H
@@ -135,7 +136,11 @@ typedef struct dpx_opts {
   int32_t force_variant;    /* -1: automatic (autotuned if asked, else a built-in choice per
                                transform length); otherwise a column-pass variant index
                                (see dpx_variant_count / dpx_variant_name).  The transform
-                               variants (0-3) give the same results bit for bit; variant 4
+                               variants (0-3) give the same results bit for bit; they name
+                               the tile widths and transfer-function forms of the staged
+                               column passes, of which some lengths have one: 1024 padded and
+                               512 unpadded points run 8 columns whichever is asked for, 1600
+                               padded points also the mirrored form.  Variant 4
                                (DFT as complex matrix products on the FP32 matrix cores,
                                transform lengths up to 512) agrees with them to rounding.
                                DPX_E_UNSUPPORTED if the variant is not built for a design. */
@@ -246,7 +251,8 @@ dpx_status dpx_plan_destroy(dpx_plan* plan);
 int32_t dpx_radix_plan_count(int32_t M);
 const char* dpx_radix_plan_name(int32_t M, int32_t plan);
 
-/* The radix plans design `design` runs: its row passes and its column passes. */
+/* The radix plans design `design` runs: its row passes and its column passes.  Column passes of plan 0
+ * run split transforms with radices of their own, except unpadded ones of 1024 and 1600 points. */
 dpx_status dpx_plan_radix(const dpx_plan* plan, int32_t design, int32_t* row_plan, int32_t* col_plan);
 
 /* Packed-buffer offsets of design `design` (0 <= design < n_designs). */

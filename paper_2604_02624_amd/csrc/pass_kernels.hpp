@@ -843,10 +843,11 @@ __device__ __forceinline__ void col_split_body(const ColArgs& a, int bx, int by,
 
 // The same for halves of 512 points (ColSplit3): eight columns, one wavefront per column in B, the
 // halves one after the other, one wavelength per block.  Two block barriers per half, none between a
-// half's C and the next A, since a row thread's slots are its own.  Bound by vector instructions and
-// the power they draw (2.0 GHz).  Three blocks of eight wavefronts share a CU; 1024 points, 1024
-// wavelengths: 2463 us per pass against 2927 for the staged form with its two blocks (2483 and 2517
-// with two and four wavelengths per block and the next one's rows prefetched).
+// half's C and the next A, since a row thread's slots are its own.  Bound by vector issue: at four cycles
+// each and the 1.8 to 1.9 GHz that they leave the chip, the 1197 vector instructions per wavefront take the
+// whole launch (VALU busy 111 %, 88 % in the staged form).  Three blocks of eight wavefronts share a CU;
+// 1024 points, 1024 wavelengths: 2418 us per pass against 2858 for the staged form with its two blocks
+// (with one, two and four wavelengths per block and the next one's rows prefetched 2463, 2483, 2517).
 template <int M, int PAD, bool CONJ, int HM, bool FULL>
 __device__ __forceinline__ void col_split3_body(const ColArgs& a, int bx, int by, float2* tile, float2* tab) {
   using G = ColSplit3<M, PAD>;
@@ -995,11 +996,12 @@ __device__ __forceinline__ void col800_rows(const ColArgs& a, const float2* own,
   schedule_fence();
 }
 
-// The same for halves of 800 points (ColSplit800): eight columns on 256 threads.  Bound by issue
-// and by the registers: 25 inputs, 25 sums and 32 frequencies per lane hold it to 12 wavefronts per CU,
-// where the staged form ran 10 on twice the points.  128 wavelengths of the glass design's discs,
-// us per pass: staged, every frequency evaluated 1535; this form with two blocks per CU 1215, with the
-// mirrored transfer function 1080, with three blocks 1012.
+// The same for halves of 800 points (ColSplit800): eight columns on 256 threads.  Bound by vector issue and
+// by the registers: 25 inputs, 25 sums and 32 frequencies per lane hold it to 12 wavefronts per CU, where
+// the staged form ran 10 on twice the points; they issue in 93 % of the cycles (111 % with the 24
+// wavefronts of the 512-point halves) and wait for 30 % of their time.  128 wavelengths of the glass
+// design's discs, us per pass: staged, every frequency evaluated 1535; this form with two blocks per CU
+// 1215, with the mirrored transfer function 1080, with three blocks 1012.
 template <int M, int PAD, bool CONJ, int HM, bool FULL>
 __device__ __forceinline__ void col_split800_body(const ColArgs& a, int bx, int by, float2* tile) {
   using G = ColSplit800<M, PAD>;
